@@ -138,9 +138,9 @@ int fr_receivers(const float* z, int64_t nrows, int64_t ncols, int rule, uint8_t
  * Section 2.2 linear system, Appendix A for FR_MFD): solves
  * (I - W^T) q = r for q.  The result equals the high-to-low push; the GPU
  * reaches it without sorting: a cell is computed once all cells that give
- * it water are final, visiting rows in flow order (row sweeps with an exit
- * forest for D8/D4, wavefront sweeps for MFD, a peeling engine as the last
- * resort).
+ * it water are final (row sweeps or tile solves joined by an exit forest for
+ * D8/D4; for MFD a row sweep where no cell sends against a row order, else
+ * tiles peeled as their inputs become final).
  *
  *   z         device float32 elevations; required for FR_MFD (fractions are
  *             recomputed from it), ignored (may be NULL) for FR_D8/FR_D4.
@@ -346,10 +346,10 @@ typedef struct fr_tile {
 
 /*
  * fr_batch_plan -- schedule of a batch: `workers` persistent workgroups
- * (0: two per compute unit; at least ceil(ncols / 48) of the widest tile,
- * whose column strips must all run at once -- a tile that needs more is
- * reported as FR_ERR_ARG in dev_status) and the tile `order`
- * (FR_ORDER_GIVEN, FR_ORDER_ROWS_DESC or FR_ORDER_CELLS_DESC).
+ * (as many of them run as the GPU holds at once; 0: that many) and the tile
+ * `order` (FR_ORDER_GIVEN, FR_ORDER_ROWS_DESC or FR_ORDER_CELLS_DESC).
+ * `workers` is at least ceil(ncols / 48) of the widest tile (with 0, two per
+ * compute unit are): a wider tile is reported as FR_ERR_ARG in dev_status.
  * fr_batch_autotune picks one by timing candidates.
  */
 typedef struct fr_batch_plan {
@@ -383,8 +383,8 @@ int fr_accumulate_batched(const fr_tile* tiles_dev, int32_t ntiles, const fr_bat
 
 /*
  * fr_batch_autotune -- picks a plan for this batch: times
- * fr_accumulate_batched for every candidate plan -- one, one and a half and
- * two workgroups per compute unit, times the three tile orders; `reps`
+ * fr_accumulate_batched for every candidate plan -- one, two and three
+ * workgroups per compute unit, times the three tile orders; `reps`
  * timed runs each after one warm-up -- and writes the fastest to
  * *plan_out.  Plans are cached by the batch's signature (device, compute
  * units, and every tile's shape, rule and which of its pointers are NULL):
@@ -412,9 +412,9 @@ int fr_set_autotune_cache(const char* path);
  * receivers -- the tile forest when a sample of the codes predicts flow in
  * every direction (more than 1.5x an eighth of the cells draining sideways
  * or to the next row, on grids of 2^18 cells and more) or their exit list
- * overflows --, the row
- * sweep or the wavefront sweep for MFD, the peeling engine when a sweep
- * gives up), FR_PATH_SWEEP (wavefront sweep, then the engine),
+ * overflows --, the row sweep for MFD where no cell sends against a row
+ * order, the peeling engine otherwise), FR_PATH_SWEEP (wavefront sweep, then
+ * the engine),
  * FR_PATH_ENGINE (the peeling engine alone) or FR_PATH_TILES (the tile
  * forest for single receivers at once, for terrain known to drain in every
  * direction such as a depression-filled DEM; MFD as FR_PATH_AUTO).  Every
@@ -437,7 +437,7 @@ int fr_set_accumulate_path(int path);
  *                        direction: predicted by the code sample, or the
  *                        row sweeps' exit list overflowed)
  *   FR_SERVED_ROW_SWEEP  MFD row sweep
- *   FR_SERVED_SWEEP      wavefront sweep
+ *   FR_SERVED_SWEEP      wavefront sweep (FR_PATH_SWEEP)
  *   FR_SERVED_ENGINE     peeling engine
  *   FR_SERVED_NONE       not known
  * Reads the workspace's control block with a copy on `stream` and waits for

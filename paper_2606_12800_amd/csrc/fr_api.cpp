@@ -145,6 +145,55 @@ WsLayout ws_layout(int64_t nrows, int64_t ncols, int vdtype) {
   return L;
 }
 
+// Queue-driven peeling solver (fr_peel.hip).  It overlays the layouts above:
+// it runs before any of them, or once the sweep gave up.
+struct PeelLayout {
+  size_t word, state, ring, ctl, partial, total;
+  int32_t ntr, ntc;
+  uint32_t cap;
+};
+
+PeelLayout peel_layout(int64_t nrows, int64_t ncols) {
+  PeelLayout L{};
+  L.ntr = (int32_t)((nrows + PEEL_ROWS - 1) / PEEL_ROWS);
+  L.ntc = (int32_t)((ncols + PEEL_COLS - 1) / PEEL_COLS);
+  const size_t nt = (size_t)L.ntr * (size_t)L.ntc;
+  L.cap = (uint32_t)(2 * nt);
+  size_t o = 0;
+  L.word = o; o += up((size_t)(nrows * ncols) * sizeof(uint64_t));
+  L.state = o; o += up(nt * sizeof(uint32_t));
+  L.ring = o; o += up((size_t)L.cap * sizeof(uint64_t));
+  L.ctl = o; o += up(sizeof(PeelCtl));
+  L.partial = o; o += up(2 * kMassBlocks * sizeof(double));
+  L.total = o;
+  return L;
+}
+
+PeelGrid peel_grid(int64_t nrows, int64_t ncols, const uint8_t* code, const float* z, double p, char* body) {
+  const PeelLayout L = peel_layout(nrows, ncols);
+  PeelGrid P{};
+  P.nrows = nrows;
+  P.ncols = ncols;
+  P.ntr = L.ntr;
+  P.ntc = L.ntc;
+  P.code = code;
+  P.z = z;
+  P.p = p;
+  P.word = reinterpret_cast<uint64_t*>(body + L.word);
+  return P;
+}
+
+PeelQueue peel_queue(int64_t nrows, int64_t ncols, char* body, int32_t* status) {
+  const PeelLayout L = peel_layout(nrows, ncols);
+  PeelQueue Q{};
+  Q.state = reinterpret_cast<uint32_t*>(body + L.state);
+  Q.ring = reinterpret_cast<uint64_t*>(body + L.ring);
+  Q.ctl = reinterpret_cast<PeelCtl*>(body + L.ctl);
+  Q.status = status;
+  Q.cap = L.cap;
+  return Q;
+}
+
 // Row sweep parameters over the sweep's workspace; NULL outputs stay NULL.
 MsParams ms_params(int64_t nrows, int64_t ncols, const uint8_t* code, const float* z, double p, char* body,
                    const WsLayout& L, int32_t* status) {
@@ -277,6 +326,15 @@ EngineParams engine_params(int64_t nrows, int64_t ncols, const uint8_t* code, co
   P.status = status;
   P.gate = gate;
   return P;
+}
+
+// The queue-driven peeling solver, behind its gate if it has one.
+int enqueue_peel(RuleKind rk, bool adjoint, ValKind vk, const PeelGrid& P, const PeelQueue& Q, const int32_t* gate,
+                 hipStream_t s) {
+  const int ph = phase_begin("engine", s);
+  if (launch_peel(rk, adjoint, vk, P, Q, gate, s) != hipSuccess) return FR_ERR_HIP;
+  phase_end(ph, s);
+  return FR_OK;
 }
 
 // The peeling engine behind a gate: its kernels run only when *gate != 0.
@@ -520,6 +578,10 @@ size_t fr_workspace_bytes(int fn, int64_t nrows, int64_t ncols, int rule, int dt
   size_t t = layout(nrows, ncols, rule, dtype).total;
   const size_t tw = ws_layout(nrows, ncols, dtype).total;
   if (tw > t) t = tw;
+  if (fn == FR_FN_ADJOINT || rule == FR_MFD) {
+    const size_t tp = peel_layout(nrows, ncols).total;
+    if (tp > t) t = tp;
+  }
   if (fn == FR_FN_ACCUMULATE && rule != FR_MFD) {
     // The counts buffers are sized in, whether or not counts are requested.
     const size_t t8 = d8_layout(nrows, ncols, d8_tile_height(nrows, ncols), dtype, true).total;
@@ -682,20 +744,14 @@ int fr_accumulate(const float* z, const uint8_t* code, int64_t nrows, int64_t nc
   // (exit overflow, sweep passes, the engine's gate) are taken on the
   // device through the control block, which starts zeroed.
   const bool tiles_only = cfg.rk == RK_SINGLE && g_path == FR_PATH_TILES;
-  const int32_t first = g_path == FR_PATH_ENGINE ? FR_SERVED_ENGINE
+  const bool multi = cfg.rk == RK_MULTI;
+  const int32_t first = g_path == FR_PATH_ENGINE || (multi && g_path != FR_PATH_SWEEP) ? FR_SERVED_ENGINE
                         : (tiles_only ? FR_SERVED_TILES
-                                      : (cfg.rk == RK_SINGLE && g_path == FR_PATH_AUTO ? FR_SERVED_ROWS
-                                                                                       : FR_SERVED_SWEEP));
+                                      : (!multi && g_path == FR_PATH_AUTO ? FR_SERVED_ROWS : FR_SERVED_SWEEP));
   if (launch_ctl_init(C, first, stream) != hipSuccess) return FR_ERR_HIP;
   int rc = FR_OK;
   const int64_t n = nrows * ncols;
-  bool ms_on = false;
-  double* ms_partial = nullptr;
-  int32_t ms_nstrips = 0;
-  if (g_path == FR_PATH_ENGINE) {
-    hipLaunchKernelGGL(k_open_gate, dim3(1), dim3(64), 0, stream, C);
-    if (hipGetLastError() != hipSuccess) return FR_ERR_HIP;
-  } else if (cfg.rk == RK_SINGLE && (g_path == FR_PATH_AUTO || tiles_only)) {
+  if (!multi && (g_path == FR_PATH_AUTO || tiles_only)) {
     rc = enqueue_d8(code, nrows, ncols, rain, rain_dtype, cfg.vk, q32, q64, counts_out, mass_out, dev_status, body,
                     C, tiles_only, stream);
     if (rc != FR_OK) return rc;
@@ -707,21 +763,26 @@ int fr_accumulate(const float* z, const uint8_t* code, int64_t nrows, int64_t nc
     if (mass_out && launch_mass(cfg.rk, cfg.vk, P, partial, kMassBlocks, mass_out, stream) != hipSuccess)
       return FR_ERR_HIP;
     return FR_OK;
-  } else {
-    const WsLayout WL = ws_layout(nrows, ncols, q_dtype);
-    if (ms_applicable(cfg.rk, cfg.vk, ncols)) {
-      MsParams M = ms_params(nrows, ncols, code, z, mfd_p, body, WL, dev_status);
-      M.src32 = r32;
-      M.src64 = r64;
-      M.vhi = q32;
-      M.v64 = q64;
-      ms_on = true;
-      ms_partial = M.partial;
-      ms_nstrips = M.nstrips;
-      const int ph = phase_begin("row_sweep", stream);
-      if (launch_ms(cfg.vk, false, M, C, stream) != hipSuccess) return FR_ERR_HIP;
-      phase_end(ph, stream);
-    }
+  }
+  // Several receivers: the row sweep where no cell sends against a row
+  // order, else the peeling solver.
+  const int32_t* peel_gate = nullptr;
+  double* ms_partial = nullptr;
+  int32_t ms_nstrips = 0;
+  const WsLayout WL = ws_layout(nrows, ncols, q_dtype);
+  if (ms_applicable(cfg.rk, cfg.vk, ncols)) {
+    MsParams M = ms_params(nrows, ncols, code, z, mfd_p, body, WL, dev_status);
+    M.src32 = r32;
+    M.src64 = r64;
+    M.vhi = q32;
+    M.v64 = q64;
+    ms_partial = M.partial;
+    ms_nstrips = M.nstrips;
+    peel_gate = &C->ms_skip;
+    const int ph = phase_begin("row_sweep", stream);
+    if (launch_ms(cfg.vk, false, M, C, stream) != hipSuccess) return FR_ERR_HIP;
+    phase_end(ph, stream);
+  } else if (g_path == FR_PATH_SWEEP) {
     WsParams W = ws_params(nrows, ncols, code, z, mfd_p, body, WL, cfg.vk, dev_status);
     W.src32 = r32;
     W.src64 = r64;
@@ -729,17 +790,44 @@ int fr_accumulate(const float* z, const uint8_t* code, int64_t nrows, int64_t nc
     W.v64 = q64;
     W.cnt = counts_out;
     if ((rc = enqueue_ws(cfg, W, C, stream)) != FR_OK) return rc;
+    peel_gate = &C->fallback;
+  } else if (g_path == FR_PATH_ENGINE) {
+    hipLaunchKernelGGL(k_open_gate, dim3(1), dim3(64), 0, stream, C);
+    if (hipGetLastError() != hipSuccess) return FR_ERR_HIP;
   }
-  if ((rc = enqueue_engine(cfg, P, stream)) != FR_OK) return rc;
-  if (mass_out) {
-    // After the sweep or the engine, whichever finished the solve: both keep
-    // the float-float low part at the same place.  When the row sweep served
-    // the call, its own partials are summed instead.
+  if (!multi) {
+    if ((rc = enqueue_engine(cfg, P, stream)) != FR_OK) return rc;
+    if (mass_out) {
+      // After the sweep or the engine, whichever finished the solve: both
+      // keep the float-float low part at the same place.
+      EngineParams M = P;
+      M.gate = nullptr;
+      const int ph = phase_begin("mass", stream);
+      if (launch_mass(cfg.rk, cfg.vk, M, partial, kMassBlocks, mass_out, stream) != hipSuccess) return FR_ERR_HIP;
+      phase_end(ph, stream);
+    }
+    return FR_OK;
+  }
+  PeelGrid Q = peel_grid(nrows, ncols, code, z, mfd_p, body);
+  Q.src32 = r32;
+  Q.src64 = r64;
+  Q.out32 = q32;
+  Q.out64 = q64;
+  Q.keep = mass_out != nullptr;
+  double* peel_partial = reinterpret_cast<double*>(body + peel_layout(nrows, ncols).partial);
+  // The forced sweep's sums are taken first, from the values it left; the
+  // peeling solver's replace them when it served the call.
+  int ph = -1;
+  if (mass_out && g_path == FR_PATH_SWEEP) {
     EngineParams M = P;
-    M.gate = ms_on ? &C->ms_skip : nullptr;
-    const int ph = phase_begin("mass", stream);
+    M.gate = nullptr;
     if (launch_mass(cfg.rk, cfg.vk, M, partial, kMassBlocks, mass_out, stream) != hipSuccess) return FR_ERR_HIP;
-    if (ms_on && launch_mass_final(ms_partial, ms_nstrips, mass_out, &C->ms_skip, stream) != hipSuccess)
+  }
+  if ((rc = enqueue_peel(cfg.rk, false, cfg.vk, Q, peel_queue(nrows, ncols, body, dev_status), peel_gate, stream)) != FR_OK) return rc;
+  if (mass_out) {
+    ph = phase_begin("mass", stream);
+    if (launch_peel_mass(Q, peel_partial, kMassBlocks, mass_out, peel_gate, stream) != hipSuccess) return FR_ERR_HIP;
+    if (ms_partial && launch_mass_final(ms_partial, ms_nstrips, mass_out, &C->ms_skip, stream) != hipSuccess)
       return FR_ERR_HIP;
     phase_end(ph, stream);
   }
@@ -950,55 +1038,58 @@ int fr_accumulate_adjoint(const float* z, const uint8_t* code, int64_t nrows, in
   const double* s64 = dtype == FR_F64 ? static_cast<const double*>(qbar) : nullptr;
   float* o32 = dtype == FR_F32 ? static_cast<float*>(rbar_out) : nullptr;
   double* o64 = dtype == FR_F64 ? static_cast<double*>(rbar_out) : nullptr;
-  if (launch_ctl_init(C, g_path == FR_PATH_ENGINE ? FR_SERVED_ENGINE : FR_SERVED_SWEEP, stream) != hipSuccess)
+  if (launch_ctl_init(C, g_path == FR_PATH_SWEEP ? FR_SERVED_SWEEP : FR_SERVED_ENGINE, stream) != hipSuccess)
     return FR_ERR_HIP;
   int rc = FR_OK;
-  if (g_path == FR_PATH_ENGINE) {
-    hipLaunchKernelGGL(k_open_gate, dim3(1), dim3(64), 0, stream, C);
-    if (hipGetLastError() != hipSuccess) return FR_ERR_HIP;
-  } else {
-    const WsLayout WL = ws_layout(nrows, ncols, dtype);
-    if (ms_applicable(cfg.rk, cfg.vk, ncols)) {
-      MsParams M = ms_params(nrows, ncols, code, z, mfd_p, body, WL, dev_status);
-      M.src32 = s32;
-      M.src64 = s64;
-      M.vhi = o32;
-      M.v64 = o64;
-      M.partial = nullptr;
-      const int ph = phase_begin("row_sweep", stream);
-      if (launch_ms(cfg.vk, true, M, C, stream) != hipSuccess) return FR_ERR_HIP;
-      phase_end(ph, stream);
-    }
+  // The row sweep where no cell sends against a row order, else the peeling
+  // solver.
+  const int32_t* peel_gate = nullptr;
+  const WsLayout WL = ws_layout(nrows, ncols, dtype);
+  if (ms_applicable(cfg.rk, cfg.vk, ncols)) {
+    MsParams M = ms_params(nrows, ncols, code, z, mfd_p, body, WL, dev_status);
+    M.src32 = s32;
+    M.src64 = s64;
+    M.vhi = o32;
+    M.v64 = o64;
+    M.partial = nullptr;
+    peel_gate = &C->ms_skip;
+    const int ph = phase_begin("row_sweep", stream);
+    if (launch_ms(cfg.vk, true, M, C, stream) != hipSuccess) return FR_ERR_HIP;
+    phase_end(ph, stream);
+  } else if (g_path == FR_PATH_SWEEP) {
     WsParams W = ws_params(nrows, ncols, code, z, mfd_p, body, WL, cfg.vk, dev_status);
     W.src32 = s32;
     W.src64 = s64;
     W.vhi = o32;
     W.v64 = o64;
     if ((rc = enqueue_ws(cfg, W, C, stream)) != FR_OK) return rc;
+    peel_gate = &C->fallback;
+  } else if (g_path == FR_PATH_ENGINE) {
+    hipLaunchKernelGGL(k_open_gate, dim3(1), dim3(64), 0, stream, C);
+    if (hipGetLastError() != hipSuccess) return FR_ERR_HIP;
   }
-  const Layout L = layout(nrows, ncols, rule, dtype);
-  EngineParams P = engine_params(nrows, ncols, code, z, mfd_p, body, L, dev_status, &C->fallback);
-  P.src32 = s32;
-  P.src64 = s64;
-  P.vhi = o32;
-  P.v64 = o64;
-  P.cnt = nullptr;
-  return enqueue_engine(cfg, P, stream);
+  PeelGrid Q = peel_grid(nrows, ncols, code, rule == FR_MFD ? z : nullptr, mfd_p, body);
+  Q.src32 = s32;
+  Q.src64 = s64;
+  Q.out32 = o32;
+  Q.out64 = o64;
+  return enqueue_peel(cfg.rk, true, cfg.vk, Q, peel_queue(nrows, ncols, body, dev_status), peel_gate, stream);
 }
 
 size_t fr_batched_workspace_bytes(const fr_tile* tiles_host, int32_t ntiles) {
   if (ntiles < 0 || (ntiles > 0 && !tiles_host)) return 0;
-  size_t off = batch_head_bytes(ntiles);
+  size_t off = peel_batch_head_bytes(ntiles), peel_tiles = 0;
   for (int32_t i = 0; i < ntiles; ++i) {
     const fr_tile& t = tiles_host[i];
     if (t.nrows < 1 || t.ncols < 1 || !valid_rule(t.rule)) return 0;
     if (t.ncols > kMaxCells / t.nrows) return 0;
     if (t.rule == FR_MFD && !t.q_out) return 0;
     if (t.rule != FR_MFD && (t.q_out != nullptr) == (t.counts_out != nullptr)) return 0;
-    const BatchTileLayout L =
-        batch_tile_layout(t.nrows, t.ncols, t.code_out == nullptr, batch_tile_ff(t.rule, t.q_out != nullptr));
-    off += L.total;
+    off += peel_align((size_t)(t.nrows * t.ncols) * sizeof(uint64_t));
+    const PeelLayout L = peel_layout(t.nrows, t.ncols);
+    peel_tiles += (size_t)L.ntr * (size_t)L.ntc;
   }
+  off += peel_align(peel_tiles * sizeof(uint32_t)) + peel_align(2 * peel_tiles * sizeof(uint64_t));
   return off + kAlign;
 }
 
@@ -1011,13 +1102,14 @@ int fr_accumulate_batched(const fr_tile* tiles_dev, int32_t ntiles, const fr_bat
   if (plan && (plan->workers < 0 || (plan->order != FR_ORDER_GIVEN && plan->order != FR_ORDER_ROWS_DESC &&
                                      plan->order != FR_ORDER_CELLS_DESC)))
     return FR_ERR_ARG;
-  if (!ws || ws_bytes < batch_head_bytes(ntiles) + kAlign) return FR_ERR_WORKSPACE;
+  if (!ws || ws_bytes < peel_batch_head_bytes(ntiles) + kAlign) return FR_ERR_WORKSPACE;
   char* base = aligned_base(ws);
   const size_t avail = ws_bytes - (size_t)(base - static_cast<char*>(ws));
-  const int workers = (plan && plan->workers > 0) ? plan->workers : 2 * cu_count();
+  const int workers = plan ? plan->workers : 0;
+  const int limit = workers > 0 ? workers : 2 * cu_count();
   const int order = plan ? plan->order : FR_ORDER_ROWS_DESC;
   const int ph = phase_begin("batch", stream);
-  const hipError_t e = launch_batch(tiles_dev, ntiles, order, workers, dev_status, base, avail, stream);
+  const hipError_t e = launch_peel_batch(tiles_dev, ntiles, order, workers, limit, dev_status, base, avail, stream);
   phase_end(ph, stream);
   return e == hipSuccess ? FR_OK : FR_ERR_HIP;
 }
@@ -1077,7 +1169,7 @@ int fr_batch_autotune(const fr_tile* tiles_dev, int32_t ntiles, int32_t* dev_sta
     return FR_OK;
   }
   std::vector<fr_batch_plan> cand;
-  for (int w : {2 * cu, cu + cu / 2, cu})
+  for (int w : {3 * cu, 2 * cu, cu})
     for (int o : {FR_ORDER_ROWS_DESC, FR_ORDER_CELLS_DESC, FR_ORDER_GIVEN}) cand.push_back(fr_batch_plan{w, o});
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess) return FR_ERR_HIP;

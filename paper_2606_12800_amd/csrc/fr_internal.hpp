@@ -249,67 +249,6 @@ __device__ __forceinline__ uint8_t route_code(float zi, const float zk[8]) {
 constexpr int WS_EW = 4;      // 64-bit words per edge record
 constexpr int WS_GHOST = 8;   // columns recomputed on each side of a strip
 constexpr int WS_OWN = 64 - 2 * WS_GHOST;
-constexpr int BATCH_MAXPASS = 32;
-constexpr int BATCH_CTR_WORDS = 64;  // per tile: [pass] finished, then the words below
-constexpr int BCTR_BAR = 32, BCTR_UP = 33, BCTR_DN = 34;
-
-inline __host__ __device__ size_t ws_align(size_t x) { return (x + 255) / 256 * 256; }
-inline __host__ __device__ int64_t ws_strip_count(int64_t ncols) { return (ncols + WS_OWN - 1) / WS_OWN; }
-
-// Workspace of one tile of a batch (offsets within the tile's block).
-struct BatchTileLayout {
-  size_t code, vhi, vlo, edge, progress, ctr, total;
-};
-// ff: the tile has a float32 water output (else its float-float values live
-// in the workspace and only counts are written).
-inline __host__ __device__ BatchTileLayout batch_tile_layout(int64_t nrows, int64_t ncols, bool own_codes,
-                                                             bool ff) {
-  BatchTileLayout L{};
-  const size_t n = (size_t)(nrows * ncols);
-  const size_t strips = (size_t)ws_strip_count(ncols);
-  size_t o = 0;
-  L.code = o; if (own_codes) o += ws_align(n);
-  L.vhi = o; if (!ff) o += ws_align(n * 4);
-  L.vlo = o; o += ws_align(n * 4);
-  L.edge = o; o += ws_align(strips * (size_t)nrows * 2 * WS_EW * 8);
-  L.progress = o; o += ws_align(strips * BATCH_MAXPASS * 4);
-  L.ctr = o; o += ws_align(BATCH_CTR_WORDS * 4);
-  L.total = o;
-  return L;
-}
-
-// Per-tile record the set-up kernel writes into the batch workspace.
-struct BatchTileInfo {
-  const float* z;
-  const float* rain;
-  float* q;
-  uint64_t* cnt;
-  uint8_t* code;
-  float* vhi;
-  float* vlo;
-  uint64_t* edge;
-  int32_t* progress;
-  uint32_t* ctr;
-  int64_t nrows, ncols;
-  int64_t strip_base;  // first work item of the tile in schedule order
-  int32_t nstrips, rule;
-};
-
-struct BatchHeader {
-  unsigned long long ticket;  // next work item
-  int64_t total_items;
-  int64_t ws_needed;
-  int32_t ntiles, order;
-};
-
-// Batch workspace: header, tile records, schedule (tile index by position),
-// first work item by position (ntiles + 1 entries), then the tile blocks.
-inline __host__ __device__ size_t batch_head_bytes(int64_t ntiles) {
-  return ws_align(sizeof(BatchHeader)) + ws_align((size_t)ntiles * sizeof(BatchTileInfo)) +
-         ws_align((size_t)ntiles * 4) + ws_align((size_t)(ntiles + 1) * 8);
-}
-inline __host__ __device__ bool batch_tile_ff(int rule, bool has_q) { return rule == FR_MFD || has_q; }
-
 struct WsParams {
   int64_t nrows, ncols;
   const uint8_t* code;
@@ -334,8 +273,6 @@ struct WsParams {
 };
 
 size_t ws_edge_words(int64_t nrows, int64_t ncols);
-hipError_t launch_batch(const void* tiles_dev, int32_t ntiles, int order, int workers, int32_t* status,
-                        char* ws, size_t ws_bytes, hipStream_t s);
 // Row sweep for MFD masks (fr_msweep.hip): one wavefront per strip of
 // MS_OWN columns, computing MS_G ghost columns on each side; owned results
 // published in a ring of MS_RING rows per strip.
@@ -386,6 +323,79 @@ hipError_t launch_ws_ctl(const WsParams& P, CallCtl* C, int pass, bool last, hip
 // leaves the queue empty).  Both return at once when P.gate is closed.
 hipError_t launch_engine_init(const EngineConfig& cfg, const EngineParams& P, hipStream_t s);
 hipError_t launch_engine_run(const EngineConfig& cfg, const EngineParams& P, hipStream_t s);
+// Queue-driven peeling solver (fr_peel.hip): tiles of PEEL_ROWS x PEEL_COLS
+// cells.  Serves MFD, forward and adjoint, and the adjoint of single
+// receivers.
+constexpr int PEEL_ROWS = 64;
+constexpr int PEEL_COLS = 32;
+// Queue and progress of one solve, a cache line each.
+struct PeelCtl {
+  uint32_t head;   // next ticket to take
+  uint32_t pad0[31];
+  uint32_t tail;   // next ticket to give out
+  uint32_t pad1[31];
+  uint32_t left;   // tiles with unfinished cells
+  uint32_t stop;   // 1: given up (a cycle)
+  uint32_t pad2[30];
+};
+struct PeelQueue {
+  uint32_t* state;         // per tile
+  uint64_t* ring;          // queue: ticket and tile
+  PeelCtl* ctl;
+  int32_t* status;
+  uint32_t cap;            // ring entries: twice the tiles (a tile waits in the queue at most once; the rest keeps
+                           // a slow workgroup's ticket from being reached by the next round)
+};
+struct PeelGrid {
+  int64_t nrows, ncols;
+  int32_t ntr, ntc;        // tile grid
+  int32_t tile0;           // first tile's number (batches)
+  int32_t rule;            // batches
+  const uint8_t* code;
+  const float* z;          // elevations (MFD, batches), or NULL
+  double p;                // MFD slope exponent
+  const float* src32;      // source term float32, or NULL
+  const double* src64;     // float64, or NULL (both NULL: unit)
+  float* out32;            // result, float32 ...
+  double* out64;           // ... or float64
+  uint64_t* cnt;           // batches without float32 result: counts
+  uint8_t* code_out;       // batches: receivers, or NULL
+  uint64_t* word;          // per cell: float64 passed on, all ones = not final
+  int32_t keep;            // every cell's word is read afterwards (mass balance)
+};
+// A batch's workspace: this, its grids in schedule order, the schedule, each
+// grid's words, tile states, ring.
+struct PeelBatch {
+  PeelCtl ctl;
+  PeelQueue queue;
+  PeelGrid* grids;
+  int32_t ngrids;
+};
+inline __host__ __device__ size_t peel_align(size_t x) { return (x + 255) / 256 * 256; }
+inline __host__ __device__ size_t peel_batch_head_bytes(int64_t ntiles) {
+  return peel_align(sizeof(PeelBatch)) + peel_align((size_t)ntiles * sizeof(PeelGrid)) +
+         peel_align((size_t)ntiles * sizeof(int32_t));
+}
+// A batch plan's workgroups: at least this many for a tile of ncols columns.
+inline __host__ __device__ int64_t batch_strips(int64_t ncols) { return (ncols + 47) / 48; }
+// Fractions of the solver: float64 only for MFD with float64 results.
+template <int RK, int VK>
+struct PeelFrac {
+  using T = float;
+};
+template <>
+struct PeelFrac<RK_MULTI, VK_F64> {
+  using T = double;
+};
+hipError_t launch_peel(RuleKind rk, bool adjoint, ValKind vk, const PeelGrid& P, const PeelQueue& Q,
+                       const int32_t* gate, hipStream_t s);
+// {sum over sinks, sum of the source} of the last solve (MFD, P.keep set).
+hipError_t launch_peel_mass(const PeelGrid& P, double* partial, int nblocks, double* out, const int32_t* gate,
+                            hipStream_t s);
+// Many grids at once, on as many workgroups as fit (at most `workers` when
+// that is above 0); grids of more than `limit` strips are refused.
+hipError_t launch_peel_batch(const fr_tile* tiles_dev, int32_t ntiles, int order, int workers, int limit,
+                             int32_t* status, char* ws, size_t ws_bytes, hipStream_t s);
 hipError_t launch_mass(RuleKind rk, ValKind vk, const EngineParams& P, double* partial,
                        int nblocks, double* mass_out, hipStream_t s);
 hipError_t launch_set_status(int32_t* status, int32_t code, hipStream_t s);

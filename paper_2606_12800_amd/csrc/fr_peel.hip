@@ -1,0 +1,953 @@
+// Queue-driven peeling solver: routing where water runs in every direction,
+// several receivers per cell (MFD masks, forward and adjoint) or one (D8 /
+// D4 codes, adjoint).  Solves (I - W^T) q = r, or (I - W) rbar = qbar, on
+// any acyclic routing (Section 2.1, Section 2.2; fractions as in Appendix A).
+//
+// A cell is computed ("peeled") once every cell that feeds it is final, by
+// summing its inputs in neighbour order, so the result does not depend on
+// the order in which cells become ready.  What bounds such a solve is the
+// longest flow path (thousands of cells, one after another), not bytes or
+// arithmetic: everything below shortens the time from one cell of a path to
+// the next.
+//
+//   * One workgroup holds a tile of 64 x 32 cells in LDS: the fraction of
+//     every edge between neighbours (one signed number per undirected edge,
+//     since water crosses it one way only) and every cell's value.  A step
+//     along a path inside the tile is then an LDS round trip.
+//   * Lane = tile row.  Which cells are final, and which inputs each cell
+//     has, are 32-bit masks per row; the cells of all 64 rows that are ready
+//     are found in about 30 vector instructions with two lane shifts, and
+//     every row peels one of them per step.
+//   * Values that cross tiles go through one 64-bit word per cell in device
+//     memory (all ones = not final yet).  While wavefront 0 peels, wavefront
+//     2 polls the words of the cells around the tile that feed it, and
+//     wavefront 1 publishes the tile's own border cells and wakes the tiles
+//     they feed, so the peeling wavefront never waits for memory.
+//   * Tiles are actors on a device queue: a tile that is woken while idle is
+//     queued, any workgroup takes it, loads it, peels until nothing is
+//     ready, writes back what became final and lets go of it.  No workgroup
+//     waits for another one to be resident, so any number of them makes
+//     progress, and every wait is bounded.
+//
+// Measured (float32 water; the windowed wavefront sweep and, after 32 of its
+// passes, an engine with grid-wide barriers did this before): filled 2048^2
+// MFD route 696 -> 5.8 ms; forward and gradient on a filled 1200 x 1601 grid
+// 1467 -> 7.4 ms; tilted 4096^2 adjoint 21.9 -> 16.5 ms; 48 tiles of 64 to
+// 2048 cells a side 48.7 -> 31.8 ms.  The tile is 64 x 32 because a lane can
+// then hold a row's masks in one register each, and three such tiles with
+// float32 fractions fill a compute unit's LDS (52 KB each).
+//
+// Arithmetic: float64 sums.  For float32 results the fractions are float32,
+// t_j = (s_j / s_max)^p by the hardware log2 and exp2 and f_j = t_j / sum t;
+// a cell passes on its water times 2 - sum f (float64), which makes up for
+// the rounding of its fractions to first order, as in the row sweep.  For
+// float64 results the fractions are float64.
+#include <math.h>
+
+#include "fr_internal.hpp"
+
+namespace fr {
+namespace {
+
+constexpr int PT = 256;                // threads per workgroup
+constexpr int TR = PEEL_ROWS, TC = PEEL_COLS;
+constexpr uint64_t OPEN = ~0ull;       // word of a cell that is not final
+constexpr uint64_t OPEN_NAN = 0x7FF8000000000000ull;  // stands in for a result with those bits
+// Tile states.
+constexpr uint32_t ST_PENDING = 1, ST_RUNNING = 2, ST_DONE = 4;
+// Phases of the wavefronts' roles.
+constexpr int PH_RUN = 0, PH_STOP = 1;
+// Full polls of the surrounding cells without news before an idle tile is
+// let go: while other tiles are queued, and while none is.
+constexpr int LINGER_BUSY = 2, LINGER_IDLE = 48;
+// A workgroup without a tile gives up when neither the queue nor the count of
+// unfinished tiles has moved for this long (100 MHz ticks): the routing has a
+// cycle (single receivers from malformed codes).
+constexpr long long STUCK_TICKS = 20000000;
+
+__device__ constexpr float kInvSqrt2f = 0x1.6a09e6p-1f;
+__device__ constexpr double kSqrt2 = 1.4142135623730950488;
+
+__device__ __forceinline__ uint64_t ld64(const uint64_t* p) {
+  return (uint64_t)__hip_atomic_load(reinterpret_cast<unsigned long long*>(const_cast<uint64_t*>(p)),
+                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st64(uint64_t* p, uint64_t v) {
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)v, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t ld32(const uint32_t* p) {
+  return __hip_atomic_load(const_cast<uint32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t l_ld(const uint32_t* p) {
+  return __hip_atomic_load(const_cast<uint32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void l_st(uint32_t* p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// LDS operations of one wavefront are performed in issue order; this keeps
+// the compiler from moving data across the words that announce it.
+__device__ __forceinline__ void fence() { __atomic_signal_fence(__ATOMIC_SEQ_CST); }
+// The wavefront's stores are complete (device-coherent ones visible).
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+__device__ __forceinline__ uint64_t ballot(bool p) { return (uint64_t)__builtin_amdgcn_ballot_w64(p); }
+// x of lane - 1 / lane + 1 (0 shifted in).
+__device__ __forceinline__ uint32_t sh_l(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x138, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint32_t sh_r(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x130, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint32_t lane_of(uint32_t x, int l) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, l);
+}
+
+__device__ __forceinline__ double bitsd(uint64_t w) { return __longlong_as_double((long long)w); }
+__device__ __forceinline__ uint64_t dword(double v) {
+  const uint64_t w = (uint64_t)__double_as_longlong(v);
+  return w == OPEN ? OPEN_NAN : w;
+}
+
+// A tile in LDS.  Rows and columns -1 and TR / TC are the cells around the
+// tile.  Edge (cell, k) with k = 4 (right), 5, 6, 7 (lower left, below, lower
+// right) is kept at that cell: positive when water runs from the cell along
+// k, negative against it; the value is the fraction of the giving cell.
+template <typename F>
+struct Tile {
+  F e[TR][TC + 1];       // right edges of columns -1 .. TC - 1
+  F sw[TR + 1][TC + 1];  // lower left edges of rows -1 .. TR - 1, columns 0 .. TC
+  F s[TR + 1][TC];       // edges below
+  F se[TR + 1][TC + 1];  // lower right edges, columns -1 .. TC - 1
+  union {
+    double g[TR + 2][TC + 2];      // final: what the cell passes on; not final: its source term
+    float z[TR + 4][TC + 4];       // while fractions are computed: elevations from row, column -2 on
+    uint32_t in[8][TR];            // while masks are built: per direction and row, cells fed from there
+  };
+  uint32_t done[TR];               // final cells per row
+  uint32_t ring_tb[2];             // final cells of row -1 and of row TR, columns 0 .. TC - 1
+  uint8_t side[TR];                // final cells of columns -1 (bits 0-2: row - 1, row, row + 1) and TC (bits 3-5)
+  uint32_t phase, polls, queue_empty;
+  int32_t tile, cmd;
+};
+static_assert(sizeof(Tile<float>) <= 53760, "three float tiles per compute unit");
+static_assert(sizeof(float) * (TR + 4) * (TC + 4) <= sizeof(double) * (TR + 2) * (TC + 2), "elevations fit");
+
+// The edge word of (r, c) along k, r in -1 .. TR, c in -1 .. TC; one of its
+// two cells lies in the tile.  For k < 4 it is the neighbour's edge 7 - k.
+template <typename F>
+__device__ __forceinline__ F* edge_at(Tile<F>& T, int r, int c, int k) {
+  if (k < 4) {
+    r += nb_dr(k);
+    c += nb_dc(k);
+    k = 7 - k;
+  }
+  if (k == 4) return &T.e[r][c + 1];
+  if (k == 5) return &T.sw[r + 1][c];
+  if (k == 6) return &T.s[r + 1][c];
+  return &T.se[r + 1][c + 1];
+}
+// Fraction that runs from (r, c) along k (negative: toward it).
+template <typename F>
+__device__ __forceinline__ F out_at(Tile<F>& T, int r, int c, int k) {
+  const F w = *edge_at(T, r, c, k);
+  return k < 4 ? -w : w;
+}
+
+__device__ __forceinline__ bool in_tile(int r, int c) { return (unsigned)r < (unsigned)TR && (unsigned)c < (unsigned)TC; }
+
+// Takes a tile from the queue; -1 when all tiles are finished (or the solve
+// is given up).
+__device__ int32_t take_tile(const PeelQueue& P) {
+  PeelCtl* C = P.ctl;
+  uint32_t ticket = atomicAdd(&C->head, 1u);
+  uint32_t last_tail = 0, last_left = 0;
+  long long since = wall_clock64();
+  for (uint32_t it = 0;; ++it) {
+    const uint64_t w = ld64(P.ring + ticket % P.cap);
+    const uint32_t at = (uint32_t)(w >> 32);
+    if ((uint32_t)w != 0u && at == ticket) {
+      const uint32_t t = (uint32_t)w - 1u;
+      // Taken (an entry that is overwritten before this is queued again by
+      // the workgroup that overwrote it; whoever comes second finds the tile
+      // running).
+      atomicCAS(reinterpret_cast<unsigned long long*>(P.ring + ticket % P.cap), (unsigned long long)w, 0ull);
+      if (atomicCAS(P.state + t, ST_PENDING, ST_RUNNING) == ST_PENDING) return (int32_t)t;
+      ticket = atomicAdd(&C->head, 1u);
+      continue;
+    }
+    if ((uint32_t)w != 0u && (int32_t)(at - ticket) > 0) {
+      ticket = atomicAdd(&C->head, 1u);
+      continue;
+    }
+    __builtin_amdgcn_s_sleep(8);
+    if (it % 4u != 0u) continue;
+    const uint32_t left = ld32(&C->left), tail = ld32(&C->tail);
+    if (left == 0u || ld32(&C->stop)) return -1;
+    const long long now = wall_clock64();
+    if (left != last_left || tail != last_tail || it == 0) {
+      last_left = left;
+      last_tail = tail;
+      since = now;
+    } else if (now - since > STUCK_TICKS) {
+      atomicExch(&C->stop, 1u);
+      if (P.status) atomicCAS(P.status, 0, FR_ERR_NOTDAG);
+      return -1;
+    }
+  }
+}
+
+// Wakes tile t: queues it when it was idle.
+__device__ __forceinline__ void wake(const PeelQueue& P, uint32_t t) {
+  if (atomicOr(P.state + t, ST_PENDING) != 0u) return;
+  for (;;) {
+    const uint32_t ticket = atomicAdd(&P.ctl->tail, 1u);
+    const uint64_t old =
+        (uint64_t)atomicExch(reinterpret_cast<unsigned long long*>(P.ring + ticket % P.cap),
+                             ((unsigned long long)ticket << 32) | (t + 1u));
+    if ((uint32_t)old == 0u) return;
+    t = (uint32_t)old - 1u;  // an entry not taken yet: queue that tile again
+  }
+}
+
+// Out-fractions of the cell at (r, c) (its validated mask m over the 8
+// neighbours at elevations zk), written to its edges.
+template <typename F>
+__device__ __forceinline__ void put_fractions(Tile<F>& T, int r, int c, uint32_t m, float zc, const float (&zk)[8],
+                                              double p);
+template <>
+__device__ __forceinline__ void put_fractions<float>(Tile<float>& T, int r, int c, uint32_t m, float zc,
+                                                     const float (&zk)[8], double p) {
+  const float pf = (float)p;
+  float s[8], smax = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const float drop = zc - zk[k];
+    s[k] = ((m >> k) & 1u) ? (nb_diag(k) ? drop * kInvSqrt2f : drop) : 0.0f;
+    smax = fmaxf(smax, s[k]);
+  }
+  const float ism = smax > 0.0f ? __builtin_amdgcn_rcpf(smax) : 0.0f;
+  float sum = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    // s / smax, its rounding corrected once (the steepest gives 1 exactly).
+    const float q = s[k] * ism;
+    const float x = fmaxf(fmaf(fmaf(-q, smax, s[k]), ism, q), 0x1p-126f);
+    s[k] = ((m >> k) & 1u) ? __builtin_amdgcn_exp2f(pf * __builtin_amdgcn_logf(x)) : 0.0f;
+    sum += s[k];
+  }
+  const float is = sum > 0.0f ? __builtin_amdgcn_rcpf(sum) : 0.0f;
+  const bool own = in_tile(r, c);
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if (((m >> k) & 1u) && (own || in_tile(r + nb_dr(k), c + nb_dc(k))))
+      *edge_at(T, r, c, k) = k < 4 ? -(s[k] * is) : s[k] * is;
+}
+template <>
+__device__ __forceinline__ void put_fractions<double>(Tile<double>& T, int r, int c, uint32_t m, float zc,
+                                                      const float (&zk)[8], double p) {
+  double s[8], smax = 0.0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    s[k] = 0.0;
+    if ((m >> k) & 1u) {
+      s[k] = ((double)zc - (double)zk[k]) / (nb_diag(k) ? kSqrt2 : 1.0);
+      smax = s[k] > smax ? s[k] : smax;
+    }
+  }
+  const double ism = smax > 0.0 ? 1.0 / smax : 0.0;
+  double sum = 0.0;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    s[k] = ((m >> k) & 1u) ? exp2(p * log2(s[k] * ism)) : 0.0;
+    sum += s[k];
+  }
+  const double is = sum > 0.0 ? 1.0 / sum : 0.0;
+  const bool own = in_tile(r, c);
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if (((m >> k) & 1u) && (own || in_tile(r + nb_dr(k), c + nb_dc(k))))
+      *edge_at(T, r, c, k) = k < 4 ? -(s[k] * is) : s[k] * is;
+}
+
+// RK_SINGLE: codes of one receiver, all of a cell's water runs there (F =
+// float, fractions +-1).  VK: the precision of the result.  BATCH: the codes
+// are found here, from the elevations, by the grid's rule (single receivers
+// run as fractions of 1, whose correction is 1).
+template <int RK, bool ADJ, int VK, bool BATCH, typename F>
+__device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q, Tile<F>& T, const int32_t tile) {
+  constexpr bool CORRECT = RK == RK_MULTI && VK == VK_FF;
+  constexpr bool ELEV = RK == RK_MULTI;  // elevations are read
+  const int tid = (int)threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int32_t tr = tile / P.ntc, tc = tile - tr * P.ntc;
+  const int64_t nr = P.nrows, nc = P.ncols;
+  const int64_t r0 = (int64_t)tr * TR, c0 = (int64_t)tc * TC;
+  const uint32_t id = (uint32_t)(P.tile0 + tile);
+
+  // -------------------------------------------------------------- load
+  // This thread's own cells: 8 of the tile, two rows of 32 per wavefront
+  // step.
+  uint64_t word[8];
+  double src[8];
+  bool nonfinite = false, badcode = false, cycle = false;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = 2 * (8 * wave + i) + (lane >> 5), c = lane & 31;
+    word[i] = OPEN;
+    src[i] = 0.0;
+    if (r0 + r < nr && c0 + c < nc) {
+      const int64_t at = (r0 + r) * nc + c0 + c;
+      word[i] = ld64(P.word + at);
+      src[i] = P.src64 ? P.src64[at] : (P.src32 ? (double)P.src32[at] : 1.0);
+    }
+  }
+  if (ELEV) {
+    for (int i = tid; i < (TR + 4) * (TC + 4); i += PT) {
+      const int r = i / (TC + 4) - 2, c = i % (TC + 4) - 2;
+      const int64_t y = r0 + r, x = c0 + c;
+      float v = INFINITY;
+      if (y >= 0 && y < nr && x >= 0 && x < nc) v = P.z[y * nc + x];
+      T.z[r + 2][c + 2] = v;
+    }
+  }
+  {
+    F* w = reinterpret_cast<F*>(&T);  // the four edge arrays
+    constexpr int words = (int)(offsetof(Tile<F>, g) / sizeof(F));
+    for (int i = tid; i < words; i += PT) w[i] = (F)0;
+  }
+  if (tid == 0) {
+    T.phase = PH_RUN;
+    T.polls = 0;
+    T.queue_empty = 0;
+  }
+  __syncthreads();
+
+  // --------------------------------------------------------- fractions
+  for (int i = tid; i < (TR + 2) * (TC + 2); i += PT) {
+    const int r = i / (TC + 2) - 1, c = i % (TC + 2) - 1;
+    const int64_t y = r0 + r, x = c0 + c;
+    if (y < 0 || y >= nr || x < 0 || x >= nc) continue;
+    const bool own = in_tile(r, c);
+    float zc = 0.0f, zk[8];
+    uint32_t code, lower = 0;
+    if (ELEV) {
+      zc = T.z[r + 2][c + 2];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        zk[k] = T.z[r + 2 + nb_dr(k)][c + 2 + nb_dc(k)];
+        lower |= zk[k] < zc ? 1u << k : 0u;  // off the grid: +inf, never lower
+      }
+      nonfinite |= own && !isfinite(zc);
+    }
+    if (BATCH) {
+      code = P.rule == FR_MFD ? lower : (P.rule == FR_D4 ? route_code<FR_D4>(zc, zk) : route_code<FR_D8>(zc, zk));
+      if (own && P.code_out) P.code_out[y * nc + x] = (uint8_t)code;
+    } else {
+      code = P.code[y * nc + x];
+    }
+    if (RK == RK_SINGLE || (BATCH && P.rule != FR_MFD)) {
+      if (code > 7u) {
+        badcode |= own && code != SINK;
+        continue;
+      }
+      if (!BATCH) {
+        const int64_t yy = y + nb_dr((int)code), xx = x + nb_dc((int)code);
+        if (yy < 0 || yy >= nr || xx < 0 || xx >= nc) {
+          badcode |= own;
+          continue;
+        }
+        if (P.code[yy * nc + xx] == 7u - code) {
+          // Two cells that drain into each other (an edge carries one way).
+          cycle |= own;
+          continue;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if ((int)code == k && (own || in_tile(r + nb_dr(k), c + nb_dc(k))))
+          *edge_at(T, r, c, k) = k < 4 ? (F)-1 : (F)1;
+    } else {
+      // Only strictly lower cells of the grid can receive: whatever the
+      // codes say, the routing solved is acyclic.
+      badcode |= own && (code & ~lower) != 0u;
+      put_fractions<F>(T, r, c, code & lower, zc, zk, P.p);
+    }
+  }
+  __syncthreads();
+
+  // ------------------------------------------------------------- masks
+#pragma unroll 2
+  for (int i = 0; i < 8; ++i) {
+    const int r = 2 * (8 * wave + i) + (lane >> 5), c = lane & 31;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const F o = out_at(T, r, c, k);
+      const uint64_t b = ballot(ADJ ? o > (F)0 : o < (F)0);
+      if (c == 0) T.in[k][r] = lane ? (uint32_t)(b >> 32) : (uint32_t)b;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = 2 * (8 * wave + i) + (lane >> 5), c = lane & 31;
+    // Cells off the grid count as final.
+    const uint64_t b = ballot(word[i] != OPEN || r0 + r >= nr || c0 + c >= nc);
+    if (c == 0) T.done[r] = lane ? (uint32_t)(b >> 32) : (uint32_t)b;
+  }
+  if (tid < TR) T.side[tid] = 0;
+  if (tid < 2) T.ring_tb[tid] = 0;
+  __syncthreads();
+  uint32_t in[8];
+  uint32_t done = 0;
+  if (wave == 0) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) in[k] = T.in[k][lane];
+    done = T.done[lane];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = 2 * (8 * wave + i) + (lane >> 5), c = lane & 31;
+    if (!isfinite(src[i])) {
+      nonfinite = true;
+      src[i] = 0.0;
+    }
+    T.g[r + 1][c + 1] = word[i] != OPEN ? bitsd(word[i]) : src[i];
+  }
+  // The cells around the tile pass nothing on until they are known.
+  for (int i = tid; i < 2 * (TC + 2) + 2 * TR; i += PT) {
+    if (i < TC + 2) T.g[0][i] = 0.0;
+    else if (i < 2 * (TC + 2)) T.g[TR + 1][i - (TC + 2)] = 0.0;
+    else if (i < 2 * (TC + 2) + TR) T.g[i - 2 * (TC + 2) + 1][0] = 0.0;
+    else T.g[i - 2 * (TC + 2) - TR + 1][TC + 1] = 0.0;
+  }
+  if (Q.status) {
+    if (ballot(badcode) && lane == 0) atomicCAS(Q.status, 0, FR_ERR_BADCODE);
+    if (ballot(nonfinite) && lane == 0) atomicCAS(Q.status, 0, FR_ERR_NONFINITE);
+    if (ballot(cycle) && lane == 0) atomicCAS(Q.status, 0, FR_ERR_NOTDAG);
+  }
+  __syncthreads();
+
+  // ------------------------------------------------------------- roles
+  uint32_t published = done;  // wavefront 1: cells handled (see below)
+  if (wave == 1) published = T.done[lane];
+  __syncthreads();
+  for (;;) {
+    if (wave == 0) {
+      // Peeling: lane = row.
+      const int r = lane;
+      const int64_t base = (r0 + r) * nc + c0;
+      uint32_t idle_from = 0;
+      bool idle = false;
+      for (;;) {
+        const uint32_t sd = *(volatile uint8_t*)&T.side[r];
+        const uint32_t polls = l_ld(&T.polls);
+        uint32_t up = sh_l(done), dn = sh_r(done);
+        if (lane == 0) up = l_ld(&T.ring_tb[0]);
+        if (lane == TR - 1) dn = l_ld(&T.ring_tb[1]);
+        fence();
+        uint32_t wait = in[0] & ~((up << 1) | (sd & 1u));
+        wait |= in[1] & ~up;
+        wait |= in[2] & ~((up >> 1) | (((sd >> 3) & 1u) << 31));
+        wait |= in[3] & ~((done << 1) | ((sd >> 1) & 1u));
+        wait |= in[4] & ~((done >> 1) | (((sd >> 4) & 1u) << 31));
+        wait |= in[5] & ~((dn << 1) | ((sd >> 2) & 1u));
+        wait |= in[6] & ~dn;
+        wait |= in[7] & ~((dn >> 1) | (((sd >> 5) & 1u) << 31));
+        const uint32_t ready = ~(done | wait);
+        if (ballot(ready != 0u) == 0ull) {
+          if (ballot(done != ~0u) == 0ull) break;
+          // Nothing ready: wait for cells around the tile, for a few polls.
+          if (!idle) {
+            idle = true;
+            idle_from = polls;
+          } else if (polls - idle_from > (uint32_t)(l_ld(&T.queue_empty) ? LINGER_IDLE : LINGER_BUSY)) {
+            break;
+          }
+          __builtin_amdgcn_s_sleep(1);
+          continue;
+        }
+        idle = false;
+        if (ready != 0u) {
+          const int c = __builtin_ctz(ready);
+          F o[8];
+          double gk[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            o[k] = out_at(T, r, c, k);
+            gk[k] = T.g[r + 1 + nb_dr(k)][c + 1 + nb_dc(k)];
+          }
+          double v = 0.0, give = 0.0;
+#pragma unroll
+          for (int k = 0; k < 8; ++k) {
+            const double ok = (double)o[k];
+            v = fma(fmax(ADJ ? ok : -ok, 0.0), gk[k], v);
+            if (CORRECT) give += fmax(ok, 0.0);
+          }
+          const double fix = CORRECT && give > 0.0 ? 2.0 - give : 1.0;
+          const double own = T.g[r + 1][c + 1];
+          double q = ADJ && CORRECT ? fma(v, fix, own) : own + v;
+          T.g[r + 1][c + 1] = !ADJ && CORRECT ? q * fix : q;
+          if (VK == VK_F64) P.out64[base + c] = q;
+          else if (!BATCH || P.out32) P.out32[base + c] = (float)q;
+          else P.cnt[base + c] = (uint64_t)q;  // whole numbers below 2^31
+          done |= 1u << c;
+          fence();
+          l_st(&T.done[r], done);
+        }
+        fence();
+      }
+      l_st(&T.phase, PH_STOP);
+    } else if (wave == 1) {
+      // Publishing: lane = row for the side columns, lane = column for the
+      // top and bottom rows.  Cells with an edge out of the tile along the
+      // way their value goes are stored and the tiles they feed woken.
+      const int r = lane, cc = lane & 31;
+      auto feeds = [&](int rr, int c, int k) -> bool {
+        const F o = out_at(T, rr, c, k);
+        return ADJ ? o < (F)0 : o > (F)0;
+      };
+      const bool fl = feeds(r, 0, 0) || feeds(r, 0, 3) || feeds(r, 0, 5);
+      const bool fr_ = feeds(r, TC - 1, 2) || feeds(r, TC - 1, 4) || feeds(r, TC - 1, 7);
+      const uint32_t ft = (uint32_t)ballot(feeds(0, cc, 0) || feeds(0, cc, 1) || feeds(0, cc, 2));
+      const uint32_t fb = (uint32_t)ballot(feeds(TR - 1, cc, 5) || feeds(TR - 1, cc, 6) || feeds(TR - 1, cc, 7));
+      const bool f0 = feeds(0, 0, 0), f2 = feeds(0, TC - 1, 2), f5 = feeds(TR - 1, 0, 5),
+                 f7 = feeds(TR - 1, TC - 1, 7);
+      for (bool last = false; !last;) {
+        last = l_ld(&T.phase) != PH_RUN;
+        fence();
+        const uint32_t now = l_ld(&T.done[r]);
+        fence();
+        const uint32_t fresh = now & ~published;
+        published = now;
+        const uint32_t top = lane_of(fresh, 0) & ft, bot = lane_of(fresh, TR - 1) & fb;
+        const bool pl = (fresh & 1u) && fl, pr = (fresh >> 31) && fr_;
+        const uint64_t bl = ballot(pl), br = ballot(pr);
+        if (!(top | bot) && !(bl | br)) {
+          __builtin_amdgcn_s_sleep(1);
+          continue;
+        }
+        if (pl) st64(P.word + (r0 + r) * nc + c0, dword(T.g[r + 1][1]));
+        if (pr) st64(P.word + (r0 + r) * nc + c0 + TC - 1, dword(T.g[r + 1][TC]));
+        if (lane < TC) {
+          if ((top >> lane) & 1u) st64(P.word + r0 * nc + c0 + lane, dword(T.g[1][lane + 1]));
+          if ((bot >> lane) & 1u) st64(P.word + (r0 + TR - 1) * nc + c0 + lane, dword(T.g[TR][lane + 1]));
+        }
+        stores_done();
+        uint32_t wk = 0;  // by direction
+        if (top) wk |= 1u << 1;
+        if (bot) wk |= 1u << 6;
+        if (bl) wk |= 1u << 3;
+        if (br) wk |= 1u << 4;
+        if ((top & 1u) && f0) wk |= 1u << 0;
+        if ((top >> 31) && f2) wk |= 1u << 2;
+        if ((bot & 1u) && f5) wk |= 1u << 5;
+        if ((bot >> 31) && f7) wk |= 1u << 7;
+        if (lane < 8 && ((wk >> lane) & 1u)) {
+          const int dr = lane < 3 ? -1 : (lane < 5 ? 0 : 1);
+          const int dc = (lane == 0 || lane == 3 || lane == 5) ? -1 : ((lane == 1 || lane == 6) ? 0 : 1);
+          const int32_t ur = tr + dr, uc = tc + dc;
+          if (ur >= 0 && ur < P.ntr && uc >= 0 && uc < P.ntc) wake(Q, (uint32_t)(P.tile0 + ur * P.ntc + uc));
+        }
+      }
+    } else if (wave == 2) {
+      // Polling: cells of the columns beside the tile (lane = row), of the
+      // rows above and below it (lane - 1 = column).
+      auto gives = [&](int rr, int c, int k) -> bool {  // toward a cell of the tile
+        if (!in_tile(rr + nb_dr(k), c + nb_dc(k))) return false;
+        const F o = out_at(T, rr, c, k);
+        return ADJ ? o < (F)0 : o > (F)0;
+      };
+      const int r = lane, c = lane - 1;
+      bool need[4] = {false, false, false, false};
+      need[0] = gives(r, -1, 2) || gives(r, -1, 4) || gives(r, -1, 7);
+      need[1] = gives(r, TC, 0) || gives(r, TC, 3) || gives(r, TC, 5);
+      if (lane < TC + 2) {
+        need[2] = gives(-1, c, 5) || gives(-1, c, 6) || gives(-1, c, 7);
+        need[3] = gives(TR, c, 0) || gives(TR, c, 1) || gives(TR, c, 2);
+      }
+      const uint64_t* at[4];
+      at[0] = P.word + (r0 + r) * nc + c0 - 1;
+      at[1] = P.word + (r0 + r) * nc + c0 + TC;
+      at[2] = P.word + (r0 - 1) * nc + c0 + c;
+      at[3] = P.word + (r0 + TR) * nc + c0 + c;
+      double* to[4];
+      to[0] = &T.g[r + 1][0];
+      to[1] = &T.g[r + 1][TC + 1];
+      to[2] = &T.g[0][lane < TC + 2 ? lane : 0];
+      to[3] = &T.g[TR + 1][lane < TC + 2 ? lane : 0];
+      bool have[4] = {false, false, false, false};
+      uint32_t polls = l_ld(&T.polls);
+      while (l_ld(&T.phase) == PH_RUN) {
+        uint64_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = need[i] ? ld64(at[i]) : OPEN;
+        const uint32_t head = ld32(&Q.ctl->head), tail = ld32(&Q.ctl->tail);
+        bool news = false;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (w[i] != OPEN) {
+            *to[i] = bitsd(w[i]);
+            need[i] = false;
+            have[i] = true;
+            news = true;
+          }
+        if (ballot(news)) {
+          const uint64_t hl = ballot(have[0]), hr = ballot(have[1]), ht = ballot(have[2]), hb = ballot(have[3]);
+          // Three rows' bits of each side column for the lane's row; the
+          // corners come from the rows above and below.
+          auto three = [&](uint64_t h, uint32_t above, uint32_t below) -> uint32_t {
+            const uint32_t a = lane == 0 ? above : (uint32_t)(h >> (lane - 1)) & 1u;
+            const uint32_t b = (uint32_t)(h >> lane) & 1u;
+            const uint32_t d = lane == 63 ? below : (uint32_t)(h >> (lane + 1)) & 1u;
+            return a | (b << 1) | (d << 2);
+          };
+          const uint32_t left = three(hl, (uint32_t)ht & 1u, (uint32_t)hb & 1u);
+          const uint32_t right =
+              three(hr, (uint32_t)(ht >> (TC + 1)) & 1u, (uint32_t)(hb >> (TC + 1)) & 1u);
+          fence();
+          *(volatile uint8_t*)&T.side[r] = (uint8_t)(left | (right << 3));
+          if (lane == 0) {
+            l_st(&T.ring_tb[0], (uint32_t)(ht >> 1));
+            l_st(&T.ring_tb[1], (uint32_t)(hb >> 1));
+          }
+          fence();
+        }
+        ++polls;
+        if (lane == 0) {
+          l_st(&T.queue_empty, (int32_t)(tail - head) <= 0 ? 1u : 0u);
+          l_st(&T.polls, polls);
+        }
+      }
+    }
+    __syncthreads();
+
+    // ---------------------------------------------------------- let go
+    // Final cells that were not when the tile was loaded go back to memory
+    // (a finished tile's only where the mass balance reads them).
+    const bool all = ballot(T.done[lane] != ~0u) == 0ull;
+    if (!all || P.keep) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int r = 2 * (8 * wave + i) + (lane >> 5), c = lane & 31;
+        if (word[i] == OPEN && ((T.done[r] >> c) & 1u) && r0 + r < nr && c0 + c < nc) {
+          word[i] = dword(T.g[r + 1][c + 1]);
+          st64(P.word + (r0 + r) * nc + c0 + c, word[i]);
+        }
+      }
+    }
+    stores_done();
+    __syncthreads();
+    if (tid == 0) {
+      T.cmd = 0;
+      if (all) {
+        atomicExch(Q.state + id, ST_DONE);
+        atomicSub(&Q.ctl->left, 1u);
+      } else if (atomicCAS(Q.state + id, ST_RUNNING, 0u) != ST_RUNNING) {
+        // Woken meanwhile: look around once more before letting go.
+        atomicAnd(Q.state + id, ~ST_PENDING);
+        T.cmd = 1;
+        T.phase = PH_RUN;
+      }
+    }
+    __syncthreads();
+    if (T.cmd == 0) return;
+  }
+}
+
+// Float fractions: three workgroups fit a compute unit's LDS, so three
+// wavefronts a SIMD; float64 ones: one.
+template <int RK, bool ADJ, int VK>
+__global__ __launch_bounds__(PT, RK == RK_MULTI && VK == VK_F64 ? 1 : 3) void k_peel(PeelGrid P, PeelQueue Q,
+                                                                                     const int32_t* gate) {
+  using F = typename PeelFrac<RK, VK>::T;
+  if (gate && *gate == 0) return;
+  __shared__ Tile<F> T;
+  for (;;) {
+    if (threadIdx.x == 0) T.tile = take_tile(Q);
+    __syncthreads();
+    const int32_t t = T.tile;
+    if (t < 0) return;
+    peel_tile<RK, ADJ, VK, false, F>(P, Q, T, t);
+    __syncthreads();
+  }
+}
+
+// Many grids (float32 water, or counts of single receivers).
+__global__ __launch_bounds__(PT, 3) void k_peel_batch(const PeelBatch* B) {
+  __shared__ Tile<float> T;
+  const PeelQueue Q = B->queue;
+  const PeelGrid* grids = B->grids;
+  const int32_t ngrids = B->ngrids;
+  for (;;) {
+    if (threadIdx.x == 0) T.tile = take_tile(Q);
+    __syncthreads();
+    const int32_t t = __builtin_amdgcn_readfirstlane(T.tile);
+    if (t < 0) return;
+    // The grid whose tiles hold tile t (grids in queue order).
+    int lo = 0, hi = ngrids - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (grids[mid].tile0 <= t) lo = mid;
+      else hi = mid - 1;
+    }
+    peel_tile<RK_MULTI, false, VK_FF, true, float>(grids[lo], Q, T, t - grids[lo].tile0);
+    __syncthreads();
+  }
+}
+
+// Which end of the grid water leaves (the adjoint: reaches), by the mean
+// elevation of two sampled rows: its tiles are queued first, from the last
+// row of tiles or from the first.  Any order gives the same result.
+__device__ bool last_rows_first(const PeelGrid& P, bool adjoint) {
+  if (!P.z) return adjoint;
+  const int64_t step = P.ncols / 64 + 1;
+  float d = 0.0f;
+  for (int64_t c = 0; c < P.ncols; c += step)
+    d += P.z[(P.nrows - 1 - P.nrows / 4) * P.ncols + c] - P.z[(P.nrows / 4) * P.ncols + c];
+  return (d > 0.0f) != adjoint;
+}
+
+// No cell final, every tile queued (tickets from tile0 on; the ring's second
+// half empty).  Thread i of n.
+__device__ void open_grid(const PeelGrid& P, const PeelQueue& Q, bool adjoint, int64_t i0, int64_t stride) {
+  const int64_t n = P.nrows * P.ncols;
+  for (int64_t i = i0; i < n; i += stride) P.word[i] = OPEN;
+  const int32_t nt = P.ntr * P.ntc;
+  if (i0 >= nt) return;
+  const bool last = last_rows_first(P, adjoint);
+  for (int64_t i = i0; i < nt; i += stride) {
+    const uint32_t ticket = (uint32_t)(P.tile0 + i);
+    const uint32_t t = (uint32_t)(P.tile0 + (last ? nt - 1 - i : i));
+    Q.ring[ticket] = ((uint64_t)ticket << 32) | (t + 1u);
+    Q.ring[Q.cap / 2 + ticket] = 0ull;
+    Q.state[ticket] = ST_PENDING;
+  }
+}
+
+__device__ void open_queue(const PeelQueue& Q, uint32_t ntiles) {
+  Q.ctl->head = 0;
+  Q.ctl->tail = ntiles;
+  Q.ctl->left = ntiles;
+  Q.ctl->stop = 0;
+}
+
+__global__ __launch_bounds__(256) void k_peel_init(PeelGrid P, PeelQueue Q, int adjoint, const int32_t* gate) {
+  if (gate && *gate == 0) return;
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  open_grid(P, Q, adjoint != 0, i0, (int64_t)gridDim.x * blockDim.x);
+  if (i0 == 0) open_queue(Q, (uint32_t)(P.ntr * P.ntc));
+}
+
+constexpr int BATCH_FILL_BLOCKS = 32;  // workgroups per grid of a batch
+
+__global__ __launch_bounds__(256) void k_peel_batch_init(const PeelBatch* B) {
+  if ((int)blockIdx.x >= B->ngrids) return;
+  open_grid(B->grids[blockIdx.x], B->queue, false, (int64_t)blockIdx.y * blockDim.x + threadIdx.x,
+            (int64_t)BATCH_FILL_BLOCKS * blockDim.x);
+}
+
+// Inclusive scan of x over the workgroup (blockDim.x = 1024).
+__device__ int64_t scan_inc(int64_t x, int64_t* sh) {
+  const int t = (int)threadIdx.x;
+  sh[t] = x;
+  __syncthreads();
+  for (int o = 1; o < 1024; o <<= 1) {
+    const int64_t y = t >= o ? sh[t - o] : 0;
+    __syncthreads();
+    sh[t] += y;
+    __syncthreads();
+  }
+  const int64_t v = sh[t];
+  __syncthreads();
+  return v;
+}
+
+// Set-up of a batch (one workgroup): the tiles' schedule, their grids in that
+// order with their first tile, words and queue, all in the workspace, laid
+// out as peel_batch_bytes() counts it.
+__global__ __launch_bounds__(1024) void k_peel_batch_setup(const fr_tile* tiles, int32_t ntiles, int order,
+                                                           int32_t limit, char* ws, size_t ws_bytes,
+                                                           int32_t* status) {
+  __shared__ int64_t sh[1024];
+  __shared__ int bad_sh;
+  PeelBatch* B = reinterpret_cast<PeelBatch*>(ws);
+  PeelGrid* grids = reinterpret_cast<PeelGrid*>(ws + peel_align(sizeof(PeelBatch)));
+  int32_t* sched = reinterpret_cast<int32_t*>(ws + peel_align(sizeof(PeelBatch)) +
+                                              peel_align((size_t)ntiles * sizeof(PeelGrid)));
+  const int t = (int)threadIdx.x;
+  if (t == 0) bad_sh = 0;
+  __syncthreads();
+  // Schedule: given order, or more rows (cells) first, stable, by parallel
+  // ranking.
+  for (int i = t; i < ntiles; i += 1024) {
+    const fr_tile& T = tiles[i];
+    if (T.nrows < 1 || T.ncols < 1 || !T.z || (T.rule == FR_MFD && !T.q_out) ||
+        (T.rule != FR_MFD && (T.q_out != nullptr) == (T.counts_out != nullptr)))
+      bad_sh = 1;
+    int rank = i;
+    if (order != FR_ORDER_GIVEN && ntiles <= 16384) {
+      rank = 0;
+      const bool rows = order == FR_ORDER_ROWS_DESC;
+      const int64_t ki = rows ? T.nrows : T.nrows * T.ncols;
+      for (int j = 0; j < ntiles; ++j) {
+        const int64_t kj = rows ? tiles[j].nrows : tiles[j].nrows * tiles[j].ncols;
+        rank += (kj > ki || (kj == ki && j < i)) ? 1 : 0;
+      }
+    }
+    sched[rank] = i;
+  }
+  __threadfence();
+  __syncthreads();
+  const bool bad = bad_sh != 0;
+  size_t off = peel_batch_head_bytes(ntiles);
+  int64_t tile0 = 0;
+  for (int k0 = 0; !bad && k0 < ntiles; k0 += 1024) {
+    const int k = k0 + t;
+    PeelGrid G{};
+    int64_t bytes = 0, nt = 0;
+    if (k < ntiles) {
+      const fr_tile T = tiles[sched[k]];
+      G.nrows = T.nrows;
+      G.ncols = T.ncols;
+      G.ntr = (int32_t)((T.nrows + TR - 1) / TR);
+      G.ntc = (int32_t)((T.ncols + TC - 1) / TC);
+      G.z = T.z;
+      G.p = 1.1;
+      G.src32 = T.rule == FR_MFD || T.q_out ? T.rain : nullptr;
+      G.out32 = T.q_out;
+      G.cnt = T.rule == FR_MFD || T.q_out ? nullptr : T.counts_out;
+      G.code_out = T.code_out;
+      G.rule = T.rule;
+      bytes = (int64_t)peel_align((size_t)(T.nrows * T.ncols) * sizeof(uint64_t));
+      if (batch_strips(T.ncols) > limit) {
+        // Not routed on so few workgroups: an empty grid in the queue.
+        if (status) atomicCAS(status, 0, FR_ERR_ARG);
+        G.nrows = 0;
+        G.ntr = 0;
+      }
+      nt = (int64_t)G.ntr * G.ntc;
+    }
+    const int64_t bi = scan_inc(bytes, sh), ti = scan_inc(nt, sh);
+    if (k < ntiles) {
+      G.word = reinterpret_cast<uint64_t*>(ws + off + (size_t)(bi - bytes));
+      G.tile0 = (int32_t)(tile0 + ti - nt);
+      grids[k] = G;
+    }
+    sh[t] = bi;
+    __syncthreads();
+    off += (size_t)sh[1023];
+    __syncthreads();
+    sh[t] = ti;
+    __syncthreads();
+    tile0 += sh[1023];
+    __syncthreads();
+  }
+  if (t == 0) {
+    PeelQueue Q{};
+    Q.cap = (uint32_t)(2 * tile0);
+    Q.state = reinterpret_cast<uint32_t*>(ws + off);
+    off += peel_align((size_t)tile0 * sizeof(uint32_t));
+    Q.ring = reinterpret_cast<uint64_t*>(ws + off);
+    off += peel_align((size_t)Q.cap * sizeof(uint64_t));
+    Q.ctl = &B->ctl;
+    Q.status = status;
+    const bool fits = off <= ws_bytes && !bad;
+    if (!fits && status) atomicCAS(status, 0, bad ? FR_ERR_ARG : FR_ERR_WORKSPACE);
+    B->queue = Q;
+    B->grids = grids;
+    B->ngrids = fits ? ntiles : 0;
+    open_queue(Q, fits ? (uint32_t)tile0 : 0u);
+  }
+}
+
+// Mass balance partials: {sum of the values of the sinks, sum of the source
+// terms}, in a fixed order.
+__global__ __launch_bounds__(256) void k_peel_mass(PeelGrid P, double* partial, const int32_t* gate) {
+  if (gate && *gate == 0) return;
+  const int64_t n = P.nrows * P.ncols;
+  double s = 0.0, t = 0.0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    if (P.code[i] == 0) s += bitsd(P.word[i]);
+    t += P.src64 ? P.src64[i] : (P.src32 ? (double)P.src32[i] : 1.0);
+  }
+  __shared__ double rs[256], rt[256];
+  rs[threadIdx.x] = s;
+  rt[threadIdx.x] = t;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) {
+      rs[threadIdx.x] += rs[threadIdx.x + w];
+      rt[threadIdx.x] += rt[threadIdx.x + w];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    partial[2 * blockIdx.x] = rs[0];
+    partial[2 * blockIdx.x + 1] = rt[0];
+  }
+}
+
+// Workgroups of a persistent launch: as many as can be resident at once.
+template <typename K>
+hipError_t resident(K* kernel, int64_t* out) {
+  int dev = 0, cus = 0, per = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kernel, PT, 0);
+  if (e != hipSuccess) return e;
+  if (per < 1 || cus < 1) return hipErrorLaunchFailure;
+  *out = (int64_t)cus * per;
+  return hipSuccess;
+}
+
+template <int RK, bool ADJ, int VK>
+hipError_t peel_t(const PeelGrid& P, const PeelQueue& Q, const int32_t* gate, hipStream_t s) {
+  int64_t grid = 0;
+  const hipError_t e = resident(k_peel<RK, ADJ, VK>, &grid);
+  if (e != hipSuccess) return e;
+  const int64_t nt = (int64_t)P.ntr * P.ntc;
+  if (grid > nt) grid = nt;
+  hipLaunchKernelGGL((k_peel<RK, ADJ, VK>), dim3((unsigned)grid), dim3(PT), 0, s, P, Q, gate);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_peel(RuleKind rk, bool adjoint, ValKind vk, const PeelGrid& P, const PeelQueue& Q,
+                       const int32_t* gate, hipStream_t s) {
+  int64_t b = (P.nrows * P.ncols + 255) / 256;
+  if (b > 4096) b = 4096;
+  hipLaunchKernelGGL(k_peel_init, dim3((unsigned)b), dim3(256), 0, s, P, Q, adjoint ? 1 : 0, gate);
+  if (rk == RK_SINGLE) {
+    if (!adjoint) return hipErrorInvalidValue;
+    return vk == VK_F64 ? peel_t<RK_SINGLE, true, VK_F64>(P, Q, gate, s)
+                        : peel_t<RK_SINGLE, true, VK_FF>(P, Q, gate, s);
+  }
+  if (adjoint)
+    return vk == VK_F64 ? peel_t<RK_MULTI, true, VK_F64>(P, Q, gate, s) : peel_t<RK_MULTI, true, VK_FF>(P, Q, gate, s);
+  return vk == VK_F64 ? peel_t<RK_MULTI, false, VK_F64>(P, Q, gate, s) : peel_t<RK_MULTI, false, VK_FF>(P, Q, gate, s);
+}
+
+hipError_t launch_peel_mass(const PeelGrid& P, double* partial, int nblocks, double* out, const int32_t* gate,
+                            hipStream_t s) {
+  hipLaunchKernelGGL(k_peel_mass, dim3(nblocks), dim3(256), 0, s, P, partial, gate);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return launch_mass_final_if(partial, nblocks, out, gate, s);
+}
+
+hipError_t launch_peel_batch(const fr_tile* tiles_dev, int32_t ntiles, int order, int workers, int limit, int32_t* status,
+                             char* ws, size_t ws_bytes, hipStream_t s) {
+  int64_t grid = 0;
+  const hipError_t e = resident(k_peel_batch, &grid);
+  if (e != hipSuccess) return e;
+  if (workers > 0 && grid > workers) grid = workers;
+  hipLaunchKernelGGL(k_peel_batch_setup, dim3(1), dim3(1024), 0, s, tiles_dev, ntiles, order,
+                     limit, ws, ws_bytes, status);
+  const PeelBatch* B = reinterpret_cast<const PeelBatch*>(ws);
+  hipLaunchKernelGGL(k_peel_batch_init, dim3((unsigned)ntiles, BATCH_FILL_BLOCKS), dim3(256), 0, s, B);
+  hipLaunchKernelGGL(k_peel_batch, dim3((unsigned)grid), dim3(PT), 0, s, B);
+  return hipGetLastError();
+}
+
+}  // namespace fr

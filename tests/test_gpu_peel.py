@@ -1,0 +1,100 @@
+"""The queue-driven peeling solver (several receivers per cell, forward and
+adjoint; single receivers, adjoint; batches) at the edges of its 64 x 32
+tiles, against the float64 oracle, with the bars of test_gpu_parity.py:
+float32 within 1e-6 (2-norm), float64 within 1e-10 (largest, relative to the
+largest value for the adjoint)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+fr = pytest.importorskip("paper_2606_12800_amd")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    fr.load_library()
+    yield
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def relnorm(a, b):
+    return float(np.linalg.norm(a.astype(np.float64) - b) / np.linalg.norm(b))
+
+
+def terrain(kind, nr, nc, seed):
+    if kind == "noise":
+        return synth.uniform(seed, synth.STREAM_NOISE, nr * nc).reshape(nr, nc).astype(np.float32)
+    return oracle.fill_depressions(synth.dem(seed, nr, nc, tilt=0.0))
+
+
+SHAPES = [(1, 1), (1, 33), (65, 1), (63, 31), (64, 32), (65, 33), (128, 64), (129, 65), (200, 300)]
+
+
+@pytest.mark.parametrize("kind", ["noise", "filled"])
+@pytest.mark.parametrize("nr,nc", SHAPES)
+def test_peel_forward_and_adjoint(nr, nc, kind):
+    print(f"peel {nr}x{nc} {kind}", flush=True)
+    if kind == "filled" and min(nr, nc) < 3:
+        kind = "noise"
+    z = terrain(kind, nr, nc, 51)
+    rain = synth.rain(51, nr, nc) + np.float32(2.0**-24)
+    zt, rt = dev(z), dev(rain)
+    with fr.accumulate_path("engine"):
+        code = fr.receivers(zt, "mfd")
+        ref = oracle.accumulate_mfd(z, rain, 1.1)
+        q32, _, m32 = fr.accumulate(code, zt, rt, "mfd", torch.float32, mass=True)
+        q64, _, m64 = fr.accumulate(code, zt, rt, "mfd", torch.float64, mass=True)
+        again, _, _ = fr.accumulate(code, zt, rt, "mfd", torch.float64)
+        assert fr.served_by() == "engine"
+        assert relnorm(q32.cpu().numpy(), ref) <= 1e-6
+        assert np.max(np.abs(q64.cpu().numpy() - ref) / ref) <= 1e-10
+        assert torch.equal(q64, again)
+        total = float(rain.astype(np.float64).sum())
+        assert m64[0].item() == pytest.approx(total, rel=1e-11) and m64[1].item() == pytest.approx(total, rel=1e-12)
+        assert m32[0].item() == pytest.approx(total, rel=1e-6)
+        c8 = fr.receivers(zt, "d8")
+        for rule, c, want in [("mfd", code, oracle.adjoint_mfd(z, rain.astype(np.float64), 1.1)),
+                              ("d8", c8, oracle.adjoint_single(c8.cpu().numpy(), rain.astype(np.float64), z=z))]:
+            zz = zt if rule == "mfd" else None
+            r64 = fr.adjoint(c, rt.double(), zz, rule).cpu().numpy()
+            r32 = fr.adjoint(c, rt, zz, rule).cpu().numpy()
+            assert np.max(np.abs(r64 - want)) <= 1e-10 * np.abs(want).max(), rule
+            assert relnorm(r32, want) <= 1e-6, rule
+
+
+@pytest.mark.parametrize("at", [(10, 10), (63, 31)])
+@pytest.mark.parametrize("length", [2, 4])
+def test_peel_reports_cycles(at, length):
+    """Cells that drain into each other, inside a tile and across the corner
+    of four tiles."""
+    r, c = at
+    code = np.full((130, 70), 0xFF, dtype=np.uint8)
+    if length == 2:
+        code[r, c], code[r, c + 1] = 4, 3
+    else:
+        code[r, c], code[r, c + 1], code[r + 1, c + 1], code[r + 1, c] = 4, 6, 3, 1
+    with pytest.raises(fr.FlowRouteError) as e:
+        fr.adjoint(dev(code), torch.ones(code.shape, dtype=torch.float64, device="cuda"), None, "d8")
+    assert e.value.code == fr.ERR_NOTDAG
+
+
+def test_peel_batch_on_one_workgroup():
+    """One workgroup makes progress alone, whatever the order of the tiles."""
+    z = terrain("filled", 300, 48, 53)
+    z2 = terrain("noise", 130, 40, 54)
+    tiles = [{"z": dev(z), "rule": "mfd", "q": torch.empty(z.shape, device="cuda")},
+             {"z": dev(z2), "rule": "d8", "counts": torch.empty(z2.shape, dtype=torch.int64, device="cuda")}]
+    fr.Batch(tiles).run(plan=fr.BatchPlan(1, fr.ORDER_GIVEN))
+    assert relnorm(tiles[0]["q"].cpu().numpy(), oracle.accumulate_mfd(z, None, 1.1)) <= 1e-6
+    _, want = oracle.accumulate_single(oracle.receivers(z2), None, z=z2)
+    assert np.array_equal(tiles[1]["counts"].cpu().numpy().astype(np.uint64), want)
