@@ -153,10 +153,11 @@ struct PeelLayout {
   uint32_t cap;
 };
 
-PeelLayout peel_layout(int64_t nrows, int64_t ncols) {
+// frac64: float64 fractions (MFD with float64 results).
+PeelLayout peel_layout(int64_t nrows, int64_t ncols, bool frac64) {
   PeelLayout L{};
   L.ntr = (int32_t)((nrows + PEEL_ROWS - 1) / PEEL_ROWS);
-  L.ntc = (int32_t)((ncols + PEEL_COLS - 1) / PEEL_COLS);
+  L.ntc = (int32_t)((ncols + peel_cols(frac64) - 1) / peel_cols(frac64));
   const size_t nt = (size_t)L.ntr * (size_t)L.ntc;
   L.cap = (uint32_t)(2 * nt);
   size_t o = 0;
@@ -169,8 +170,8 @@ PeelLayout peel_layout(int64_t nrows, int64_t ncols) {
   return L;
 }
 
-PeelGrid peel_grid(int64_t nrows, int64_t ncols, const uint8_t* code, const float* z, double p, char* body) {
-  const PeelLayout L = peel_layout(nrows, ncols);
+PeelGrid peel_grid(int64_t nrows, int64_t ncols, const uint8_t* code, const float* z, double p, char* body,
+                   const PeelLayout& L) {
   PeelGrid P{};
   P.nrows = nrows;
   P.ncols = ncols;
@@ -183,8 +184,7 @@ PeelGrid peel_grid(int64_t nrows, int64_t ncols, const uint8_t* code, const floa
   return P;
 }
 
-PeelQueue peel_queue(int64_t nrows, int64_t ncols, char* body, int32_t* status) {
-  const PeelLayout L = peel_layout(nrows, ncols);
+PeelQueue peel_queue(char* body, const PeelLayout& L, int32_t* status) {
   PeelQueue Q{};
   Q.state = reinterpret_cast<uint32_t*>(body + L.state);
   Q.ring = reinterpret_cast<uint64_t*>(body + L.ring);
@@ -579,7 +579,7 @@ size_t fr_workspace_bytes(int fn, int64_t nrows, int64_t ncols, int rule, int dt
   const size_t tw = ws_layout(nrows, ncols, dtype).total;
   if (tw > t) t = tw;
   if (fn == FR_FN_ADJOINT || rule == FR_MFD) {
-    const size_t tp = peel_layout(nrows, ncols).total;
+    const size_t tp = peel_layout(nrows, ncols, rule == FR_MFD && dtype == FR_F64).total;
     if (tp > t) t = tp;
   }
   if (fn == FR_FN_ACCUMULATE && rule != FR_MFD) {
@@ -808,13 +808,14 @@ int fr_accumulate(const float* z, const uint8_t* code, int64_t nrows, int64_t nc
     }
     return FR_OK;
   }
-  PeelGrid Q = peel_grid(nrows, ncols, code, z, mfd_p, body);
+  const PeelLayout PL = peel_layout(nrows, ncols, cfg.vk == VK_F64);
+  PeelGrid Q = peel_grid(nrows, ncols, code, z, mfd_p, body, PL);
   Q.src32 = r32;
   Q.src64 = r64;
   Q.out32 = q32;
   Q.out64 = q64;
   Q.keep = mass_out != nullptr;
-  double* peel_partial = reinterpret_cast<double*>(body + peel_layout(nrows, ncols).partial);
+  double* peel_partial = reinterpret_cast<double*>(body + PL.partial);
   // The forced sweep's sums are taken first, from the values it left; the
   // peeling solver's replace them when it served the call.
   int ph = -1;
@@ -823,7 +824,7 @@ int fr_accumulate(const float* z, const uint8_t* code, int64_t nrows, int64_t nc
     M.gate = nullptr;
     if (launch_mass(cfg.rk, cfg.vk, M, partial, kMassBlocks, mass_out, stream) != hipSuccess) return FR_ERR_HIP;
   }
-  if ((rc = enqueue_peel(cfg.rk, false, cfg.vk, Q, peel_queue(nrows, ncols, body, dev_status), peel_gate, stream)) != FR_OK) return rc;
+  if ((rc = enqueue_peel(cfg.rk, false, cfg.vk, Q, peel_queue(body, PL, dev_status), peel_gate, stream)) != FR_OK) return rc;
   if (mass_out) {
     ph = phase_begin("mass", stream);
     if (launch_peel_mass(Q, peel_partial, kMassBlocks, mass_out, peel_gate, stream) != hipSuccess) return FR_ERR_HIP;
@@ -1068,12 +1069,13 @@ int fr_accumulate_adjoint(const float* z, const uint8_t* code, int64_t nrows, in
     hipLaunchKernelGGL(k_open_gate, dim3(1), dim3(64), 0, stream, C);
     if (hipGetLastError() != hipSuccess) return FR_ERR_HIP;
   }
-  PeelGrid Q = peel_grid(nrows, ncols, code, rule == FR_MFD ? z : nullptr, mfd_p, body);
+  const PeelLayout PL = peel_layout(nrows, ncols, rule == FR_MFD && dtype == FR_F64);
+  PeelGrid Q = peel_grid(nrows, ncols, code, rule == FR_MFD ? z : nullptr, mfd_p, body, PL);
   Q.src32 = s32;
   Q.src64 = s64;
   Q.out32 = o32;
   Q.out64 = o64;
-  return enqueue_peel(cfg.rk, true, cfg.vk, Q, peel_queue(nrows, ncols, body, dev_status), peel_gate, stream);
+  return enqueue_peel(cfg.rk, true, cfg.vk, Q, peel_queue(body, PL, dev_status), peel_gate, stream);
 }
 
 size_t fr_batched_workspace_bytes(const fr_tile* tiles_host, int32_t ntiles) {
@@ -1086,7 +1088,7 @@ size_t fr_batched_workspace_bytes(const fr_tile* tiles_host, int32_t ntiles) {
     if (t.rule == FR_MFD && !t.q_out) return 0;
     if (t.rule != FR_MFD && (t.q_out != nullptr) == (t.counts_out != nullptr)) return 0;
     off += peel_align((size_t)(t.nrows * t.ncols) * sizeof(uint64_t));
-    const PeelLayout L = peel_layout(t.nrows, t.ncols);
+    const PeelLayout L = peel_layout(t.nrows, t.ncols, false);
     peel_tiles += (size_t)L.ntr * (size_t)L.ntc;
   }
   off += peel_align(peel_tiles * sizeof(uint32_t)) + peel_align(2 * peel_tiles * sizeof(uint64_t));

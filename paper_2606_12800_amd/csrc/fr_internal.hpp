@@ -323,11 +323,12 @@ hipError_t launch_ws_ctl(const WsParams& P, CallCtl* C, int pass, bool last, hip
 // leaves the queue empty).  Both return at once when P.gate is closed.
 hipError_t launch_engine_init(const EngineConfig& cfg, const EngineParams& P, hipStream_t s);
 hipError_t launch_engine_run(const EngineConfig& cfg, const EngineParams& P, hipStream_t s);
-// Queue-driven peeling solver (fr_peel.hip): tiles of PEEL_ROWS x PEEL_COLS
-// cells.  Serves MFD, forward and adjoint, and the adjoint of single
-// receivers.
-constexpr int PEEL_ROWS = 64;
-constexpr int PEEL_COLS = 32;
+// Queue-driven peeling solver (fr_peel.hip): tiles of PEEL_ROWS x
+// peel_cols() cells.  Serves MFD, forward and adjoint, and the adjoint of
+// single receivers.  Tiles with float64 fractions are a little narrower, so
+// that two of them fit a compute unit's LDS.
+constexpr int PEEL_ROWS = 32;
+inline __host__ __device__ constexpr int peel_cols(bool frac64) { return frac64 ? 58 : 64; }
 // Queue and progress of one solve, a cache line each.
 struct PeelCtl {
   uint32_t head;   // next ticket to take

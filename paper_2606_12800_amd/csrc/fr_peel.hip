@@ -10,19 +10,24 @@
 // arithmetic: everything below shortens the time from one cell of a path to
 // the next.
 //
-//   * One workgroup holds a tile of 64 x 32 cells in LDS: the fraction of
+//   * One workgroup holds a tile of 32 x 64 cells in LDS: the fraction of
 //     every edge between neighbours (one signed number per undirected edge,
 //     since water crosses it one way only) and every cell's value.  A step
 //     along a path inside the tile is then an LDS round trip.
-//   * Lane = tile row.  Which cells are final, and which inputs each cell
-//     has, are 32-bit masks per row; the cells of all 64 rows that are ready
-//     are found in about 30 vector instructions with two lane shifts, and
-//     every row peels one of them per step.
+//   * A lane holds one cell of every tile row: lane (2 r + c) mod 64 holds
+//     cell (r, c) as bit r.  Which cells are final, and which inputs each
+//     cell has, are then 32-bit masks per lane, the neighbours' masks are
+//     lane rotations, all ready cells are found in about 30 vector
+//     instructions, and each lane peels one of them per step.  The cells of a
+//     row, of a column and of either diagonal lie in different lanes, so the
+//     cells that become ready together mostly do too (with a lane per row a
+//     step peeled 3 cells of a grid that drains along its columns).
 //   * Values that cross tiles go through one 64-bit word per cell in device
-//     memory (all ones = not final yet).  While wavefront 0 peels, wavefront
-//     2 polls the words of the cells around the tile that feed it, and
-//     wavefront 1 publishes the tile's own border cells and wakes the tiles
-//     they feed, so the peeling wavefront never waits for memory.
+//     memory (all ones = not final yet).  While one wavefront peels, another
+//     polls the words of the cells around the tile that feed it, and a third
+//     publishes the tile's own border cells and wakes the tiles they feed, so
+//     the peeling wavefront never waits for memory.  The peeling wavefronts
+//     of the workgroups on a compute unit run on different SIMDs.
 //   * Tiles are actors on a device queue: a tile that is woken while idle is
 //     queued, any workgroup takes it, loads it, peels until nothing is
 //     ready, writes back what became final and lets go of it.  No workgroup
@@ -31,11 +36,19 @@
 //
 // Measured (float32 water; the windowed wavefront sweep and, after 32 of its
 // passes, an engine with grid-wide barriers did this before): filled 2048^2
-// MFD route 696 -> 5.8 ms; forward and gradient on a filled 1200 x 1601 grid
-// 1467 -> 7.4 ms; tilted 4096^2 adjoint 21.9 -> 16.5 ms; 48 tiles of 64 to
-// 2048 cells a side 48.7 -> 31.8 ms.  The tile is 64 x 32 because a lane can
-// then hold a row's masks in one register each, and three such tiles with
-// float32 fractions fill a compute unit's LDS (52 KB each).
+// MFD route 731 -> 3.8 ms; forward and gradient on a filled 1200 x 1601 grid
+// 1203 -> 4.5 ms; tilted 4096^2 adjoint 21.5 -> 11.8 ms; 48 tiles of 64 to
+// 2048 cells a side 48.0 -> 15.4 ms.  A step takes 0.35 to 0.4 us (a chain of
+// lane rotations, 17 LDS reads and a sum of eight products), a value's way to
+// the next tile about 3 us, loading a tile 15 to 25 us.  Against that: with
+// the peeling wavefronts left on one SIMD a step of three workgroups on a
+// compute unit took 1.0 us; tiles let go after 2 polls without news instead
+// of 32 were loaded up to 4 times as often (48 tiles: 30 ms); a queue for
+// each XCD with blocks of neighbouring tiles was slower throughout (raw
+// 4096^2 1.7 -> 16 ms: neighbours were in LDS together less often, and a
+// value's way was no shorter).  The tile is 32 x 64 because a row of it is
+// then two full lines of every input, and because three such tiles with
+// float32 fractions fill a compute unit's LDS (53 KB each).
 //
 // Arithmetic: float64 sums.  For float32 results the fractions are float32,
 // t_j = (s_j / s_max)^p by the hardware log2 and exp2 and f_j = t_j / sum t;
@@ -50,16 +63,15 @@ namespace fr {
 namespace {
 
 constexpr int PT = 256;                // threads per workgroup
-constexpr int TR = PEEL_ROWS, TC = PEEL_COLS;
+constexpr int TR = PEEL_ROWS;
 constexpr uint64_t OPEN = ~0ull;       // word of a cell that is not final
-constexpr uint64_t OPEN_NAN = 0x7FF8000000000000ull;  // stands in for a result with those bits
 // Tile states.
 constexpr uint32_t ST_PENDING = 1, ST_RUNNING = 2, ST_DONE = 4;
 // Phases of the wavefronts' roles.
 constexpr int PH_RUN = 0, PH_STOP = 1;
 // Full polls of the surrounding cells without news before an idle tile is
 // let go: while other tiles are queued, and while none is.
-constexpr int LINGER_BUSY = 2, LINGER_IDLE = 48;
+constexpr int LINGER_BUSY = 32, LINGER_IDLE = 96;
 // A workgroup without a tile gives up when neither the queue nor the count of
 // unfinished tiles has moved for this long (100 MHz ticks): the routing has a
 // cycle (single receivers from malformed codes).
@@ -92,21 +104,20 @@ __device__ __forceinline__ void fence() { __atomic_signal_fence(__ATOMIC_SEQ_CST
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 __device__ __forceinline__ uint64_t ballot(bool p) { return (uint64_t)__builtin_amdgcn_ballot_w64(p); }
-// x of lane - 1 / lane + 1 (0 shifted in).
-__device__ __forceinline__ uint32_t sh_l(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x138, 0xF, 0xF, true);
+// x of lane - 1 / lane + 1 (mod 64).
+__device__ __forceinline__ uint32_t from_below(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x13C, 0xF, 0xF, false);
 }
-__device__ __forceinline__ uint32_t sh_r(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x130, 0xF, 0xF, true);
-}
-__device__ __forceinline__ uint32_t lane_of(uint32_t x, int l) {
-  return (uint32_t)__builtin_amdgcn_readlane((int)x, l);
+__device__ __forceinline__ uint32_t from_above(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x134, 0xF, 0xF, false);
 }
 
 __device__ __forceinline__ double bitsd(uint64_t w) { return __longlong_as_double((long long)w); }
 __device__ __forceinline__ uint64_t dword(double v) {
+  // A result whose upper half has those bits (a NaN) gives way to another NaN.
   const uint64_t w = (uint64_t)__double_as_longlong(v);
-  return w == OPEN ? OPEN_NAN : w;
+  const uint32_t hi = (uint32_t)(w >> 32);
+  return ((uint64_t)(hi == ~0u ? 0x7FF80000u : hi) << 32) | (uint32_t)w;
 }
 
 // A tile in LDS.  Rows and columns -1 and TR / TC are the cells around the
@@ -115,46 +126,61 @@ __device__ __forceinline__ uint64_t dword(double v) {
 // k, negative against it; the value is the fraction of the giving cell.
 template <typename F>
 struct Tile {
-  F e[TR][TC + 1];       // right edges of columns -1 .. TC - 1
-  F sw[TR + 1][TC + 1];  // lower left edges of rows -1 .. TR - 1, columns 0 .. TC
-  F s[TR + 1][TC];       // edges below
-  F se[TR + 1][TC + 1];  // lower right edges, columns -1 .. TC - 1
+  static constexpr int TC = peel_cols(sizeof(F) == 8);
+  static constexpr int W = TC + 2;          // row pitch, from column -1 on
+  static constexpr int PLANE = (TR + 1) * W;  // one direction's edges, from row -1 on (right edges: from row 0)
+  F edge[4 * PLANE - W];
   union {
-    double g[TR + 2][TC + 2];      // final: what the cell passes on; not final: its source term
-    float z[TR + 4][TC + 4];       // while fractions are computed: elevations from row, column -2 on
-    uint32_t in[8][TR];            // while masks are built: per direction and row, cells fed from there
+    double g[TR + 2][W];           // final: what the cell passes on; not final: its source term
+    struct {                       // while fractions are computed:
+      float z[TR + 4][TC + 4];     // elevations from row, column -2 on,
+      uint8_t code[TR + 2][W];     // codes from row, column -1 on
+    };
+    uint8_t mask[11][64][4];       // while masks are built: a byte per wavefront and lane
   };
-  uint32_t done[TR];               // final cells per row
-  uint32_t ring_tb[2];             // final cells of row -1 and of row TR, columns 0 .. TC - 1
-  uint8_t side[TR];                // final cells of columns -1 (bits 0-2: row - 1, row, row + 1) and TC (bits 3-5)
+  uint32_t done[64];               // final cells per lane (while loading: per row, two words)
+  uint32_t wait[64];               // cells with an input from outside that is not final, per lane
   uint32_t phase, polls, queue_empty;
   int32_t tile, cmd;
+  int32_t simd[5];                 // the wavefronts' SIMDs, the workgroup's slot
 };
 static_assert(sizeof(Tile<float>) <= 53760, "three float tiles per compute unit");
-static_assert(sizeof(float) * (TR + 4) * (TC + 4) <= sizeof(double) * (TR + 2) * (TC + 2), "elevations fit");
+static_assert(sizeof(Tile<double>) <= 81920, "two float64 tiles per compute unit");
 
-// The edge word of (r, c) along k, r in -1 .. TR, c in -1 .. TC; one of its
-// two cells lies in the tile.  For k < 4 it is the neighbour's edge 7 - k.
+// Which lane holds cell (r, c), as bit r; the column of lane l's bit r.
+__device__ __forceinline__ int lane_at(int r, int c) { return (2 * r + c) & 63; }
+__device__ __forceinline__ int col_at(int l, int r) { return (l - 2 * r) & 63; }
+
+// A cell's place in the arrays of pitch W, for addresses that differ from
+// direction to direction by constants.
 template <typename F>
-__device__ __forceinline__ F* edge_at(Tile<F>& T, int r, int c, int k) {
-  if (k < 4) {
-    r += nb_dr(k);
-    c += nb_dc(k);
-    k = 7 - k;
-  }
-  if (k == 4) return &T.e[r][c + 1];
-  if (k == 5) return &T.sw[r + 1][c];
-  if (k == 6) return &T.s[r + 1][c];
-  return &T.se[r + 1][c + 1];
+__device__ __forceinline__ int place(int r, int c) {
+  return (r + 1) * Tile<F>::W + c + 1;
 }
-// Fraction that runs from (r, c) along k (negative: toward it).
+// The edge word of the cell at place `at` along k; one of the edge's two
+// cells lies in the tile.  For k < 4 it is the neighbour's edge 7 - k.
 template <typename F>
-__device__ __forceinline__ F out_at(Tile<F>& T, int r, int c, int k) {
-  const F w = *edge_at(T, r, c, k);
+__device__ __forceinline__ F* edge_at(Tile<F>& T, int at, int k) {
+  constexpr int W = Tile<F>::W;
+  F* first = T.edge + (at - W - 1);
+  return k >= 4 ? first + ((k - 4) * Tile<F>::PLANE + 1)
+                : first + ((3 - k) * Tile<F>::PLANE + nb_dr(k) * W + nb_dc(k) + 1);
+}
+// Fraction that runs from that cell along k (negative: toward it).
+template <typename F>
+__device__ __forceinline__ F out_at(Tile<F>& T, int at, int k) {
+  const F w = *edge_at(T, at, k);
   return k < 4 ? -w : w;
 }
+template <typename F>
+__device__ __forceinline__ F out_at(Tile<F>& T, int r, int c, int k) {
+  return out_at(T, place<F>(r, c), k);
+}
 
-__device__ __forceinline__ bool in_tile(int r, int c) { return (unsigned)r < (unsigned)TR && (unsigned)c < (unsigned)TC; }
+template <typename F>
+__device__ __forceinline__ bool in_tile(int r, int c) {
+  return (unsigned)r < (unsigned)TR && (unsigned)c < (unsigned)Tile<F>::TC;
+}
 
 // Takes a tile from the queue; -1 when all tiles are finished (or the solve
 // is given up).
@@ -210,13 +236,13 @@ __device__ __forceinline__ void wake(const PeelQueue& P, uint32_t t) {
   }
 }
 
-// Out-fractions of the cell at (r, c) (its validated mask m over the 8
-// neighbours at elevations zk), written to its edges.
+// Out-fractions of the cell at place `at` (its validated mask m over the 8
+// neighbours at elevations zk), those of the mask `put` written to its edges.
 template <typename F>
-__device__ __forceinline__ void put_fractions(Tile<F>& T, int r, int c, uint32_t m, float zc, const float (&zk)[8],
-                                              double p);
+__device__ __forceinline__ void put_fractions(Tile<F>& T, int at, uint32_t put, uint32_t m, float zc,
+                                              const float (&zk)[8], double p);
 template <>
-__device__ __forceinline__ void put_fractions<float>(Tile<float>& T, int r, int c, uint32_t m, float zc,
+__device__ __forceinline__ void put_fractions<float>(Tile<float>& T, int at, uint32_t put, uint32_t m, float zc,
                                                      const float (&zk)[8], double p) {
   const float pf = (float)p;
   float s[8], smax = 0.0f;
@@ -237,14 +263,13 @@ __device__ __forceinline__ void put_fractions<float>(Tile<float>& T, int r, int 
     sum += s[k];
   }
   const float is = sum > 0.0f ? __builtin_amdgcn_rcpf(sum) : 0.0f;
-  const bool own = in_tile(r, c);
+  put &= m;
 #pragma unroll
   for (int k = 0; k < 8; ++k)
-    if (((m >> k) & 1u) && (own || in_tile(r + nb_dr(k), c + nb_dc(k))))
-      *edge_at(T, r, c, k) = k < 4 ? -(s[k] * is) : s[k] * is;
+    if ((put >> k) & 1u) *edge_at(T, at, k) = k < 4 ? -(s[k] * is) : s[k] * is;
 }
 template <>
-__device__ __forceinline__ void put_fractions<double>(Tile<double>& T, int r, int c, uint32_t m, float zc,
+__device__ __forceinline__ void put_fractions<double>(Tile<double>& T, int at, uint32_t put, uint32_t m, float zc,
                                                       const float (&zk)[8], double p) {
   double s[8], smax = 0.0;
 #pragma unroll
@@ -263,11 +288,10 @@ __device__ __forceinline__ void put_fractions<double>(Tile<double>& T, int r, in
     sum += s[k];
   }
   const double is = sum > 0.0 ? 1.0 / sum : 0.0;
-  const bool own = in_tile(r, c);
+  put &= m;
 #pragma unroll
   for (int k = 0; k < 8; ++k)
-    if (((m >> k) & 1u) && (own || in_tile(r + nb_dr(k), c + nb_dc(k))))
-      *edge_at(T, r, c, k) = k < 4 ? -(s[k] * is) : s[k] * is;
+    if ((put >> k) & 1u) *edge_at(T, at, k) = k < 4 ? -(s[k] * is) : s[k] * is;
 }
 
 // RK_SINGLE: codes of one receiver, all of a cell's water runs there (F =
@@ -278,42 +302,86 @@ template <int RK, bool ADJ, int VK, bool BATCH, typename F>
 __device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q, Tile<F>& T, const int32_t tile) {
   constexpr bool CORRECT = RK == RK_MULTI && VK == VK_FF;
   constexpr bool ELEV = RK == RK_MULTI;  // elevations are read
-  const int tid = (int)threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  constexpr int TC = Tile<F>::TC;
+  // The thread index, opaque to the compiler: what is derived from it is
+  // computed anew for each tile instead of held in registers across tiles.
+  int tid = (int)threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int32_t tr = tile / P.ntc, tc = tile - tr * P.ntc;
   const int64_t nr = P.nrows, nc = P.ncols;
   const int64_t r0 = (int64_t)tr * TR, c0 = (int64_t)tc * TC;
   const uint32_t id = (uint32_t)(P.tile0 + tile);
 
   // -------------------------------------------------------------- load
-  // This thread's own cells: 8 of the tile, two rows of 32 per wavefront
-  // step.
+  // Every load is issued before the first is waited for; those off the grid
+  // read its nearest cell and are replaced after (behind a branch each would
+  // be waited for).  This thread's own cells: row 8 wave + i, column lane.
+  constexpr int ZN = (TR + 4) * (TC + 4), ZU = (ZN + PT - 1) / PT;
+  constexpr int CN = (TR + 2) * (TC + 2), CU = (CN + PT - 1) / PT;
+  const int oc = lane, or0 = 8 * wave;
+  const bool column = oc < TC;
+  const int32_t rlast = (int32_t)(nr - 1 - r0 < TR + 1 ? nr - 1 - r0 : TR + 1);  // last row and column on the grid
+  const int32_t clast = (int32_t)(nc - 1 - c0 < TC + 1 ? nc - 1 - c0 : TC + 1);  // (from the tile's first)
+  const int32_t rfirst = tr > 0 ? -2 : 0, cfirst = tc > 0 ? -2 : 0;
+  const int64_t cell0 = r0 * nc + c0;
+  auto near = [&](int r, int c) -> int64_t {
+    const int32_t rr = r < rfirst ? rfirst : (r > rlast ? rlast : r), cc = c < cfirst ? cfirst : (c > clast ? clast : c);
+    return cell0 + (int64_t)rr * nc + cc;
+  };
+  auto on_grid = [&](int r, int c) -> bool { return r >= rfirst && r <= rlast && c >= cfirst && c <= clast; };
   uint64_t word[8];
-  double src[8];
+  uint64_t raw[8];  // source terms as loaded
   bool nonfinite = false, badcode = false, cycle = false;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const int r = 2 * (8 * wave + i) + (lane >> 5), c = lane & 31;
-    word[i] = OPEN;
-    src[i] = 0.0;
-    if (r0 + r < nr && c0 + c < nc) {
-      const int64_t at = (r0 + r) * nc + c0 + c;
-      word[i] = ld64(P.word + at);
-      src[i] = P.src64 ? P.src64[at] : (P.src32 ? (double)P.src32[at] : 1.0);
+    const int64_t at = near(or0 + i, oc);
+    word[i] = ld64(P.word + at);
+    if (P.src64) raw[i] = (uint64_t)__double_as_longlong(P.src64[at]);
+    else raw[i] = P.src32 ? __float_as_uint(P.src32[at]) : 0x3F800000u;
+  }
+  float zv[ELEV ? ZU : 1];
+  if (ELEV) {
+#pragma unroll
+    for (int j = 0; j < ZU; ++j) {
+      const int i = tid + j * PT;
+      zv[j] = P.z[near(i / (TC + 4) - 2, i % (TC + 4) - 2)];
     }
   }
-  if (ELEV) {
-    for (int i = tid; i < (TR + 4) * (TC + 4); i += PT) {
-      const int r = i / (TC + 4) - 2, c = i % (TC + 4) - 2;
-      const int64_t y = r0 + r, x = c0 + c;
-      float v = INFINITY;
-      if (y >= 0 && y < nr && x >= 0 && x < nc) v = P.z[y * nc + x];
-      T.z[r + 2][c + 2] = v;
+  uint8_t cv[BATCH ? 1 : CU];
+  if (!BATCH) {
+#pragma unroll
+    for (int j = 0; j < CU; ++j) {
+      const int i = tid + j * PT;
+      cv[j] = P.code[near(i / (TC + 2) - 1, i % (TC + 2) - 1)];
     }
   }
   {
-    F* w = reinterpret_cast<F*>(&T);  // the four edge arrays
-    constexpr int words = (int)(offsetof(Tile<F>, g) / sizeof(F));
-    for (int i = tid; i < words; i += PT) w[i] = (F)0;
+    // The four edge arrays.
+    uint64_t* w = reinterpret_cast<uint64_t*>(&T);
+    for (int i = tid; i < (int)(sizeof(T.edge) / 8); i += PT) w[i] = 0ull;
+  }
+  if (ELEV) {
+#pragma unroll
+    for (int j = 0; j < ZU; ++j) {
+      const int i = tid + j * PT;
+      if (i < ZN) (&T.z[0][0])[i] = on_grid(i / (TC + 4) - 2, i % (TC + 4) - 2) ? zv[j] : INFINITY;
+    }
+  }
+  if (!BATCH) {
+#pragma unroll
+    for (int j = 0; j < CU; ++j) {
+      const int i = tid + j * PT;
+      if (i < CN) (&T.code[0][0])[i] = cv[j];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    // Cells off the grid count as final.
+    const int r = or0 + i;
+    if (!column || !on_grid(r, oc)) word[i] = 0;
+    const uint64_t b = ballot(word[i] != OPEN);
+    if (lane < 2) T.done[2 * r + lane] = (uint32_t)(b >> (32 * lane));
   }
   if (tid == 0) {
     T.phase = PH_RUN;
@@ -323,11 +391,22 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q,
   __syncthreads();
 
   // --------------------------------------------------------- fractions
-  for (int i = tid; i < (TR + 2) * (TC + 2); i += PT) {
+#pragma unroll 1
+  for (int i = tid; i < CN; i += PT) {
     const int r = i / (TC + 2) - 1, c = i % (TC + 2) - 1;
     const int64_t y = r0 + r, x = c0 + c;
-    if (y < 0 || y >= nr || x < 0 || x >= nc) continue;
-    const bool own = in_tile(r, c);
+    if (!on_grid(r, c)) continue;
+    const bool own = in_tile<F>(r, c);
+    // The edges with a cell in the tile, by direction.
+    const int at = place<F>(r, c);
+    uint32_t put = 0xFFu;
+    if (!own) {
+      const uint32_t cols = (c >= 1 && c <= TC ? 0x29u : 0u) | (c >= 0 && c < TC ? 0x42u : 0u) |
+                            (c >= -1 && c < TC - 1 ? 0x94u : 0u);
+      const uint32_t rows = (r >= 1 && r <= TR ? 0x07u : 0u) | (r >= 0 && r < TR ? 0x18u : 0u) |
+                            (r >= -1 && r < TR - 1 ? 0xE0u : 0u);
+      put = cols & rows;
+    }
     float zc = 0.0f, zk[8];
     uint32_t code, lower = 0;
     if (ELEV) {
@@ -343,7 +422,7 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q,
       code = P.rule == FR_MFD ? lower : (P.rule == FR_D4 ? route_code<FR_D4>(zc, zk) : route_code<FR_D8>(zc, zk));
       if (own && P.code_out) P.code_out[y * nc + x] = (uint8_t)code;
     } else {
-      code = P.code[y * nc + x];
+      code = T.code[r + 1][c + 1];
     }
     if (RK == RK_SINGLE || (BATCH && P.rule != FR_MFD)) {
       if (code > 7u) {
@@ -351,7 +430,9 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q,
         continue;
       }
       if (!BATCH) {
-        const int64_t yy = y + nb_dr((int)code), xx = x + nb_dc((int)code);
+        const int kr = (int)code < 3 ? -1 : ((int)code < 5 ? 0 : 1);
+        const int kc = (code == 0u || code == 3u || code == 5u) ? -1 : ((code == 1u || code == 6u) ? 0 : 1);
+        const int64_t yy = y + kr, xx = x + kc;
         if (yy < 0 || yy >= nr || xx < 0 || xx >= nc) {
           badcode |= own;
           continue;
@@ -362,56 +443,73 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q,
           continue;
         }
       }
-#pragma unroll
+      #pragma unroll
       for (int k = 0; k < 8; ++k)
-        if ((int)code == k && (own || in_tile(r + nb_dr(k), c + nb_dc(k))))
-          *edge_at(T, r, c, k) = k < 4 ? (F)-1 : (F)1;
+        if ((int)code == k && ((put >> k) & 1u)) *edge_at(T, at, k) = k < 4 ? (F)-1 : (F)1;
     } else {
       // Only strictly lower cells of the grid can receive: whatever the
       // codes say, the routing solved is acyclic.
       badcode |= own && (code & ~lower) != 0u;
-      put_fractions<F>(T, r, c, code & lower, zc, zk, P.p);
+      put_fractions<F>(T, at, put, code & lower, zc, zk, P.p);
     }
   }
   __syncthreads();
 
   // ------------------------------------------------------------- masks
-#pragma unroll 2
-  for (int i = 0; i < 8; ++i) {
-    const int r = 2 * (8 * wave + i) + (lane >> 5), c = lane & 31;
+  // Wavefront w finds rows 8 w to 8 w + 7 of every lane: bytes w of the
+  // lane's masks.  mask[8]: inputs from outside the tile; [9]: final; [10]:
+  // feeds a cell outside.
+  {
+    uint32_t m[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll 1
+    for (int i = 0; i < 8; ++i) {
+      const int r = 8 * wave + i, c = col_at(lane, r);
+      if (c >= TC) {
+        m[9] |= 1u << i;
+        continue;
+      }
+      const int at = place<F>(r, c);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const F o = out_at(T, r, c, k);
-      const uint64_t b = ballot(ADJ ? o > (F)0 : o < (F)0);
-      if (c == 0) T.in[k][r] = lane ? (uint32_t)(b >> 32) : (uint32_t)b;
+      for (int k = 0; k < 8; ++k) {
+        const F o = out_at(T, at, k);
+        const uint32_t b = (ADJ ? o > (F)0 : o < (F)0) ? 1u << i : 0u;
+        const bool inside = in_tile<F>(r + nb_dr(k), c + nb_dc(k));
+        m[k] |= inside ? b : 0u;
+        m[8] |= inside ? 0u : b;
+        m[10] |= !inside && (ADJ ? o < (F)0 : o > (F)0) ? 1u << i : 0u;
+      }
+      m[9] |= ((T.done[2 * r + (c >> 5)] >> (c & 31)) & 1u) << i;
     }
-  }
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int r = 2 * (8 * wave + i) + (lane >> 5), c = lane & 31;
-    // Cells off the grid count as final.
-    const uint64_t b = ballot(word[i] != OPEN || r0 + r >= nr || c0 + c >= nc);
-    if (c == 0) T.done[r] = lane ? (uint32_t)(b >> 32) : (uint32_t)b;
+    for (int k = 0; k < 11; ++k) T.mask[k][lane][wave] = (uint8_t)m[k];
   }
-  if (tid < TR) T.side[tid] = 0;
-  if (tid < 2) T.ring_tb[tid] = 0;
   __syncthreads();
+  // Roles: the peeling wavefront is the one on SIMD (workgroup slot mod 4).
+  int lw = 0;
+  for (int w = 3; w >= 0; --w)
+    if (T.simd[w] == T.simd[4]) lw = w;
+  const int role = __builtin_amdgcn_readfirstlane((wave - lw) & 3);
   uint32_t in[8];
-  uint32_t done = 0;
-  if (wave == 0) {
+  uint32_t done = 0, feeder = 0;
+  if (role == 0) {
+    auto whole = [&](int k) -> uint32_t { return *reinterpret_cast<const uint32_t*>(&T.mask[k][lane][0]); };
 #pragma unroll
-    for (int k = 0; k < 8; ++k) in[k] = T.in[k][lane];
-    done = T.done[lane];
+    for (int k = 0; k < 8; ++k) in[k] = whole(k);
+    T.wait[lane] = whole(8);
+    done = whole(9);
+    feeder = whole(10);
+    T.done[lane] = done;
   }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const int r = 2 * (8 * wave + i) + (lane >> 5), c = lane & 31;
-    if (!isfinite(src[i])) {
+    const int r = or0 + i;
+    double v = P.src64 ? bitsd(raw[i]) : (double)__uint_as_float((uint32_t)raw[i]);
+    if (!isfinite(v)) {
       nonfinite = true;
-      src[i] = 0.0;
+      v = 0.0;
     }
-    T.g[r + 1][c + 1] = word[i] != OPEN ? bitsd(word[i]) : src[i];
+    if (column) T.g[r + 1][oc + 1] = word[i] != OPEN ? bitsd(word[i]) : v;
   }
   // The cells around the tile pass nothing on until they are known.
   for (int i = tid; i < 2 * (TC + 2) + 2 * TR; i += PT) {
@@ -425,38 +523,44 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q,
     if (ballot(nonfinite) && lane == 0) atomicCAS(Q.status, 0, FR_ERR_NONFINITE);
     if (ballot(cycle) && lane == 0) atomicCAS(Q.status, 0, FR_ERR_NOTDAG);
   }
+  // Border cells published so far: final ones of columns 0 and TC - 1 (lane =
+  // row) and of rows 0 and TR - 1 (lane = column).
+  const auto border_done = [&]() -> uint32_t {
+    const int rr = lane & 31;
+    return ((l_ld(&T.done[lane_at(rr, 0)]) >> rr) & 1u) | (((l_ld(&T.done[lane_at(rr, TC - 1)]) >> rr) & 1u) << 1) |
+           ((l_ld(&T.done[lane_at(0, lane)]) & 1u) << 2) | ((l_ld(&T.done[lane_at(TR - 1, lane)]) >> 31) << 3);
+  };
+  uint32_t published = role == 1 ? border_done() : 0u;
   __syncthreads();
 
   // ------------------------------------------------------------- roles
-  uint32_t published = done;  // wavefront 1: cells handled (see below)
-  if (wave == 1) published = T.done[lane];
-  __syncthreads();
   for (;;) {
-    if (wave == 0) {
-      // Peeling: lane = row.
-      const int r = lane;
-      const int64_t base = (r0 + r) * nc + c0;
+    if (role == 0) {
+      // Peeling.
+      __builtin_amdgcn_s_setprio(3);
       uint32_t idle_from = 0;
       bool idle = false;
+      uint32_t outside = l_ld(&T.wait[lane]);
       for (;;) {
-        const uint32_t sd = *(volatile uint8_t*)&T.side[r];
-        const uint32_t polls = l_ld(&T.polls);
-        uint32_t up = sh_l(done), dn = sh_r(done);
-        if (lane == 0) up = l_ld(&T.ring_tb[0]);
-        if (lane == TR - 1) dn = l_ld(&T.ring_tb[1]);
+        const uint32_t a1 = from_below(done), a2 = from_below(a1), a3 = from_below(a2);
+        const uint32_t b1 = from_above(done), b2 = from_above(b1), b3 = from_above(b2);
+        uint32_t wait = outside;
+        wait |= in[0] & ~(a3 << 1);
+        wait |= in[1] & ~(a2 << 1);
+        wait |= in[2] & ~(a1 << 1);
+        wait |= in[3] & ~a1;
+        wait |= in[4] & ~b1;
+        wait |= in[5] & ~(b1 >> 1);
+        wait |= in[6] & ~(b2 >> 1);
+        wait |= in[7] & ~(b3 >> 1);
+        // Read now, used in the next step.
+        outside = l_ld(&T.wait[lane]);
         fence();
-        uint32_t wait = in[0] & ~((up << 1) | (sd & 1u));
-        wait |= in[1] & ~up;
-        wait |= in[2] & ~((up >> 1) | (((sd >> 3) & 1u) << 31));
-        wait |= in[3] & ~((done << 1) | ((sd >> 1) & 1u));
-        wait |= in[4] & ~((done >> 1) | (((sd >> 4) & 1u) << 31));
-        wait |= in[5] & ~((dn << 1) | ((sd >> 2) & 1u));
-        wait |= in[6] & ~dn;
-        wait |= in[7] & ~((dn >> 1) | (((sd >> 5) & 1u) << 31));
         const uint32_t ready = ~(done | wait);
         if (ballot(ready != 0u) == 0ull) {
           if (ballot(done != ~0u) == 0ull) break;
           // Nothing ready: wait for cells around the tile, for a few polls.
+          const uint32_t polls = l_ld(&T.polls);
           if (!idle) {
             idle = true;
             idle_from = polls;
@@ -468,14 +572,17 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q,
         }
         idle = false;
         if (ready != 0u) {
-          const int c = __builtin_ctz(ready);
+          const int r = __builtin_ctz(ready), c = col_at(lane, r);
+          const int at = place<F>(r, c);
+          double* g0 = &T.g[0][0] + (at - Tile<F>::W - 1);  // the upper left neighbour
           F o[8];
           double gk[8];
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
-            o[k] = out_at(T, r, c, k);
-            gk[k] = T.g[r + 1 + nb_dr(k)][c + 1 + nb_dc(k)];
+            o[k] = out_at(T, at, k);
+            gk[k] = g0[(nb_dr(k) + 1) * Tile<F>::W + nb_dc(k) + 1];
           }
+          double& gc = g0[Tile<F>::W + 1];
           double v = 0.0, give = 0.0;
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
@@ -484,86 +591,134 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q,
             if (CORRECT) give += fmax(ok, 0.0);
           }
           const double fix = CORRECT && give > 0.0 ? 2.0 - give : 1.0;
-          const double own = T.g[r + 1][c + 1];
-          double q = ADJ && CORRECT ? fma(v, fix, own) : own + v;
-          T.g[r + 1][c + 1] = !ADJ && CORRECT ? q * fix : q;
-          if (VK == VK_F64) P.out64[base + c] = q;
-          else if (!BATCH || P.out32) P.out32[base + c] = (float)q;
-          else P.cnt[base + c] = (uint64_t)q;  // whole numbers below 2^31
-          done |= 1u << c;
+          const double own = gc;
+          const double q = ADJ && CORRECT ? fma(v, fix, own) : own + v;
+          gc = !ADJ && CORRECT ? q * fix : q;
+          done |= 1u << r;
           fence();
-          l_st(&T.done[r], done);
+          l_st(&T.done[lane], done);
+          const int64_t cell = cell0 + (int64_t)((uint32_t)r * (uint32_t)nc + (uint32_t)c);
+          // Stored at once for the tiles that poll it; the publishing
+          // wavefront stores it again, to know when it has arrived.
+          if ((feeder >> r) & 1u) st64(P.word + cell, dword(gc));
+          if (VK == VK_F64) P.out64[cell] = q;
+          else if (!BATCH || P.out32) P.out32[cell] = (float)q;
+          else P.cnt[cell] = (uint64_t)q;  // whole numbers below 2^31
         }
         fence();
       }
       l_st(&T.phase, PH_STOP);
-    } else if (wave == 1) {
-      // Publishing: lane = row for the side columns, lane = column for the
-      // top and bottom rows.  Cells with an edge out of the tile along the
-      // way their value goes are stored and the tiles they feed woken.
-      const int r = lane, cc = lane & 31;
+      __builtin_amdgcn_s_setprio(0);
+    } else if (role == 1) {
+      // Publishing: cells with an edge out of the tile along the way their
+      // value goes are stored and the tiles they feed woken.
+      const int r = lane & 31, cc = lane < TC ? lane : TC - 1;
       auto feeds = [&](int rr, int c, int k) -> bool {
         const F o = out_at(T, rr, c, k);
         return ADJ ? o < (F)0 : o > (F)0;
       };
-      const bool fl = feeds(r, 0, 0) || feeds(r, 0, 3) || feeds(r, 0, 5);
-      const bool fr_ = feeds(r, TC - 1, 2) || feeds(r, TC - 1, 4) || feeds(r, TC - 1, 7);
-      const uint32_t ft = (uint32_t)ballot(feeds(0, cc, 0) || feeds(0, cc, 1) || feeds(0, cc, 2));
-      const uint32_t fb = (uint32_t)ballot(feeds(TR - 1, cc, 5) || feeds(TR - 1, cc, 6) || feeds(TR - 1, cc, 7));
+      uint32_t feed = 0;  // as border_done()
+      if (lane < TR) {
+        feed |= feeds(r, 0, 0) || feeds(r, 0, 3) || feeds(r, 0, 5) ? 1u : 0u;
+        feed |= feeds(r, TC - 1, 2) || feeds(r, TC - 1, 4) || feeds(r, TC - 1, 7) ? 2u : 0u;
+      }
+      if (lane < TC) {
+        feed |= feeds(0, cc, 0) || feeds(0, cc, 1) || feeds(0, cc, 2) ? 4u : 0u;
+        feed |= feeds(TR - 1, cc, 5) || feeds(TR - 1, cc, 6) || feeds(TR - 1, cc, 7) ? 8u : 0u;
+      }
       const bool f0 = feeds(0, 0, 0), f2 = feeds(0, TC - 1, 2), f5 = feeds(TR - 1, 0, 5),
                  f7 = feeds(TR - 1, TC - 1, 7);
+      uint32_t all_fed = 0;  // tiles this one feeds, by direction
+      {
+        const uint64_t t = ballot((feed & 4u) != 0u), b = ballot((feed & 8u) != 0u);
+        if (t) all_fed |= 1u << 1;
+        if (b) all_fed |= 1u << 6;
+        if (ballot((feed & 1u) != 0u)) all_fed |= 1u << 3;
+        if (ballot((feed & 2u) != 0u)) all_fed |= 1u << 4;
+        if (f0) all_fed |= 1u << 0;
+        if (f2) all_fed |= 1u << 2;
+        if (f5) all_fed |= 1u << 5;
+        if (f7) all_fed |= 1u << 7;
+      }
+      const auto half_done = [&]() -> bool { return __popcll(ballot(__popc(l_ld(&T.done[lane])) >= TR / 2)) >= 32; };
+      bool foretold = half_done();
+      uint32_t wk = 0;  // tiles to wake, by direction
       for (bool last = false; !last;) {
         last = l_ld(&T.phase) != PH_RUN;
         fence();
-        const uint32_t now = l_ld(&T.done[r]);
+        const uint32_t now = border_done();
         fence();
-        const uint32_t fresh = now & ~published;
+        const uint32_t fresh = now & ~published & feed;
         published = now;
-        const uint32_t top = lane_of(fresh, 0) & ft, bot = lane_of(fresh, TR - 1) & fb;
-        const bool pl = (fresh & 1u) && fl, pr = (fresh >> 31) && fr_;
-        const uint64_t bl = ballot(pl), br = ballot(pr);
-        if (!(top | bot) && !(bl | br)) {
-          __builtin_amdgcn_s_sleep(1);
+        if (ballot(fresh != 0u)) {
+          if (fresh & 1u) st64(P.word + (r0 + r) * nc + c0, dword(T.g[r + 1][1]));
+          if (fresh & 2u) st64(P.word + (r0 + r) * nc + c0 + TC - 1, dword(T.g[r + 1][TC]));
+          if (fresh & 4u) st64(P.word + r0 * nc + c0 + cc, dword(T.g[1][cc + 1]));
+          if (fresh & 8u) st64(P.word + (r0 + TR - 1) * nc + c0 + cc, dword(T.g[TR][cc + 1]));
+          const uint64_t top = ballot((fresh & 4u) != 0u), bot = ballot((fresh & 8u) != 0u);
+          if (top) wk |= 1u << 1;
+          if (bot) wk |= 1u << 6;
+          if (ballot((fresh & 1u) != 0u)) wk |= 1u << 3;
+          if (ballot((fresh & 2u) != 0u)) wk |= 1u << 4;
+          if ((top & 1u) && f0) wk |= 1u << 0;
+          if (((top >> (TC - 1)) & 1u) && f2) wk |= 1u << 2;
+          if ((bot & 1u) && f5) wk |= 1u << 5;
+          if (((bot >> (TC - 1)) & 1u) && f7) wk |= 1u << 7;
+        }
+        // A tile that is half finished wakes those it feeds while workgroups
+        // are idle, so that they are in LDS when it ends.
+        if (!foretold && half_done()) {
+          foretold = true;
+          if (l_ld(&T.queue_empty)) wk |= all_fed;
+        }
+        // While other tiles are queued, tiles are woken once this one stops:
+        // they find more to do then, and those in LDS see the words anyway.
+        if (wk == 0u || !(last || l_ld(&T.queue_empty))) {
+          __builtin_amdgcn_s_sleep(2);
           continue;
         }
-        if (pl) st64(P.word + (r0 + r) * nc + c0, dword(T.g[r + 1][1]));
-        if (pr) st64(P.word + (r0 + r) * nc + c0 + TC - 1, dword(T.g[r + 1][TC]));
-        if (lane < TC) {
-          if ((top >> lane) & 1u) st64(P.word + r0 * nc + c0 + lane, dword(T.g[1][lane + 1]));
-          if ((bot >> lane) & 1u) st64(P.word + (r0 + TR - 1) * nc + c0 + lane, dword(T.g[TR][lane + 1]));
-        }
         stores_done();
-        uint32_t wk = 0;  // by direction
-        if (top) wk |= 1u << 1;
-        if (bot) wk |= 1u << 6;
-        if (bl) wk |= 1u << 3;
-        if (br) wk |= 1u << 4;
-        if ((top & 1u) && f0) wk |= 1u << 0;
-        if ((top >> 31) && f2) wk |= 1u << 2;
-        if ((bot & 1u) && f5) wk |= 1u << 5;
-        if ((bot >> 31) && f7) wk |= 1u << 7;
         if (lane < 8 && ((wk >> lane) & 1u)) {
           const int dr = lane < 3 ? -1 : (lane < 5 ? 0 : 1);
           const int dc = (lane == 0 || lane == 3 || lane == 5) ? -1 : ((lane == 1 || lane == 6) ? 0 : 1);
           const int32_t ur = tr + dr, uc = tc + dc;
           if (ur >= 0 && ur < P.ntr && uc >= 0 && uc < P.ntc) wake(Q, (uint32_t)(P.tile0 + ur * P.ntc + uc));
         }
+        wk = 0;
       }
-    } else if (wave == 2) {
-      // Polling: cells of the columns beside the tile (lane = row), of the
-      // rows above and below it (lane - 1 = column).
+    } else {
+      // Polling (two wavefronts, so that words are looked at twice as often):
+      // cells of the columns beside the tile (lane - 1 = row), of the rows
+      // above and below it (lane = column); and the cells of the tile that
+      // wait for them (lane = row, lane = column).
       auto gives = [&](int rr, int c, int k) -> bool {  // toward a cell of the tile
-        if (!in_tile(rr + nb_dr(k), c + nb_dc(k))) return false;
+        if (!in_tile<F>(rr + nb_dr(k), c + nb_dc(k))) return false;
         const F o = out_at(T, rr, c, k);
         return ADJ ? o < (F)0 : o > (F)0;
       };
-      const int r = lane, c = lane - 1;
+      auto takes = [&](int rr, int c, int k) -> bool {
+        const F o = out_at(T, rr, c, k);
+        return ADJ ? o > (F)0 : o < (F)0;
+      };
+      const int r = lane - 1, c = lane;
+      const bool side = lane < TR + 2, cap = lane < TC, edge = lane < TR;
       bool need[4] = {false, false, false, false};
-      need[0] = gives(r, -1, 2) || gives(r, -1, 4) || gives(r, -1, 7);
-      need[1] = gives(r, TC, 0) || gives(r, TC, 3) || gives(r, TC, 5);
-      if (lane < TC + 2) {
+      uint32_t takes4[4] = {0, 0, 0, 0};  // bits 0-2: from the lane before, this lane, the lane after
+      if (side) {
+        need[0] = gives(r, -1, 2) || gives(r, -1, 4) || gives(r, -1, 7);
+        need[1] = gives(r, TC, 0) || gives(r, TC, 3) || gives(r, TC, 5);
+      }
+      if (edge) {
+        takes4[0] = (takes(lane, 0, 0) ? 1u : 0u) | (takes(lane, 0, 3) ? 2u : 0u) | (takes(lane, 0, 5) ? 4u : 0u);
+        takes4[1] = (takes(lane, TC - 1, 2) ? 1u : 0u) | (takes(lane, TC - 1, 4) ? 2u : 0u) |
+                    (takes(lane, TC - 1, 7) ? 4u : 0u);
+      }
+      if (cap) {
         need[2] = gives(-1, c, 5) || gives(-1, c, 6) || gives(-1, c, 7);
         need[3] = gives(TR, c, 0) || gives(TR, c, 1) || gives(TR, c, 2);
+        takes4[2] = (takes(0, c, 0) ? 1u : 0u) | (takes(0, c, 1) ? 2u : 0u) | (takes(0, c, 2) ? 4u : 0u);
+        takes4[3] =
+            (takes(TR - 1, c, 5) ? 1u : 0u) | (takes(TR - 1, c, 6) ? 2u : 0u) | (takes(TR - 1, c, 7) ? 4u : 0u);
       }
       const uint64_t* at[4];
       at[0] = P.word + (r0 + r) * nc + c0 - 1;
@@ -571,17 +726,21 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q,
       at[2] = P.word + (r0 - 1) * nc + c0 + c;
       at[3] = P.word + (r0 + TR) * nc + c0 + c;
       double* to[4];
-      to[0] = &T.g[r + 1][0];
-      to[1] = &T.g[r + 1][TC + 1];
-      to[2] = &T.g[0][lane < TC + 2 ? lane : 0];
-      to[3] = &T.g[TR + 1][lane < TC + 2 ? lane : 0];
+      to[0] = &T.g[side ? lane : 0][0];
+      to[1] = &T.g[side ? lane : 0][TC + 1];
+      to[2] = &T.g[0][cap ? c + 1 : 0];
+      to[3] = &T.g[TR + 1][cap ? c + 1 : 0];
       bool have[4] = {false, false, false, false};
       uint32_t polls = l_ld(&T.polls);
       while (l_ld(&T.phase) == PH_RUN) {
         uint64_t w[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) w[i] = need[i] ? ld64(at[i]) : OPEN;
-        const uint32_t head = ld32(&Q.ctl->head), tail = ld32(&Q.ctl->tail);
+        uint32_t head = 0, tail = 0;
+        if (role == 2) {
+          head = ld32(&Q.ctl->head);
+          tail = ld32(&Q.ctl->tail);
+        }
         bool news = false;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -593,27 +752,33 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q,
           }
         if (ballot(news)) {
           const uint64_t hl = ballot(have[0]), hr = ballot(have[1]), ht = ballot(have[2]), hb = ballot(have[3]);
-          // Three rows' bits of each side column for the lane's row; the
-          // corners come from the rows above and below.
-          auto three = [&](uint64_t h, uint32_t above, uint32_t below) -> uint32_t {
-            const uint32_t a = lane == 0 ? above : (uint32_t)(h >> (lane - 1)) & 1u;
-            const uint32_t b = (uint32_t)(h >> lane) & 1u;
-            const uint32_t d = lane == 63 ? below : (uint32_t)(h >> (lane + 1)) & 1u;
-            return a | (b << 1) | (d << 2);
+          // Which of its three cells outside a border cell has: the corners
+          // above and below a column belong to the columns beside the tile.
+          auto three = [&](uint64_t h, uint64_t before, uint64_t after) -> uint32_t {
+            const uint64_t a = lane == 0 ? before : h >> (lane - 1);
+            const uint64_t d = lane == TC - 1 ? after : h >> ((lane + 1) & 63);
+            return ((uint32_t)a & 1u) | (((uint32_t)(h >> lane) & 1u) << 1) | (((uint32_t)d & 1u) << 2);
           };
-          const uint32_t left = three(hl, (uint32_t)ht & 1u, (uint32_t)hb & 1u);
-          const uint32_t right =
-              three(hr, (uint32_t)(ht >> (TC + 1)) & 1u, (uint32_t)(hb >> (TC + 1)) & 1u);
+          const bool wl = (takes4[0] & ~((uint32_t)(hl >> (lane & 31)) & 7u)) != 0u;
+          const bool wr = (takes4[1] & ~((uint32_t)(hr >> (lane & 31)) & 7u)) != 0u;
+          const bool wt = (takes4[2] & ~three(ht, hl, hr)) != 0u;
+          const bool wb = (takes4[3] & ~three(hb, hl >> (TR + 1), hr >> (TR + 1))) != 0u;
+          // A corner cell waits for both of its sides.
+          const uint64_t bl = ballot(wl), br = ballot(wr), bt = ballot(wt), bb = ballot(wb);
+          const bool l0 = lane == 0, l1 = lane == TR - 1, k1 = lane == TC - 1;
+          const bool ul = !wl && !(l0 && (bt & 1u)) && !(l1 && (bb & 1u));
+          const bool ur = !wr && !(l0 && ((bt >> (TC - 1)) & 1u)) && !(l1 && ((bb >> (TC - 1)) & 1u));
+          const bool ut = !wt && !(l0 && (bl & 1u)) && !(k1 && (br & 1u));
+          const bool ub = !wb && !(l0 && ((bl >> (TR - 1)) & 1u)) && !(k1 && ((br >> (TR - 1)) & 1u));
           fence();
-          *(volatile uint8_t*)&T.side[r] = (uint8_t)(left | (right << 3));
-          if (lane == 0) {
-            l_st(&T.ring_tb[0], (uint32_t)(ht >> 1));
-            l_st(&T.ring_tb[1], (uint32_t)(hb >> 1));
-          }
+          if (takes4[0] && ul) atomicAnd(&T.wait[lane_at(lane, 0)], ~(1u << (lane & 31)));
+          if (takes4[1] && ur) atomicAnd(&T.wait[lane_at(lane, TC - 1)], ~(1u << (lane & 31)));
+          if (takes4[2] && ut) atomicAnd(&T.wait[lane_at(0, lane)], ~1u);
+          if (takes4[3] && ub) atomicAnd(&T.wait[lane_at(TR - 1, lane)], ~(1u << (TR - 1)));
           fence();
         }
         ++polls;
-        if (lane == 0) {
+        if (role == 2 && lane == 0) {
           l_st(&T.queue_empty, (int32_t)(tail - head) <= 0 ? 1u : 0u);
           l_st(&T.polls, polls);
         }
@@ -628,10 +793,10 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q,
     if (!all || P.keep) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const int r = 2 * (8 * wave + i) + (lane >> 5), c = lane & 31;
-        if (word[i] == OPEN && ((T.done[r] >> c) & 1u) && r0 + r < nr && c0 + c < nc) {
-          word[i] = dword(T.g[r + 1][c + 1]);
-          st64(P.word + (r0 + r) * nc + c0 + c, word[i]);
+        const int r = or0 + i;
+        if (word[i] == OPEN && ((T.done[lane_at(r, oc)] >> r) & 1u)) {
+          word[i] = dword(T.g[r + 1][oc + 1]);
+          st64(P.word + (r0 + r) * nc + c0 + oc, word[i]);
         }
       }
     }
@@ -654,14 +819,24 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q,
   }
 }
 
+// SIMD of every wavefront and the workgroup's slot on its compute unit, from
+// the hardware's wave identity register (bits 5:4, 19:16).
+template <typename F>
+__device__ __forceinline__ void note_simds(Tile<F>& T) {
+  const uint32_t hw = __builtin_amdgcn_s_getreg((31 << 11) | 4);
+  if ((threadIdx.x & 63) == 0) T.simd[threadIdx.x >> 6] = (int)((hw >> 4) & 3u);
+  if (threadIdx.x == 0) T.simd[4] = (int)((hw >> 16) & 3u);
+}
+
 // Float fractions: three workgroups fit a compute unit's LDS, so three
-// wavefronts a SIMD; float64 ones: one.
+// wavefronts a SIMD; float64 ones: two.
 template <int RK, bool ADJ, int VK>
-__global__ __launch_bounds__(PT, RK == RK_MULTI && VK == VK_F64 ? 1 : 3) void k_peel(PeelGrid P, PeelQueue Q,
+__global__ __launch_bounds__(PT, RK == RK_MULTI && VK == VK_F64 ? 2 : 3) void k_peel(PeelGrid P, PeelQueue Q,
                                                                                      const int32_t* gate) {
   using F = typename PeelFrac<RK, VK>::T;
   if (gate && *gate == 0) return;
   __shared__ Tile<F> T;
+  note_simds(T);
   for (;;) {
     if (threadIdx.x == 0) T.tile = take_tile(Q);
     __syncthreads();
@@ -678,6 +853,7 @@ __global__ __launch_bounds__(PT, 3) void k_peel_batch(const PeelBatch* B) {
   const PeelQueue Q = B->queue;
   const PeelGrid* grids = B->grids;
   const int32_t ngrids = B->ngrids;
+  note_simds(T);
   for (;;) {
     if (threadIdx.x == 0) T.tile = take_tile(Q);
     __syncthreads();
@@ -690,7 +866,8 @@ __global__ __launch_bounds__(PT, 3) void k_peel_batch(const PeelBatch* B) {
       if (grids[mid].tile0 <= t) lo = mid;
       else hi = mid - 1;
     }
-    peel_tile<RK_MULTI, false, VK_FF, true, float>(grids[lo], Q, T, t - grids[lo].tile0);
+    const PeelGrid P = grids[lo];
+    peel_tile<RK_MULTI, false, VK_FF, true, float>(P, Q, T, t - P.tile0);
     __syncthreads();
   }
 }
@@ -810,7 +987,7 @@ __global__ __launch_bounds__(1024) void k_peel_batch_setup(const fr_tile* tiles,
       G.nrows = T.nrows;
       G.ncols = T.ncols;
       G.ntr = (int32_t)((T.nrows + TR - 1) / TR);
-      G.ntc = (int32_t)((T.ncols + TC - 1) / TC);
+      G.ntc = (int32_t)((T.ncols + peel_cols(false) - 1) / peel_cols(false));
       G.z = T.z;
       G.p = 1.1;
       G.src32 = T.rule == FR_MFD || T.q_out ? T.rain : nullptr;
