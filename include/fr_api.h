@@ -276,12 +276,14 @@ int fr_accumulate_block_iterations(const float* z, const uint8_t* code, int64_t 
  *             (the neighbours the rule can route to).
  *   eps       1 (epsilon variant) or 0 (plain).
  *   f_out     device float32[nrows*ncols], written; must not alias z.
- *   launches_out  host int32 or NULL: tile launches until nothing changed
- *             (diagnostic).
+ *   launches_out  host int32 or NULL: tile launches on the grid until nothing
+ *             changed (diagnostic).
  *   dev_status optional device int32: FR_ERR_NONFINITE if z holds NaN or Inf
  *             (f_out is then unspecified).
  *   ws, ws_bytes  workspace of fr_workspace_bytes(FR_FN_FILL, nrows, ncols,
- *             rule, FR_F32), a few bytes per 62 x 62 tile.
+ *             rule, FR_F32): a few bytes per 62 x 62 tile, and on larger grids
+ *             the coarser ones solved first (about an eighth of a byte per
+ *             cell).
  * Synchronises with the stream every few launches.  Errors: FR_ERR_ARG,
  * FR_ERR_RULE, FR_ERR_WORKSPACE, FR_ERR_TOOLARGE, FR_ERR_HIP.
  */

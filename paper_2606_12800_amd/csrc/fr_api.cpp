@@ -164,7 +164,7 @@ PeelLayout peel_layout(int64_t nrows, int64_t ncols, bool frac64) {
   L.word = o; o += up((size_t)(nrows * ncols) * sizeof(uint64_t));
   L.state = o; o += up(nt * sizeof(uint32_t));
   L.ring = o; o += up((size_t)L.cap * sizeof(uint64_t));
-  L.ctl = o; o += up(sizeof(PeelCtl));
+  L.ctl = o; o += up(sizeof(TileCtl));
   L.partial = o; o += up(2 * kMassBlocks * sizeof(double));
   L.total = o;
   return L;
@@ -184,11 +184,11 @@ PeelGrid peel_grid(int64_t nrows, int64_t ncols, const uint8_t* code, const floa
   return P;
 }
 
-PeelQueue peel_queue(char* body, const PeelLayout& L, int32_t* status) {
-  PeelQueue Q{};
+TileQueue peel_queue(char* body, const PeelLayout& L, int32_t* status) {
+  TileQueue Q{};
   Q.state = reinterpret_cast<uint32_t*>(body + L.state);
   Q.ring = reinterpret_cast<uint64_t*>(body + L.ring);
-  Q.ctl = reinterpret_cast<PeelCtl*>(body + L.ctl);
+  Q.ctl = reinterpret_cast<TileCtl*>(body + L.ctl);
   Q.status = status;
   Q.cap = L.cap;
   return Q;
@@ -329,7 +329,7 @@ EngineParams engine_params(int64_t nrows, int64_t ncols, const uint8_t* code, co
 }
 
 // The queue-driven peeling solver, behind its gate if it has one.
-int enqueue_peel(RuleKind rk, bool adjoint, ValKind vk, const PeelGrid& P, const PeelQueue& Q, const int32_t* gate,
+int enqueue_peel(RuleKind rk, bool adjoint, ValKind vk, const PeelGrid& P, const TileQueue& Q, const int32_t* gate,
                  hipStream_t s) {
   const int ph = phase_begin("engine", s);
   if (launch_peel(rk, adjoint, vk, P, Q, gate, s) != hipSuccess) return FR_ERR_HIP;
@@ -541,12 +541,35 @@ const char* fr_status_string(int code) {
 }
 
 // Depression filling: per 62 x 62 tile a queue mark and three list slots,
-// plus the list lengths and the last-change word.
-constexpr int64_t kFillTile = 62;
-size_t fill_bytes(int64_t nrows, int64_t ncols) {
-  const size_t ntiles = (size_t)((nrows + kFillTile - 1) / kFillTile) * (size_t)((ncols + kFillTile - 1) / kFillTile);
-  return up((4 * ntiles + 4) * sizeof(int32_t)) + kAlign;
+// the list lengths and the last-change word, then the coarser grids' keys.
+constexpr int32_t kFillBatch = 8, kFillCoarseLaunches = 16;
+constexpr int64_t kFillCoarseSide = 8 * FILL_TILE;  // a coarser grid goes first where both sides are longer
+struct FillLayout {
+  size_t lists, total;
+  size_t zk[FILL_LEVELS], Fk[FILL_LEVELS];
+  int64_t nr[FILL_LEVELS], nc[FILL_LEVELS];
+  int32_t nlevels;
+};
+FillLayout fill_layout(int64_t nrows, int64_t ncols) {
+  FillLayout L{};
+  const size_t nt = (size_t)((nrows + FILL_TILE - 1) / FILL_TILE) * (size_t)((ncols + FILL_TILE - 1) / FILL_TILE);
+  size_t o = 0;
+  L.lists = o; o += up((4 * nt + 4) * sizeof(int32_t));
+  L.nr[0] = nrows;
+  L.nc[0] = ncols;
+  L.nlevels = 1;
+  while (L.nlevels < FILL_LEVELS && L.nr[L.nlevels - 1] > kFillCoarseSide && L.nc[L.nlevels - 1] > kFillCoarseSide) {
+    const int l = L.nlevels++;
+    L.nr[l] = (L.nr[l - 1] + FILL_STEP - 1) / FILL_STEP;
+    L.nc[l] = (L.nc[l - 1] + FILL_STEP - 1) / FILL_STEP;
+    const size_t n = (size_t)(L.nr[l] * L.nc[l]);
+    L.zk[l] = o; o += up(n * sizeof(uint32_t));
+    L.Fk[l] = o; o += up(n * sizeof(uint32_t));
+  }
+  L.total = o;
+  return L;
 }
+size_t fill_bytes(int64_t nrows, int64_t ncols) { return fill_layout(nrows, ncols).total + kAlign; }
 
 // Block iterations: the control block, the row-sweep layout (tiles as
 // short as 16 rows bound its per-tile words), then `vectors` float64 values
@@ -636,42 +659,71 @@ int fr_fill_depressions(const float* z, int64_t nrows, int64_t ncols, int rule, 
   if (!z || !f_out || static_cast<const void*>(z) == static_cast<const void*>(f_out)) return FR_ERR_ARG;
   if (!ws || ws_bytes < fill_bytes(nrows, ncols)) return FR_ERR_WORKSPACE;
   timing_reset();
-  const int32_t ntr = (int32_t)((nrows + kFillTile - 1) / kFillTile);
-  const int32_t ntc = (int32_t)((ncols + kFillTile - 1) / kFillTile);
-  const size_t ntiles = (size_t)ntr * ntc;
+  const FillLayout L = fill_layout(nrows, ncols);
+  char* base = aligned_base(ws);
+  const bool c8 = rule != FR_D4;
+  FillLevel level[FILL_LEVELS] = {};
+  uint32_t inc = eps != 0 ? 1u : 0u;
+  for (int l = 0; l < L.nlevels; ++l) {
+    FillLevel& V = level[l];
+    V.nr = L.nr[l];
+    V.nc = L.nc[l];
+    V.ntr = (int32_t)((V.nr + FILL_TILE - 1) / FILL_TILE);
+    V.ntc = (int32_t)((V.nc + FILL_TILE - 1) / FILL_TILE);
+    V.z = l == 0 ? z : nullptr;
+    V.F = l == 0 ? f_out : nullptr;
+    V.zk = l == 0 ? nullptr : reinterpret_cast<uint32_t*>(base + L.zk[l]);
+    V.Fk = l == 0 ? nullptr : reinterpret_cast<uint32_t*>(base + L.Fk[l]);
+    V.inc = inc;
+    // Steps from a cell of a block to the next block: FILL_STEP with
+    // diagonals, twice that without.
+    inc *= c8 ? FILL_STEP : 2 * FILL_STEP;
+  }
+  const size_t ntiles = (size_t)level[0].ntr * (size_t)level[0].ntc;
   FillState S;
-  S.ntr = ntr;
-  S.ntc = ntc;
-  S.queued = reinterpret_cast<int32_t*>(aligned_base(ws));
+  S.queued = reinterpret_cast<int32_t*>(base + L.lists);
   S.list = S.queued + ntiles;
   S.nlist = S.list + 3 * ntiles;
   S.last = S.nlist + 3;
-  const bool c8 = rule != FR_D4;
   const int ph = phase_begin("fill", stream);
   int rc = FR_OK;
-  if (launch_fill_init(z, f_out, nrows, ncols, S, dev_status, stream) != hipSuccess) rc = FR_ERR_HIP;
-  // Launches go out in batches; after each the host reads the length of the
-  // next work list: empty means no tile changed in the batch's final launch,
-  // so none can change any more.  Every launch lowers values or changes
-  // nothing, so this ends.
-  constexpr int32_t kBatch = 8;
-  for (int32_t k = 0; rc == FR_OK; k += kBatch) {
-    for (int32_t j = k; j < k + kBatch && rc == FR_OK; ++j)
-      if (launch_fill_tiles(z, f_out, nrows, ncols, eps != 0, c8, S, j, stream) != hipSuccess) rc = FR_ERR_HIP;
-    int32_t pending = 0, lastk = 0, st = 0;
-    if (rc != FR_OK ||
-        hipMemcpyAsync(&pending, S.nlist + (k + kBatch) % 3, sizeof pending, hipMemcpyDeviceToHost, stream) !=
-            hipSuccess ||
-        hipMemcpyAsync(&lastk, S.last, sizeof lastk, hipMemcpyDeviceToHost, stream) != hipSuccess ||
-        (dev_status && hipMemcpyAsync(&st, dev_status, sizeof st, hipMemcpyDeviceToHost, stream) != hipSuccess) ||
-        hipStreamSynchronize(stream) != hipSuccess) {
+  for (int l = 0; l + 1 < L.nlevels && rc == FR_OK; ++l)
+    if (launch_fill_coarse(level[l], level[l + 1], c8, stream) != hipSuccess) rc = FR_ERR_HIP;
+  // Coarsest level first.  A coarser level needs no end: whatever it has
+  // reached after kFillCoarseLaunches launches lies on or above the next
+  // one's surface.  On the grid itself launches go out in batches; after each
+  // the host reads the length of the next work list: empty means no tile is
+  // left that the batch's final launch could lower a cell of, so none can
+  // change any more.  Every launch lowers values or changes nothing, so this
+  // ends.  (A launch without work takes about 3 us, a read-back 110.)
+  for (int l = L.nlevels - 1; l >= 0 && rc == FR_OK; --l) {
+    if (launch_fill_init(level[l], l + 1 < L.nlevels ? &level[l + 1] : nullptr, S, dev_status, stream) != hipSuccess)
       rc = FR_ERR_HIP;
-      break;
+    if (l > 0) {
+      for (int32_t k = 0; k < kFillCoarseLaunches && rc == FR_OK; ++k)
+        if (launch_fill_tiles(level[l], c8, S, k, stream) != hipSuccess) rc = FR_ERR_HIP;
+      continue;
     }
-    if (st != 0) break;
-    if (pending == 0) {
-      if (launches_out) *launches_out = lastk + 2;  // through the first launch without a change
-      break;
+    const int32_t batch = L.nlevels > 1 ? 2 * kFillBatch : kFillBatch;
+    for (int32_t k = 0; rc == FR_OK; k += batch) {
+      for (int32_t j = k; j < k + batch && rc == FR_OK; ++j)
+        if (launch_fill_tiles(level[l], c8, S, j, stream) != hipSuccess) rc = FR_ERR_HIP;
+      int32_t pending = 0, lastk = 0, st = 0;
+      if (rc != FR_OK ||
+          hipMemcpyAsync(&pending, S.nlist + (k + batch) % 3, sizeof pending, hipMemcpyDeviceToHost, stream) !=
+              hipSuccess ||
+          hipMemcpyAsync(&lastk, S.last, sizeof lastk, hipMemcpyDeviceToHost, stream) != hipSuccess ||
+          (dev_status &&
+           hipMemcpyAsync(&st, dev_status, sizeof st, hipMemcpyDeviceToHost, stream) != hipSuccess) ||
+          hipStreamSynchronize(stream) != hipSuccess) {
+        rc = FR_ERR_HIP;
+        break;
+      }
+      if (st != 0) break;
+      if (pending == 0) {
+        if (launches_out) *launches_out = lastk + 2;  // through the first launch without a change
+        break;
+      }
     }
   }
   phase_end(ph, stream);

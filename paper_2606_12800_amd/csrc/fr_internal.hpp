@@ -323,30 +323,31 @@ hipError_t launch_ws_ctl(const WsParams& P, CallCtl* C, int pass, bool last, hip
 // leaves the queue empty).  Both return at once when P.gate is closed.
 hipError_t launch_engine_init(const EngineConfig& cfg, const EngineParams& P, hipStream_t s);
 hipError_t launch_engine_run(const EngineConfig& cfg, const EngineParams& P, hipStream_t s);
+// Device queue of tiles (fr_queue.hpp): its words, a cache line each, and its
+// arrays.
+struct TileCtl {
+  uint32_t head;   // next ticket to take
+  uint32_t pad0[31];
+  uint32_t tail;   // next ticket to give out
+  uint32_t pad1[31];
+  uint32_t left;   // tiles left: 0 ends the work
+  uint32_t stop;   // 1: given up (a cycle)
+  uint32_t pad2[30];
+};
+struct TileQueue {
+  uint32_t* state;         // per tile
+  uint64_t* ring;          // queue: ticket and tile
+  TileCtl* ctl;
+  int32_t* status;
+  uint32_t cap;            // ring entries: twice the tiles (a tile waits in the queue at most once; the rest keeps
+                           // a slow workgroup's ticket from being reached by the next round)
+};
 // Queue-driven peeling solver (fr_peel.hip): tiles of PEEL_ROWS x
 // peel_cols() cells.  Serves MFD, forward and adjoint, and the adjoint of
 // single receivers.  Tiles with float64 fractions are a little narrower, so
 // that two of them fit a compute unit's LDS.
 constexpr int PEEL_ROWS = 32;
 inline __host__ __device__ constexpr int peel_cols(bool frac64) { return frac64 ? 58 : 64; }
-// Queue and progress of one solve, a cache line each.
-struct PeelCtl {
-  uint32_t head;   // next ticket to take
-  uint32_t pad0[31];
-  uint32_t tail;   // next ticket to give out
-  uint32_t pad1[31];
-  uint32_t left;   // tiles with unfinished cells
-  uint32_t stop;   // 1: given up (a cycle)
-  uint32_t pad2[30];
-};
-struct PeelQueue {
-  uint32_t* state;         // per tile
-  uint64_t* ring;          // queue: ticket and tile
-  PeelCtl* ctl;
-  int32_t* status;
-  uint32_t cap;            // ring entries: twice the tiles (a tile waits in the queue at most once; the rest keeps
-                           // a slow workgroup's ticket from being reached by the next round)
-};
 struct PeelGrid {
   int64_t nrows, ncols;
   int32_t ntr, ntc;        // tile grid
@@ -367,8 +368,8 @@ struct PeelGrid {
 // A batch's workspace: this, its grids in schedule order, the schedule, each
 // grid's words, tile states, ring.
 struct PeelBatch {
-  PeelCtl ctl;
-  PeelQueue queue;
+  TileCtl ctl;
+  TileQueue queue;
   PeelGrid* grids;
   int32_t ngrids;
 };
@@ -388,7 +389,7 @@ template <>
 struct PeelFrac<RK_MULTI, VK_F64> {
   using T = double;
 };
-hipError_t launch_peel(RuleKind rk, bool adjoint, ValKind vk, const PeelGrid& P, const PeelQueue& Q,
+hipError_t launch_peel(RuleKind rk, bool adjoint, ValKind vk, const PeelGrid& P, const TileQueue& Q,
                        const int32_t* gate, hipStream_t s);
 // {sum over sinks, sum of the source} of the last solve (MFD, P.keep set).
 hipError_t launch_peel_mass(const PeelGrid& P, double* partial, int nblocks, double* out, const int32_t* gate,
@@ -400,18 +401,33 @@ hipError_t launch_peel_batch(const fr_tile* tiles_dev, int32_t ntiles, int order
 hipError_t launch_mass(RuleKind rk, ValKind vk, const EngineParams& P, double* partial,
                        int nblocks, double* mass_out, hipStream_t s);
 hipError_t launch_set_status(int32_t* status, int32_t code, hipStream_t s);
-// Depression filling: tile grid and work lists (workspace).
+// Depression filling (fr_fill.hip): the grid and coarser ones, each cell of
+// which stands for FILL_STEP x FILL_STEP cells of the one before.
+constexpr int FILL_TILE = 62;  // cells a tile owns per side
+constexpr int FILL_STEP = 8;
+constexpr int FILL_LEVELS = 6;
+struct FillLevel {
+  int64_t nr, nc;
+  int32_t ntr, ntc;   // tile grid
+  const float* z;     // elevations and surface: float32 on the grid itself,
+  float* F;
+  uint32_t* zk;       // order-preserving keys on coarser ones
+  uint32_t* Fk;
+  uint32_t inc;       // what the surface rises by from a cell to the next one upstream, in keys
+};
+// Work lists of a level's tiles.
 struct FillState {
-  int32_t ntr, ntc;  // tiles of 62 x 62 cells
   int32_t* queued;   // per tile: latest launch it was queued for
-  int32_t* list;     // three lists of ntr * ntc tile indices (ring)
+  int32_t* list;     // three lists of tile indices (ring)
   int32_t* nlist;    // [3] their lengths
   int32_t* last;     // latest launch in which a tile changed
 };
-hipError_t launch_fill_init(const float* z, float* F, int64_t nr, int64_t nc, const FillState& S, int32_t* status,
+// W's elevations from V's.
+hipError_t launch_fill_coarse(const FillLevel& V, const FillLevel& W, bool c8, hipStream_t s);
+// V's start: from the coarser level W's surface, or +inf inside; every tile listed.
+hipError_t launch_fill_init(const FillLevel& V, const FillLevel* W, const FillState& S, int32_t* status,
                             hipStream_t s);
-hipError_t launch_fill_tiles(const float* z, float* F, int64_t nr, int64_t nc, bool eps, bool c8,
-                             const FillState& S, int32_t k, hipStream_t s);
+hipError_t launch_fill_tiles(const FillLevel& V, bool c8, const FillState& S, int32_t k, hipStream_t s);
 hipError_t launch_zero_f64(double* p, int n, hipStream_t s);
 
 }  // namespace fr

@@ -57,7 +57,7 @@
 // float64 results the fractions are float64.
 #include <math.h>
 
-#include "fr_internal.hpp"
+#include "fr_queue.hpp"
 
 namespace fr {
 namespace {
@@ -65,32 +65,14 @@ namespace {
 constexpr int PT = 256;                // threads per workgroup
 constexpr int TR = PEEL_ROWS;
 constexpr uint64_t OPEN = ~0ull;       // word of a cell that is not final
-// Tile states.
-constexpr uint32_t ST_PENDING = 1, ST_RUNNING = 2, ST_DONE = 4;
 // Phases of the wavefronts' roles.
 constexpr int PH_RUN = 0, PH_STOP = 1;
 // Full polls of the surrounding cells without news before an idle tile is
 // let go: while other tiles are queued, and while none is.
 constexpr int LINGER_BUSY = 32, LINGER_IDLE = 96;
-// A workgroup without a tile gives up when neither the queue nor the count of
-// unfinished tiles has moved for this long (100 MHz ticks): the routing has a
-// cycle (single receivers from malformed codes).
-constexpr long long STUCK_TICKS = 20000000;
-
 __device__ constexpr float kInvSqrt2f = 0x1.6a09e6p-1f;
 __device__ constexpr double kSqrt2 = 1.4142135623730950488;
 
-__device__ __forceinline__ uint64_t ld64(const uint64_t* p) {
-  return (uint64_t)__hip_atomic_load(reinterpret_cast<unsigned long long*>(const_cast<uint64_t*>(p)),
-                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st64(uint64_t* p, uint64_t v) {
-  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)v, __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint32_t ld32(const uint32_t* p) {
-  return __hip_atomic_load(const_cast<uint32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ uint32_t l_ld(const uint32_t* p) {
   return __hip_atomic_load(const_cast<uint32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
@@ -100,9 +82,6 @@ __device__ __forceinline__ void l_st(uint32_t* p, uint32_t v) {
 // LDS operations of one wavefront are performed in issue order; this keeps
 // the compiler from moving data across the words that announce it.
 __device__ __forceinline__ void fence() { __atomic_signal_fence(__ATOMIC_SEQ_CST); }
-// The wavefront's stores are complete (device-coherent ones visible).
-__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 __device__ __forceinline__ uint64_t ballot(bool p) { return (uint64_t)__builtin_amdgcn_ballot_w64(p); }
 // x of lane - 1 / lane + 1 (mod 64).
 __device__ __forceinline__ uint32_t from_below(uint32_t x) {
@@ -182,58 +161,9 @@ __device__ __forceinline__ bool in_tile(int r, int c) {
   return (unsigned)r < (unsigned)TR && (unsigned)c < (unsigned)Tile<F>::TC;
 }
 
-// Takes a tile from the queue; -1 when all tiles are finished (or the solve
-// is given up).
-__device__ int32_t take_tile(const PeelQueue& P) {
-  PeelCtl* C = P.ctl;
-  uint32_t ticket = atomicAdd(&C->head, 1u);
-  uint32_t last_tail = 0, last_left = 0;
-  long long since = wall_clock64();
-  for (uint32_t it = 0;; ++it) {
-    const uint64_t w = ld64(P.ring + ticket % P.cap);
-    const uint32_t at = (uint32_t)(w >> 32);
-    if ((uint32_t)w != 0u && at == ticket) {
-      const uint32_t t = (uint32_t)w - 1u;
-      // Taken (an entry that is overwritten before this is queued again by
-      // the workgroup that overwrote it; whoever comes second finds the tile
-      // running).
-      atomicCAS(reinterpret_cast<unsigned long long*>(P.ring + ticket % P.cap), (unsigned long long)w, 0ull);
-      if (atomicCAS(P.state + t, ST_PENDING, ST_RUNNING) == ST_PENDING) return (int32_t)t;
-      ticket = atomicAdd(&C->head, 1u);
-      continue;
-    }
-    if ((uint32_t)w != 0u && (int32_t)(at - ticket) > 0) {
-      ticket = atomicAdd(&C->head, 1u);
-      continue;
-    }
-    __builtin_amdgcn_s_sleep(8);
-    if (it % 4u != 0u) continue;
-    const uint32_t left = ld32(&C->left), tail = ld32(&C->tail);
-    if (left == 0u || ld32(&C->stop)) return -1;
-    const long long now = wall_clock64();
-    if (left != last_left || tail != last_tail || it == 0) {
-      last_left = left;
-      last_tail = tail;
-      since = now;
-    } else if (now - since > STUCK_TICKS) {
-      atomicExch(&C->stop, 1u);
-      if (P.status) atomicCAS(P.status, 0, FR_ERR_NOTDAG);
-      return -1;
-    }
-  }
-}
-
 // Wakes tile t: queues it when it was idle.
-__device__ __forceinline__ void wake(const PeelQueue& P, uint32_t t) {
-  if (atomicOr(P.state + t, ST_PENDING) != 0u) return;
-  for (;;) {
-    const uint32_t ticket = atomicAdd(&P.ctl->tail, 1u);
-    const uint64_t old =
-        (uint64_t)atomicExch(reinterpret_cast<unsigned long long*>(P.ring + ticket % P.cap),
-                             ((unsigned long long)ticket << 32) | (t + 1u));
-    if ((uint32_t)old == 0u) return;
-    t = (uint32_t)old - 1u;  // an entry not taken yet: queue that tile again
-  }
+__device__ __forceinline__ void wake(const TileQueue& Q, uint32_t t) {
+  if (atomicOr(Q.state + t, ST_PENDING) == 0u) push_tile(Q, t);
 }
 
 // Out-fractions of the cell at place `at` (its validated mask m over the 8
@@ -299,7 +229,7 @@ __device__ __forceinline__ void put_fractions<double>(Tile<double>& T, int at, u
 // are found here, from the elevations, by the grid's rule (single receivers
 // run as fractions of 1, whose correction is 1).
 template <int RK, bool ADJ, int VK, bool BATCH, typename F>
-__device__ __forceinline__ void peel_tile(const PeelGrid& P, const PeelQueue& Q, Tile<F>& T, const int32_t tile) {
+__device__ __forceinline__ void peel_tile(const PeelGrid& P, const TileQueue& Q, Tile<F>& T, const int32_t tile) {
   constexpr bool CORRECT = RK == RK_MULTI && VK == VK_FF;
   constexpr bool ELEV = RK == RK_MULTI;  // elevations are read
   constexpr int TC = Tile<F>::TC;
@@ -831,7 +761,7 @@ __device__ __forceinline__ void note_simds(Tile<F>& T) {
 // Float fractions: three workgroups fit a compute unit's LDS, so three
 // wavefronts a SIMD; float64 ones: two.
 template <int RK, bool ADJ, int VK>
-__global__ __launch_bounds__(PT, RK == RK_MULTI && VK == VK_F64 ? 2 : 3) void k_peel(PeelGrid P, PeelQueue Q,
+__global__ __launch_bounds__(PT, RK == RK_MULTI && VK == VK_F64 ? 2 : 3) void k_peel(PeelGrid P, TileQueue Q,
                                                                                      const int32_t* gate) {
   using F = typename PeelFrac<RK, VK>::T;
   if (gate && *gate == 0) return;
@@ -850,7 +780,7 @@ __global__ __launch_bounds__(PT, RK == RK_MULTI && VK == VK_F64 ? 2 : 3) void k_
 // Many grids (float32 water, or counts of single receivers).
 __global__ __launch_bounds__(PT, 3) void k_peel_batch(const PeelBatch* B) {
   __shared__ Tile<float> T;
-  const PeelQueue Q = B->queue;
+  const TileQueue Q = B->queue;
   const PeelGrid* grids = B->grids;
   const int32_t ngrids = B->ngrids;
   note_simds(T);
@@ -886,7 +816,7 @@ __device__ bool last_rows_first(const PeelGrid& P, bool adjoint) {
 
 // No cell final, every tile queued (tickets from tile0 on; the ring's second
 // half empty).  Thread i of n.
-__device__ void open_grid(const PeelGrid& P, const PeelQueue& Q, bool adjoint, int64_t i0, int64_t stride) {
+__device__ void open_grid(const PeelGrid& P, const TileQueue& Q, bool adjoint, int64_t i0, int64_t stride) {
   const int64_t n = P.nrows * P.ncols;
   for (int64_t i = i0; i < n; i += stride) P.word[i] = OPEN;
   const int32_t nt = P.ntr * P.ntc;
@@ -901,14 +831,7 @@ __device__ void open_grid(const PeelGrid& P, const PeelQueue& Q, bool adjoint, i
   }
 }
 
-__device__ void open_queue(const PeelQueue& Q, uint32_t ntiles) {
-  Q.ctl->head = 0;
-  Q.ctl->tail = ntiles;
-  Q.ctl->left = ntiles;
-  Q.ctl->stop = 0;
-}
-
-__global__ __launch_bounds__(256) void k_peel_init(PeelGrid P, PeelQueue Q, int adjoint, const int32_t* gate) {
+__global__ __launch_bounds__(256) void k_peel_init(PeelGrid P, TileQueue Q, int adjoint, const int32_t* gate) {
   if (gate && *gate == 0) return;
   const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   open_grid(P, Q, adjoint != 0, i0, (int64_t)gridDim.x * blockDim.x);
@@ -1020,7 +943,7 @@ __global__ __launch_bounds__(1024) void k_peel_batch_setup(const fr_tile* tiles,
     __syncthreads();
   }
   if (t == 0) {
-    PeelQueue Q{};
+    TileQueue Q{};
     Q.cap = (uint32_t)(2 * tile0);
     Q.state = reinterpret_cast<uint32_t*>(ws + off);
     off += peel_align((size_t)tile0 * sizeof(uint32_t));
@@ -1078,7 +1001,7 @@ hipError_t resident(K* kernel, int64_t* out) {
 }
 
 template <int RK, bool ADJ, int VK>
-hipError_t peel_t(const PeelGrid& P, const PeelQueue& Q, const int32_t* gate, hipStream_t s) {
+hipError_t peel_t(const PeelGrid& P, const TileQueue& Q, const int32_t* gate, hipStream_t s) {
   int64_t grid = 0;
   const hipError_t e = resident(k_peel<RK, ADJ, VK>, &grid);
   if (e != hipSuccess) return e;
@@ -1090,7 +1013,7 @@ hipError_t peel_t(const PeelGrid& P, const PeelQueue& Q, const int32_t* gate, hi
 
 }  // namespace
 
-hipError_t launch_peel(RuleKind rk, bool adjoint, ValKind vk, const PeelGrid& P, const PeelQueue& Q,
+hipError_t launch_peel(RuleKind rk, bool adjoint, ValKind vk, const PeelGrid& P, const TileQueue& Q,
                        const int32_t* gate, hipStream_t s) {
   int64_t b = (P.nrows * P.ncols + 255) / 256;
   if (b > 4096) b = 4096;

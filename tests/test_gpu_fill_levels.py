@@ -1,0 +1,47 @@
+"""Depression filling on grids with coarser levels before them (both sides
+above 496 cells, a block of 8 x 8 cells to a coarse cell): ragged last blocks,
+lakes wider than a coarse tile and white noise, bit for bit against the
+oracle's priority flood."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+fr = pytest.importorskip("paper_2606_12800_amd")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _device():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    fr.load_library()
+    yield
+
+
+def terrain(kind, nr, nc):
+    if kind == "fractal":
+        return synth.dem(61, nr, nc, tilt=0.0)
+    noise = synth.uniform(62, synth.STREAM_NOISE, nr * nc).reshape(nr, nc)
+    if kind == "noise":
+        return noise.astype(np.float32) - np.float32(0.5)  # both signs
+    # A bowl: one lake over nearly the whole grid, spilling at one edge cell.
+    rr, cc = np.meshgrid(np.arange(nr), np.arange(nc), indexing="ij")
+    z = -np.minimum(np.minimum(rr, nr - 1 - rr), np.minimum(cc, nc - 1 - cc)) + noise * 1e-3
+    z[0, nc // 3] = -0.25
+    return z.astype(np.float32)
+
+
+@pytest.mark.parametrize("rule,conn", [("d8", 8), ("d4", 4)])
+@pytest.mark.parametrize("kind,shape", [("fractal", (497, 497)), ("fractal", (505, 1003)), ("noise", (497, 520)),
+                                        ("bowl", (601, 499)), ("fractal", (496, 2000))])
+def test_fill_with_coarser_levels(kind, shape, rule, conn):
+    print(f"fill levels {kind} {shape} {rule}", flush=True)
+    z = terrain(kind, *shape)
+    for eps in (True, False):
+        f = fr.fill_depressions(torch.from_numpy(z).cuda(), rule, eps).cpu().numpy()
+        ref = oracle.fill_depressions(z, conn, eps)
+        assert np.array_equal(f.view(np.uint32), ref.view(np.uint32)), eps
