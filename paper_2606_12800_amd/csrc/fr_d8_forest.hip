@@ -12,7 +12,7 @@ namespace {
 __device__ __forceinline__ int64_t blk_row(const D8Params& P, int64_t r) { return r / ((int64_t)P.th * P.bt_r); }
 __device__ __forceinline__ int64_t blk_col(const D8Params& P, int64_t c) { return c / ((int64_t)TW * P.bt_c); }
 
-// The work-queue forest's sums (below) are held split, v = hi * 2^56 + lo
+// The chain-following forest's sums (below) are held split, v = hi * 2^56 + lo
 // with 0 <= lo < 2^56 for every term added, so that the low word never
 // carries: an exit receives its own term and at most 196 children's (one per
 // cell of the ring around its tile), below 2^64 together, and both words
@@ -30,19 +30,18 @@ __device__ __forceinline__ i128 kf_join(u128 w) {
   return (i128)(long long)(unsigned long long)(w >> 64) * ((i128)1 << 56) + (i128)(unsigned long long)w;
 }
 
-// The work-queue forest's queue (below): one 32-bit word per exit in the
+// The chain-following forest's leaves (below): a 32-bit word each in the
 // second pending-additions buffer, which that forest does not use otherwise.
 template <int VK>
-__device__ __forceinline__ uint32_t* kf_queue(const D8Params& P) {
+__device__ __forceinline__ uint32_t* kf_leaf_list(const D8Params& P) {
   return VK != VK_NONE ? reinterpret_cast<uint32_t*>(P.ex_fx[1]) : reinterpret_cast<uint32_t*>(P.ex_cnt[1]);
 }
 
 // Link: each exit's local sum into fixed point (sum buffer 0; both
-// pending buffers cleared -- for the work-queue forest only its queue
-// word), and its parent -- the exit its water reaches
-// next (block iterations: only inside its block).  An exit list that
+// pending buffers cleared, which the chain-following forest does not use),
+// and its parent -- the exit its water reaches next (block iterations: only inside its block).  An exit list that
 // overflowed its capacity opens the engine's gate instead (block
-// iterations: an error).  For the work-queue forest (QUEUE) each exit also
+// iterations: an error).  For the chain-following forest (QUEUE) each exit also
 // counts itself among its parent's children (kf_children_of), starting
 // from the zero that the tile pass that listed the exits left there.
 template <int VK, bool CNT, bool ITER, bool QUEUE = false>
@@ -57,9 +56,7 @@ __global__ __launch_bounds__(256) void k_d8_link(D8Params P) {
   }
   const int E = VK != VK_NONE ? fx_exponent<VK>(P, n) + (QUEUE ? KF_FX_HEAD : 0) : 0;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-    if (QUEUE) {
-      kf_queue<VK>(P)[i] = 0u;
-    } else {
+    if (!QUEUE) {
       if (VK != VK_NONE) {
         P.ex_fx[1][i] = 0;
         P.ex_fx[2][i] = 0;
@@ -193,23 +190,29 @@ __global__ __launch_bounds__(256) void k_d8_round(D8Params P, int j, int last) {
 }
 
 // ---------------------------------------------------------------------------
-// The exit forest by a work queue (tile-forest path, where the forest holds
-// tens of millions of exits and is about a thousand deep, so that pointer
-// doubling would move every exit's sum through ten rounds of random
-// atomics).  Each exit waits for its children; once the last one has added
-// its total, the exit is final and enters the queue; whoever takes it adds
-// its total to its parent, once.  Sums stay 128-bit integers (the order of
-// the atomics changes no bit).  Children are counted by the link step
-// (kf_children_of), the queue holds exit + 1 (0: not yet written)
-// (kf_queue, cleared by the link step), and no addition is left pending
-// for the totals.  Every access to the forest's shared words here is a
-// device-coherent atomic, so the XCDs' caches need no write-back or
-// invalidation; a finished exit's reads of its sums depend on the queue
-// word that named it.  Every wait ends: a wavefront that sees the queue's
-// tail stand still for KF_STALL_TICKS gives up (a cycle of exits, from
-// malformed codes) and reports FR_ERR_NOTDAG.
-constexpr int KF_HEAD = 8, KF_TAIL = 9;          // slots of P.flags
-constexpr uint64_t KF_STALL_TICKS = 5000000ull;  // 50 ms of the 100 MHz clock
+// The exit forest by following chains (tile-forest path, where the forest
+// holds tens of millions of exits and is about a thousand deep, so that
+// pointer doubling would move every exit's sum through ten rounds of random
+// atomics).  The leaves are listed; a lane takes a leaf, adds its total to
+// its parent and counts it off among the parent's children; the lane that
+// counts off the last child goes on with the parent, whose sum is then
+// complete, and any other is done with its chain.  So every exit's total
+// moves once, nobody waits for anybody, and one step of a chain costs three
+// trips to memory (the sum, the additions' completion, the count-down; the
+// parent after next is read beside them).  What bounds it is those trips
+// along the deepest chain and, on large grids, the random atomics.  With the
+// final parents put into a queue for any wavefront to take, a step also took
+// a reservation, a store, a poll and a read of the queue: 2.70 -> 1.34 ms at
+// 3.1 million exits (filled 12000 x 9001), 345 -> 230 us at 0.1 million (D4,
+// float64, filled 1531 x 2111).
+// Sums stay 128-bit integers (the order of the atomics changes no bit).
+// Children are counted by the link step (kf_children_of), and no addition is
+// left pending for the totals.  Every access to the forest's shared words
+// here is a device-coherent atomic, so the XCDs' caches need no write-back or
+// invalidation.  Exits in a cycle (malformed codes) are never taken up; the
+// totals step compares the exits finished with those listed and reports
+// FR_ERR_NOTDAG.
+constexpr int KF_HEAD = 8, KF_LEAVES = 9, KF_DONE = 10;  // slots of P.flags
 
 // An exit's count of children not yet final.  With counts it shares the
 // 64-bit word of the exit's count sum (count << 32 | children; counts stay
@@ -220,37 +223,9 @@ __device__ __forceinline__ uint32_t kf_children_of(const D8Params& P, uint32_t i
   return CNT ? (uint32_t)P.ex_cnt[0][i] : P.anc[1][i];
 }
 
-// Appends up to KF_PER_LANE items per lane (bit k of `mask`: par[k]) with
-// one atomic per wavefront.
-template <int K>
-__device__ __forceinline__ void kf_push_many(const D8Params& P, uint32_t* q, uint32_t mask, const uint32_t (&par)[K]) {
-  const uint32_t lane = threadIdx.x & 63;
-  uint32_t incl = (uint32_t)__popc(mask);
-  const uint32_t mine = incl;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const uint32_t y = (uint32_t)__shfl_up((int)incl, o, 64);
-    if (lane >= (uint32_t)o) incl += y;
-  }
-  const uint32_t tot = (uint32_t)__shfl((int)incl, 63, 64);
-  if (tot == 0u) return;  // uniform
-  uint32_t base = 0;
-  if (lane == 0)
-    base = __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(&P.flags[KF_TAIL]), tot, __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_AGENT);
-  uint32_t at = (uint32_t)__shfl((int)base, 0, 64) + incl - mine;
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    if ((mask >> k) & 1u) {
-      __hip_atomic_store(&q[at], par[k] + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      ++at;
-    }
-  }
-}
-
-// The leaves (holes included) into the queue: each workgroup scans a chunk
-// of KF_LEAF_CHUNK exits and reserves its slots with one atomic (the queue's
-// tail is one word: atomics on it serialise).
+// The list of leaves (holes included): each workgroup scans a chunk of
+// KF_LEAF_CHUNK exits and reserves its places with one atomic (the list's
+// length is one word: atomics on it serialise).
 constexpr uint32_t KF_LEAF_PER_THREAD = 16;
 constexpr uint32_t KF_LEAF_CHUNK = 256u * KF_LEAF_PER_THREAD;
 
@@ -258,7 +233,7 @@ template <int VK, bool CNT>
 __global__ __launch_bounds__(256) void k_kf_leaves(D8Params P) {
   const uint32_t n = *P.n_exits;
   if (n > P.cap || n == 0u) return;  // uniform
-  uint32_t* q = kf_queue<VK>(P);
+  uint32_t* q = kf_leaf_list<VK>(P);
   __shared__ uint32_t s_cnt[4], s_base;
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (uint32_t c0 = blockIdx.x * KF_LEAF_CHUNK; c0 < n; c0 += gridDim.x * KF_LEAF_CHUNK) {  // uniform
@@ -284,7 +259,7 @@ __global__ __launch_bounds__(256) void k_kf_leaves(D8Params P) {
     __syncthreads();
     if (threadIdx.x == 0) {
       const uint32_t tot = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
-      s_base = tot ? __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(&P.flags[KF_TAIL]), tot, __ATOMIC_RELAXED,
+      s_base = tot ? __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(&P.flags[KF_LEAVES]), tot, __ATOMIC_RELAXED,
                                             __HIP_MEMORY_SCOPE_AGENT)
                    : 0u;
     }
@@ -310,134 +285,148 @@ __device__ __forceinline__ u128 kf_load_fx(const u128* p) {
   return lo | (hi << 64);
 }
 
-// Persistent: each wavefront takes KF_SLOTS queue slots at a time (lane l
-// holds slots base + 64 k + l) and each lane finishes the exits its slots
-// receive, in whatever order they arrive; a slot is written only once its
-// exit is final, and every exit is written exactly once, so all n slots
-// fill (a cycle aside).
+// Persistent: each wavefront takes KF_BLOCK leaves of the list at a time and
+// deals them to its lanes' KF_PER_LANE chains as these end; the chains' steps
+// are issued together, each memory step for all of them before its results
+// are waited for.
 constexpr int KF_PER_LANE = 8;
-constexpr uint32_t KF_SLOTS = 64u * KF_PER_LANE;
+constexpr uint32_t KF_BLOCK = 64u * KF_PER_LANE;
 
 template <int VK, bool CNT>
-__global__ __launch_bounds__(256) void k_kf_run(D8Params P) {
+__global__ __launch_bounds__(256, 4) void k_kf_run(D8Params P) {
   constexpr int K = KF_PER_LANE;
   const uint32_t n = *P.n_exits;
   if (n > P.cap || n == 0u) return;  // uniform
-  uint32_t* q = kf_queue<VK>(P);
+  const uint32_t* q = kf_leaf_list<VK>(P);
   uint32_t* head = reinterpret_cast<uint32_t*>(&P.flags[KF_HEAD]);
-  const uint32_t* tail = reinterpret_cast<const uint32_t*>(&P.flags[KF_TAIL]);
+  const uint32_t leaves = *reinterpret_cast<const uint32_t*>(&P.flags[KF_LEAVES]);
   const uint32_t lane = threadIdx.x & 63;
-  uint32_t tail_seen = 0;
-  uint64_t t_seen = __builtin_amdgcn_s_memrealtime();
+  uint32_t e[K], par[K];  // the chain's exit and its parent
+  unsigned long long c[K];
+  uint32_t live = 0, fresh = 0;  // bit k: chain k under way; its count not read yet
+  uint32_t next = 0, end = 0, finished = 0;
+  bool more = true;  // leaves beyond this wavefront's block
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    e[k] = 0u;
+    par[k] = NONE;
+    c[k] = 0ull;
+  }
   for (;;) {
-    uint32_t base = 0;
-    if (lane == 0) base = __hip_atomic_fetch_add(head, KF_SLOTS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    base = (uint32_t)__shfl((int)base, 0, 64);
-    if (base >= n) return;  // uniform: every slot has been taken
-    uint32_t todo = 0;  // bit k: slot base + 64 k + lane not finished
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-      if (base + 64u * k + lane < n) todo |= 1u << k;
-    uint32_t avail = n;  // slots below the tail seen last (the others cannot be written yet)
-    while (__ballot(todo != 0u)) {  // uniform
-      // The lane's exits that have arrived are finished together, each step
-      // issued for all of them before its results are waited for: the
-      // queue words, the parents, the sums, the additions to the parents
-      // (both words at once: they never carry), then one wait, then the
-      // count-downs.  The parents made final go into the queue together.
-      uint32_t e[K], par[K];
-#pragma unroll
-      for (int k = 0; k < K; ++k) {
-        e[k] = 0u;
-        if (((todo >> k) & 1u) && base + 64u * k + lane < avail)
-          e[k] = __hip_atomic_load(&q[base + 64u * k + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // Chains that ended take the next leaves.
+    if (next == end && more && __ballot(live != (1u << K) - 1u)) {
+      if (lane == 0) next = __hip_atomic_fetch_add(head, KF_BLOCK, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      next = (uint32_t)__shfl((int)next, 0, 64);
+      if (next >= leaves) {
+        next = end = leaves;
+        more = false;
+      } else {
+        end = leaves - next > KF_BLOCK ? next + KF_BLOCK : leaves;
       }
-      // The arrived exits' parents, sums and counts, loaded together (none
-      // of them depends on another; a root's sums are loaded and unused).
-      uint32_t got = 0;
-      u128 x[K];
-      unsigned long long c[K];
+    }
+    uint32_t taken = 0;
+    if (next != end) {  // uniform
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        par[k] = NONE;
-        x[k] = 0;
-        c[k] = 0ull;
-        if (e[k] != 0u) {
-          got |= 1u << k;
+        const uint64_t open = __ballot(((live >> k) & 1u) == 0u);
+        const uint32_t at = next + (uint32_t)__popcll(open & ((1ull << lane) - 1ull));
+        if (((live >> k) & 1u) == 0u && at < end) {
+          e[k] = q[at];
+          taken |= 1u << k;
+        }
+        const uint32_t m = (uint32_t)__popcll(open);
+        next = end - next > m ? next + m : end;
+      }
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if ((taken >> k) & 1u) {
           e[k] -= 1u;
           par[k] = P.anc[0][e[k]];
+        }
+      live |= taken;
+      fresh |= taken;
+    }
+    if (__ballot(live != 0u) == 0ull) {
+      if (!more) break;  // uniform
+      continue;
+    }
+    // The chains' sums (and a leaf's count; later ones are known from the
+    // count-down), and the parents' parents.
+    u128 x[K];
+    uint32_t up[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      x[k] = 0;
+      up[k] = NONE;
+      if ((live >> k) & 1u) {
+        if (par[k] >= n) {  // a root (or a hole): the chain ends
+          par[k] = NONE;
+        } else {
+          up[k] = P.anc[0][par[k]];
           if (VK != VK_NONE) x[k] = kf_load_fx(&P.ex_fx[0][e[k]]);
-          if (CNT)  // the exit's count (its children are all final: the low word is 0)
+          if (CNT && ((fresh >> k) & 1u))
             c[k] = __hip_atomic_load(reinterpret_cast<unsigned long long*>(&P.ex_cnt[0][e[k]]), __ATOMIC_RELAXED,
                                      __HIP_MEMORY_SCOPE_AGENT) >> 32;
         }
       }
-      todo &= ~got;
-#pragma unroll
-      for (int k = 0; k < K; ++k)
-        if (par[k] >= n) par[k] = NONE;
-      if (VK != VK_NONE) {
-        // The exit's total, split again, into its parent's two words: no
-        // carry, no returned value.
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          if (par[k] != NONE) {
-            const u128 w = kf_split(kf_join(x[k]));
-            unsigned long long* pw = reinterpret_cast<unsigned long long*>(&P.ex_fx[0][par[k]]);
-            if ((unsigned long long)w != 0ull)
-              __hip_atomic_fetch_add(pw, (unsigned long long)w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((unsigned long long)(w >> 64) != 0ull)
-              __hip_atomic_fetch_add(pw + 1, (unsigned long long)(w >> 64), __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_AGENT);
-          }
-        }
-      }
-      // The last child makes the parent final: the additions above have
-      // completed (every access to the forest here is a device-coherent
-      // atomic, so no cache needs writing back) before the children go
-      // down, and a parent is queued only after its children have reached
-      // zero.  With counts, one atomic adds the count and counts the child
-      // off (count << 32, minus one).
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      uint32_t pmask = 0;
+    }
+    finished += (uint32_t)__popc(live);
+    fresh = 0;
+    if (VK != VK_NONE) {
+      // The exit's total, split again, into its parent's two words: no
+      // carry, no returned value.
 #pragma unroll
       for (int k = 0; k < K; ++k) {
-        if (par[k] != NONE) {
-          uint32_t left;
-          if (CNT)
-            left = (uint32_t)__hip_atomic_fetch_add(reinterpret_cast<unsigned long long*>(&P.ex_cnt[0][par[k]]),
-                                                    (c[k] << 32) - 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          else
-            left = __hip_atomic_fetch_add(&P.anc[1][par[k]], 0xFFFFFFFFu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (left == 1u) pmask |= 1u << k;
+        if (((live >> k) & 1u) && par[k] != NONE) {
+          const u128 w = kf_split(kf_join(x[k]));
+          unsigned long long* pw = reinterpret_cast<unsigned long long*>(&P.ex_fx[0][par[k]]);
+          if ((unsigned long long)w != 0ull)
+            __hip_atomic_fetch_add(pw, (unsigned long long)w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if ((unsigned long long)(w >> 64) != 0ull)
+            __hip_atomic_fetch_add(pw + 1, (unsigned long long)(w >> 64), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
       }
-      kf_push_many(P, q, pmask, par);
-      if (__ballot(todo != 0u)) {
-        // Waiting for slots still empty: give up when the queue stops
-        // growing (the exits left form a cycle).
-        uint32_t tl = 0;
-        if (lane == 0) tl = __hip_atomic_load(tail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        tl = (uint32_t)__shfl((int)tl, 0, 64);
-        avail = tl;
-        const uint64_t now = __builtin_amdgcn_s_memrealtime();
-        if (tl != tail_seen) {
-          tail_seen = tl;
-          t_seen = now;
-        } else if (now - t_seen > KF_STALL_TICKS) {
-          if (lane == 0) set_status(P.status, FR_ERR_NOTDAG);
-          return;
-        }
-        __builtin_amdgcn_s_sleep(2);
+    }
+    // The additions above have completed (every access to the forest here is
+    // a device-coherent atomic, so no cache needs writing back) before the
+    // children go down.  With counts, one atomic adds the count and counts
+    // the child off (count << 32, minus one), and its old value gives the
+    // parent's own count to the last child.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    unsigned long long old[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      old[k] = 0ull;
+      if (((live >> k) & 1u) && par[k] != NONE) {
+        if (CNT)
+          old[k] = __hip_atomic_fetch_add(reinterpret_cast<unsigned long long*>(&P.ex_cnt[0][par[k]]),
+                                          (c[k] << 32) - 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+          old[k] = __hip_atomic_fetch_add(&P.anc[1][par[k]], 0xFFFFFFFFu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (((live >> k) & 1u) && par[k] != NONE && (uint32_t)old[k] == 1u) {
+        c[k] += old[k] >> 32;
+        e[k] = par[k];
+        par[k] = up[k];
+      } else {
+        live &= ~(1u << k);
       }
     }
   }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) finished += (uint32_t)__shfl_xor((int)finished, o, 64);
+  if (lane == 0 && finished)
+    __hip_atomic_fetch_add(reinterpret_cast<uint32_t*>(&P.flags[KF_DONE]), finished, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The totals -- sums plus the last round's pending additions -- back from
 // fixed point into float-float or float64, where phase C reads them (the
 // pointer buffers' memory, free again); counts into sum buffer 0.  The
-// work-queue forest leaves no pending additions, its count words are
+// chain-following forest leaves no pending additions, its count words are
 // shifted down past their children, and with values each exit's total and
 // count go out as one 16-byte record (tile_total_rec), so that the tile
 // pass gathers one cache line per exit instead of three.
@@ -445,6 +434,8 @@ template <int VK, bool CNT, bool QUEUE = false>
 __global__ __launch_bounds__(256) void k_d8_totals(D8Params P) {
   const uint32_t n = *P.n_exits;
   if (n > P.cap) return;  // uniform
+  if (QUEUE && blockIdx.x == 0 && threadIdx.x == 0 && *reinterpret_cast<const uint32_t*>(&P.flags[KF_DONE]) != n)
+    set_status(P.status, FR_ERR_NOTDAG);  // exits in a cycle were never taken up
   const int f = QUEUE ? 0 : P.ctl->forest_final;
   const int E = VK != VK_NONE ? fx_exponent<VK>(P, n) + (QUEUE ? KF_FX_HEAD : 0) : 0;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
