@@ -16,7 +16,12 @@ namespace {
 
 constexpr int RCV_THREADS = 256;
 constexpr int RCV_COLS = RCV_THREADS * 4;  // columns per workgroup
-constexpr int RCV_RPB = 32;                // rows per workgroup
+// Rows per workgroup: a strip's rows wait for their loads one after another
+// (about 1 us each), so grids that 32 rows would not split into 2048
+// workgroups take fewer, down to 4 (the two halo rows come from L2).  D8 and
+// MFD at 32 rows and here: 256^2 40/25 -> 10/8 us, 1531 x 2111 52/35 ->
+// 17/15, 4096^2 53/37 -> 35/26; from 8192^2 (110/80) on 32 rows stay.
+constexpr int RCV_RPB = 32, RCV_RPB_MIN = 4, RCV_BLOCKS = 2048;
 
 struct Row6 {
   float v[6];  // columns c0-1 .. c0+4
@@ -76,11 +81,11 @@ __device__ __forceinline__ uint8_t cell_code(const Row6& up, const Row6& mid, co
 template <int RULE, bool VEC>
 __global__ __launch_bounds__(RCV_THREADS) void k_receivers(const float* __restrict__ z, int64_t nrows,
                                                            int64_t ncols, uint8_t* __restrict__ code,
-                                                           int32_t* status) {
+                                                           int32_t* status, int rpb) {
   const int lane = threadIdx.x & 63;
   const int64_t c0 = (int64_t)blockIdx.x * RCV_COLS + (int64_t)threadIdx.x * 4;
-  const int64_t r0 = (int64_t)blockIdx.y * RCV_RPB;
-  const int64_t r1 = r0 + RCV_RPB < nrows ? r0 + RCV_RPB : nrows;
+  const int64_t r0 = (int64_t)blockIdx.y * rpb;
+  const int64_t r1 = r0 + rpb < nrows ? r0 + rpb : nrows;
   Row6 up = assemble(load_raw<VEC>(z, nrows, ncols, r0 - 1, c0, lane), lane);
   Row6 mid = assemble(load_raw<VEC>(z, nrows, ncols, r0, c0, lane), lane);
   RawRow dn_raw = load_raw<VEC>(z, nrows, ncols, r0 + 1, c0, lane);
@@ -114,15 +119,17 @@ __global__ __launch_bounds__(RCV_THREADS) void k_receivers(const float* __restri
 template <int RULE>
 hipError_t launch_rule(const float* z, int64_t nrows, int64_t ncols, uint8_t* code, int32_t* status,
                        hipStream_t s) {
-  const dim3 grid((unsigned)((ncols + RCV_COLS - 1) / RCV_COLS),
-                  (unsigned)((nrows + RCV_RPB - 1) / RCV_RPB));
+  const int64_t strips = (ncols + RCV_COLS - 1) / RCV_COLS;
+  int rpb = RCV_RPB;
+  while (rpb > RCV_RPB_MIN && strips * ((nrows + rpb - 1) / rpb) < RCV_BLOCKS) rpb /= 2;
+  const dim3 grid((unsigned)strips, (unsigned)((nrows + rpb - 1) / rpb));
   const bool vec = (ncols % 4 == 0) && ((uintptr_t)z % 16 == 0) && ((uintptr_t)code % 4 == 0);
   if (vec)
     hipLaunchKernelGGL((k_receivers<RULE, true>), grid, dim3(RCV_THREADS), 0, s, z, nrows, ncols, code,
-                       status);
+                       status, rpb);
   else
     hipLaunchKernelGGL((k_receivers<RULE, false>), grid, dim3(RCV_THREADS), 0, s, z, nrows, ncols, code,
-                       status);
+                       status, rpb);
   return hipGetLastError();
 }
 
