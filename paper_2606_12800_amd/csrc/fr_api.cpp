@@ -802,19 +802,12 @@ int fr_accumulate(const float* z, const uint8_t* code, int64_t nrows, int64_t nc
                                       : (!multi && g_path == FR_PATH_AUTO ? FR_SERVED_ROWS : FR_SERVED_SWEEP));
   if (launch_ctl_init(C, first, stream) != hipSuccess) return FR_ERR_HIP;
   int rc = FR_OK;
-  const int64_t n = nrows * ncols;
   if (!multi && (g_path == FR_PATH_AUTO || tiles_only)) {
-    rc = enqueue_d8(code, nrows, ncols, rain, rain_dtype, cfg.vk, q32, q64, counts_out, mass_out, dev_status, body,
-                    C, tiles_only, stream);
-    if (rc != FR_OK) return rc;
-    // Neither list can overflow: the row sweeps' holds every cell on grids
-    // up to 2^22 cells, the tile forest's every cell on a tile perimeter.
-    if (n <= kFullCapacityCells || tiles_only) return FR_OK;
-    // Overflow fallback: the engine and its mass reduction, behind the gate.
-    if ((rc = enqueue_engine(cfg, P, stream)) != FR_OK) return rc;
-    if (mass_out && launch_mass(cfg.rk, cfg.vk, P, partial, kMassBlocks, mass_out, stream) != hipSuccess)
-      return FR_ERR_HIP;
-    return FR_OK;
+    // The row sweeps' list holds every cell on grids up to 2^22 cells; on
+    // larger ones the tile forest, whose list holds every cell on a tile
+    // perimeter, serves the call when it overflows.
+    return enqueue_d8(code, nrows, ncols, rain, rain_dtype, cfg.vk, q32, q64, counts_out, mass_out, dev_status, body,
+                      C, tiles_only, stream);
   }
   // Several receivers: the row sweep where no cell sends against a row
   // order, else the peeling solver.
