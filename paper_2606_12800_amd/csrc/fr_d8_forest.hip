@@ -512,7 +512,12 @@ hipError_t forest_t(const D8Params& P, hipStream_t s) {
   const dim3 g(forest_grid(P.cap)), b(256);
   hipLaunchKernelGGL((k_d8_link<VK, CNT, ITER>), g, b, 0, s, P);
   const int R = forest_rounds(P.cap);
-  for (int j = 0; j < R; ++j) hipLaunchKernelGGL((k_d8_round<VK, CNT>), g, b, 0, s, P, j, j == R - 1 ? 1 : 0);
+  // Rounds from the 13th on have work only in forests more than 4096 exits
+  // deep: fewer workgroups, so that those that find nothing return sooner
+  // (2048^2 387 -> 381 us, 1024^2 268 -> 262).
+  const dim3 late(g.x < 512 ? g.x : 512);
+  for (int j = 0; j < R; ++j)
+    hipLaunchKernelGGL((k_d8_round<VK, CNT>), j < 12 ? g : late, b, 0, s, P, j, j == R - 1 ? 1 : 0);
   hipLaunchKernelGGL((k_d8_totals<VK, CNT>), g, b, 0, s, P);
   return hipGetLastError();
 }
