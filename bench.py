@@ -33,7 +33,7 @@ PHASE_BYTES = {
     "d8_tiles": (1 + 4) + (1 + 4 + 4 + 8),
 }
 PHASE_KERNEL = {"receivers": "k_receivers", "d8_up": "k_d8_a (root + local sweep)", "d8_down": "k_d8_c",
-                "d8_tiles": "k_d8t (tile forest, phases A and C) + exit forest work queue"}
+                "d8_tiles": "k_d8t (tile forest, phases A and C) + exit forest"}
 ACC_BYTES = 1 + 4 + 4 + 8     # whole accumulate call: code, rain in; q, counts out
 ROUTE_BYTES = 4 + 1 + ACC_BYTES  # whole route: receivers (z in, code out) + accumulate
 # HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE runs calibrated
@@ -46,13 +46,7 @@ MEASURED_TRAFFIC = {
         "d8_up": (1.3366e10, "profiles/d8_43360_hbm_traffic.md"),
         "d8_down": (3.3176e10, "profiles/d8_43360_hbm_traffic.md"),
     },
-    # The tile phase of the filled route: both tile kernels and the exit
-    # forest's work queue (link with the children's counts, leaves, queue,
-    # totals).
-    ("d8_filled", 43360, 43360): {"d8_tiles": (9.3017e10, "profiles/d8_43360_filled_tile_forest.md")},
     ("mfd", 16384, 16384): {"row_sweep": (5.3063e9, "profiles/mfd_16384_row_sweep.md")},
-    ("adjoint", 4096, 4096): {"sweep": (6.987e8, "profiles/sweep_and_batch_hbm_traffic.md")},
-    ("batched", 512): {"batch": (2.472e10, "profiles/sweep_and_batch_hbm_traffic.md")},
 }
 # Algorithmic bytes per cell of the secondary workloads' dominant kernel
 # (arrays visible at the C ABI, each touched once): MFD float32 sweep z 4 +
@@ -215,14 +209,14 @@ def run_secondary(args, workload):
                    "cells": n * n},
         "detail": out,
     }
-    # The sweeps are bound by the latency of their row steps, not by HBM;
-    # the roofline below states how far from the HBM bound that leaves them.
-    # The dominant sweep is the row sweep (k_ms) where no cell sends
-    # against the row order, else the windowed wavefront sweep.
+    # The solvers are bound by the latency of their steps along flow paths,
+    # not by HBM; the roofline below states how far from the HBM bound that
+    # leaves them.  The dominant kernel is the row sweep (k_ms) where no cell
+    # sends against the row order, else the peeling solver (k_peel).
     ph = out["f32"]["phase_ms"]
-    phase = "row_sweep" if ph.get("row_sweep", 0.0) >= ph.get("sweep", 0.0) else "sweep"
+    phase = "row_sweep" if ph.get("row_sweep", 0.0) >= ph.get("engine", 0.0) else "engine"
     ms = ph.get(phase, out["f32"]["ms_per_step"])
-    kernel = "k_ms (row sweep, producer + consumer)" if phase == "row_sweep" else "k_ws_pass (all passes)"
+    kernel = "k_ms (row sweep, producer + consumer)" if phase == "row_sweep" else "k_peel (peeling solver)"
     achieved = SWEEP_BYTES[workload] * n * n / (ms * 1e-3) / 1e9
     line["roofline"] = roofline(achieved, kernel, (workload, n, n), phase,
                                 bytes_per_cell=SWEEP_BYTES[workload], ms_per_launch=ms, row_step_us=1e3 * ms / n)
@@ -310,7 +304,7 @@ def run_batched(args):
     """512 independent tiles, sides uniform in [64, 2048] (seed 4), tile i's DEM
     from seed 1000 + i; even tiles D8 with uint64 counts, odd tiles MFD with
     float32 water, unit rain.  Times the batched float32 route (one persistent
-    launch, autotuned schedule, replayed from a HIP graph) against per-tile
+    launch after the set-up, autotuned schedule, replayed from a HIP graph) against per-tile
     launches (fr_receivers + fr_accumulate per tile) in float32 and float64."""
     import torch
     import synth
@@ -377,7 +371,7 @@ def run_batched(args):
         "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": f"batched: {ntiles} tiles, sides U[64,2048] (seed 4), even D8 uint64 counts, "
                                f"odd MFD float32, unit rain", "cells": ncell},
-        "roofline": roofline(alg / (gpu_ms * 1e-3) / 1e9, "k_batch", ("batched", ntiles), "batch", bytes=alg,
+        "roofline": roofline(alg / (gpu_ms * 1e-3) / 1e9, "k_peel_batch", ("batched", ntiles), "batch", bytes=alg,
                              ms_per_launch=gpu_ms),
         "detail": {"plan": {"workers": plan.workers, "order": plan.order}, "timing": "HIP graph replay"},
     }

@@ -33,7 +33,7 @@ size_t up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 constexpr size_t kCtlBytes = kAlign;
 
 struct Layout {
-  size_t vlo, ext, done, rs32, iw32, d32, iw64, stamp, list0, list1, ctr, partial, total;
+  size_t vlo, ext, done, stamp, list0, list1, ctr, partial, total;
 };
 
 int64_t tiles_of(int64_t nrows, int64_t ncols) {
@@ -43,7 +43,7 @@ int64_t tiles_of(int64_t nrows, int64_t ncols) {
 // Peeling engine.  The float-float low part comes first, at the same offset
 // as the wavefront sweep's, so that the mass reduction after either path
 // reads it from one place.
-Layout layout(int64_t nrows, int64_t ncols, int rule, int vdtype) {
+Layout layout(int64_t nrows, int64_t ncols, int vdtype) {
   Layout L{};
   const size_t n = (size_t)(nrows * ncols);
   const size_t nt = (size_t)tiles_of(nrows, ncols);
@@ -51,10 +51,6 @@ Layout layout(int64_t nrows, int64_t ncols, int rule, int vdtype) {
   L.vlo = o; if (vdtype == FR_F32) o += up(n * sizeof(float));
   L.ext = o; o += up(n + 4);
   L.done = o; o += up(n + 4);
-  L.rs32 = o; if (rule == FR_MFD && vdtype == FR_F32) o += up(n * sizeof(float));
-  L.iw32 = o; if (rule == FR_MFD && vdtype == FR_F32) o += up(n * sizeof(float));
-  L.d32 = o; if (rule == FR_MFD && vdtype == FR_F32) o += up(n * sizeof(float));
-  L.iw64 = o; if (rule == FR_MFD && vdtype == FR_F64) o += up(n * sizeof(double));
   L.stamp = o; o += up(nt * sizeof(int32_t));
   L.list0 = o; o += up(nt * sizeof(int32_t));
   L.list1 = o; o += up(nt * sizeof(int32_t));
@@ -65,8 +61,7 @@ Layout layout(int64_t nrows, int64_t ncols, int rule, int vdtype) {
 }
 
 // Row-sweep single-receiver path (fr_d8.hip).  The engine's layout overlays
-// it: the engine only runs once this path gave up (exit list overflow), and
-// then nothing reads this path's data any more.
+// it: a call uses one of them.
 struct D8Layout {
   size_t root_of, node_of, ex_cell, cnt[3], fx[3], anc, loc, ctr, mass, total;
   uint32_t cap;
@@ -299,23 +294,17 @@ char* aligned_base(void* ws) {
   return reinterpret_cast<char*>((a + kAlign - 1) / kAlign * kAlign);
 }
 
-EngineParams engine_params(int64_t nrows, int64_t ncols, const uint8_t* code, const float* z, double p,
-                           char* body, const Layout& L, int32_t* status, const int32_t* gate) {
+EngineParams engine_params(int64_t nrows, int64_t ncols, const uint8_t* code, char* body, const Layout& L,
+                           int32_t* status, const int32_t* gate) {
   EngineParams P{};
   P.nrows = nrows;
   P.ncols = ncols;
   P.ntr = (int32_t)((nrows + ENG_TH - 1) / ENG_TH);
   P.ntc = (int32_t)((ncols + ENG_TW - 1) / ENG_TW);
   P.code = code;
-  P.z = z;
-  P.p = p;
   P.ext = reinterpret_cast<uint8_t*>(body + L.ext);
   P.done = reinterpret_cast<uint8_t*>(body + L.done);
   P.vlo = reinterpret_cast<float*>(body + L.vlo);
-  P.rs32 = reinterpret_cast<float*>(body + L.rs32);
-  P.iw32 = reinterpret_cast<float*>(body + L.iw32);
-  P.d32 = reinterpret_cast<float*>(body + L.d32);
-  P.iw64 = reinterpret_cast<double*>(body + L.iw64);
   P.stamp = reinterpret_cast<int32_t*>(body + L.stamp);
   P.list0 = reinterpret_cast<int32_t*>(body + L.list0);
   P.list1 = reinterpret_cast<int32_t*>(body + L.list1);
@@ -338,9 +327,9 @@ int enqueue_peel(RuleKind rk, bool adjoint, ValKind vk, const PeelGrid& P, const
 }
 
 // The peeling engine behind a gate: its kernels run only when *gate != 0.
-int enqueue_engine(const EngineConfig& cfg, const EngineParams& P, hipStream_t s) {
+int enqueue_engine(ValKind vk, bool counts, const EngineParams& P, hipStream_t s) {
   const int ph = phase_begin("engine", s);
-  if (launch_engine_init(cfg, P, s) != hipSuccess || launch_engine_run(cfg, P, s) != hipSuccess) return FR_ERR_HIP;
+  if (launch_engine_init(P, s) != hipSuccess || launch_engine_run(vk, counts, P, s) != hipSuccess) return FR_ERR_HIP;
   phase_end(ph, s);
   return FR_OK;
 }
@@ -598,7 +587,7 @@ size_t fr_workspace_bytes(int fn, int64_t nrows, int64_t ncols, int rule, int dt
   } else {
     return 0;
   }
-  size_t t = layout(nrows, ncols, rule, dtype).total;
+  size_t t = layout(nrows, ncols, dtype).total;
   const size_t tw = ws_layout(nrows, ncols, dtype).total;
   if (tw > t) t = tw;
   if (fn == FR_FN_ADJOINT || rule == FR_MFD) {
@@ -783,8 +772,8 @@ int fr_accumulate(const float* z, const uint8_t* code, int64_t nrows, int64_t nc
   const double* r64 = (rain && rain_dtype == FR_F64) ? static_cast<const double*>(rain) : nullptr;
   float* q32 = q_dtype == FR_F32 ? static_cast<float*>(q_out) : nullptr;
   double* q64 = q_dtype == FR_F64 ? static_cast<double*>(q_out) : nullptr;
-  const Layout L = layout(nrows, ncols, rule, q_dtype);
-  EngineParams P = engine_params(nrows, ncols, code, z, mfd_p, body, L, dev_status, &C->fallback);
+  const Layout L = layout(nrows, ncols, q_dtype);
+  EngineParams P = engine_params(nrows, ncols, code, body, L, dev_status, &C->fallback);
   P.src32 = r32;
   P.src64 = r64;
   P.vhi = q32;
@@ -841,7 +830,7 @@ int fr_accumulate(const float* z, const uint8_t* code, int64_t nrows, int64_t nc
     if (hipGetLastError() != hipSuccess) return FR_ERR_HIP;
   }
   if (!multi) {
-    if ((rc = enqueue_engine(cfg, P, stream)) != FR_OK) return rc;
+    if ((rc = enqueue_engine(cfg.vk, cfg.counts, P, stream)) != FR_OK) return rc;
     if (mass_out) {
       // After the sweep or the engine, whichever finished the solve: both
       // keep the float-float low part at the same place.

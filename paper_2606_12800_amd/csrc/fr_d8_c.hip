@@ -6,7 +6,7 @@ namespace fr {
 namespace {
 // ---------------------------------------------------------------------------
 // Phase C (and the block solve's final sweep).  Returns at once when the
-// exit list overflowed: the engine, or an error, takes over.
+// exit list overflowed: the tile forest, or an error, takes over.
 template <int VK, bool CNT, int RAIN, bool VEC, bool ITER>
 __global__ __launch_bounds__(64) void k_d8_c(D8Params P) {
   __shared__ double s_mass[2][64];

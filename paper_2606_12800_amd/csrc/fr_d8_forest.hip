@@ -8,7 +8,7 @@ namespace {
 // Phase B: exit forest.  The link step turns each exit's local sum into
 // fixed point and points it at the exit its water reaches next (block
 // iterations: only inside its block).  An exit list that overflowed its
-// capacity opens the engine's gate instead (block iterations: an error).
+// capacity opens the tile forest's gate instead (block iterations: an error).
 __device__ __forceinline__ int64_t blk_row(const D8Params& P, int64_t r) { return r / ((int64_t)P.th * P.bt_r); }
 __device__ __forceinline__ int64_t blk_col(const D8Params& P, int64_t c) { return c / ((int64_t)TW * P.bt_c); }
 
@@ -39,11 +39,12 @@ __device__ __forceinline__ uint32_t* kf_leaf_list(const D8Params& P) {
 
 // Link: each exit's local sum into fixed point (sum buffer 0; both
 // pending buffers cleared, which the chain-following forest does not use),
-// and its parent -- the exit its water reaches next (block iterations: only inside its block).  An exit list that
-// overflowed its capacity opens the engine's gate instead (block
-// iterations: an error).  For the chain-following forest (QUEUE) each exit also
-// counts itself among its parent's children (kf_children_of), starting
-// from the zero that the tile pass that listed the exits left there.
+// and its parent -- the exit its water reaches next (block iterations: only
+// inside its block).  An exit list that overflowed its capacity opens the tile
+// forest's gate instead (block iterations: an error).  For the
+// chain-following forest (QUEUE) each exit also counts itself among its
+// parent's children (kf_children_of), starting from the zero that the tile
+// pass that listed the exits left there.
 template <int VK, bool CNT, bool ITER, bool QUEUE = false>
 __global__ __launch_bounds__(256) void k_d8_link(D8Params P) {
   const uint32_t n = *P.n_exits;

@@ -288,7 +288,7 @@ template <bool UP, int VK, bool CNT, int RAIN>
 __global__ __launch_bounds__(HT, UP ? (RAIN == RAIN_F64 ? 5 : 6) : 4) void k_d8t(D8Params P, int ntiles) {
   if (__hip_atomic_load(&P.ctl->d8_tiles, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;  // uniform
   const uint32_t n_ex = *P.n_exits;
-  if (!UP && n_ex > P.cap) return;  // uniform: the engine takes over
+  if (!UP && n_ex > P.cap) return;  // uniform; the list holds every exit of a perimeter
   using V = typename TV<VK>::T;
   using RT = typename RainReg<RAIN>::T;
   constexpr int NCODE = (HR + 2) * HW;
@@ -863,7 +863,7 @@ __global__ __launch_bounds__(HT, UP ? (RAIN == RAIN_F64 ? 5 : 6) : 4) void k_d8t
 // The gate: the tile-forest path serves the call when the row sweeps' exit
 // list overflowed (or the caller chose it: `force`).  It starts from a clean
 // forest state (its own exit count and round flags are separate words; the
-// fixed-point unit is re-derived) and closes the engine's gate again.
+// fixed-point unit is re-derived) and clears the overflow flag.
 __global__ void k_d8t_gate(CallCtl* C, int force) {
   if (threadIdx.x == 0 && (force || C->fallback)) {
     C->d8_tiles = 1;

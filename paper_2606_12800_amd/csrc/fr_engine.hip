@@ -1,15 +1,14 @@
-// Accumulation engine: solves (I - W^T) q = r (forward) or (I - W) rbar =
-// qbar (adjoint) on the grid's routing DAG without sorting.
+// Forward accumulation engine: solves (I - W^T) q = r on a grid's routing
+// forest (one receiver a cell) without sorting.  It serves the paths a caller
+// chooses by name ("engine", and "sweep" where its passes run out).
 //
 // The paper's sequential algorithm processes cells high-to-low so that every
 // cell is visited after all cells that give it water (Section 2.1); its
 // "optimization 2" notes that only this processing order matters, not the
 // numbering (Section 3.2).  Here the order comes from dependency counting,
 // the shared-memory idea the paper cites as prior art (Section 1, Section
-// 2.1): a cell is ready once all of its inputs (donors for the forward
-// solve, receivers for the adjoint) are final, and then its value is
-//   forward:  v_i = r_i + sum_{donors j} f_{j->i} v_j
-//   adjoint:  v_i = qbar_i + sum_{receivers k} f_{i->k} v_k,
+// 2.1): a cell is ready once all of its donors are final, and then its value
+// is v_i = r_i + sum_{donors j} v_j,
 // pulled in fixed neighbour order, so results do not depend on scheduling.
 //
 // GPU layout.  The grid is cut into ENG_TH x ENG_TW tiles.  A workgroup
@@ -62,46 +61,15 @@ __device__ __forceinline__ ff ff_add(ff x, ff y) {
   return ff_fast_two_sum(s.hi, e);
 }
 
-// x * f * (1 + d) for a float32 fraction f and the small correction d of
-// its cell's fractions (the d term goes into the low part).
-__device__ __forceinline__ ff ff_mul_fd(ff x, float f, float d) {
-  const float p = x.hi * f;
-  float e = fmaf(x.hi, f, -p);
-  e = fmaf(x.lo, f, e);
-  e = fmaf(p, d, e);
-  return ff_fast_two_sum(p, e);
-}
-
-// float32 nearest to 1/sqrt(2).
-__device__ constexpr float kInvSqrt2f = 0x1.6a09e6p-1f;
-__device__ constexpr double kSqrt2 = 1.4142135623730950488;
-
 __device__ __forceinline__ void set_status(int32_t* st, int32_t code) {
   if (st) atomicCAS(st, 0, code);
 }
 
-__device__ __forceinline__ bool is_recv(int rk, uint8_t code, int k) {
-  return rk == RK_SINGLE ? (code == (uint8_t)k) : (((code >> k) & 1u) != 0);
-}
-
-// Weight of the edge from a cell at elevation zh down to a neighbour at zl in
-// direction k (MFD), float32 mode: (s / s_ref)^p with s_ref the cell's
-// steepest slope, so the exponent stays small and exp2/log2 keep ~1 ulp.
-__device__ __forceinline__ float mfd_t32(float zh, float zl, int k, float rs, float p) {
-  const float drop = zh - zl;
-  const float s = nb_diag(k) ? drop * kInvSqrt2f : drop;
-  return exp2f(p * log2f(s * rs));
-}
-
-__device__ __forceinline__ double mfd_w64(float zh, float zl, int k, double p) {
-  const double s = ((double)zh - (double)zl) / (nb_diag(k) ? kSqrt2 : 1.0);
-  return pow(s, p);
-}
+__device__ __forceinline__ bool is_recv(uint8_t code, int k) { return code == (uint8_t)k; }
 
 // ---------------------------------------------------------------------------
-// Initialisation: per-cell external pending counts, done flags, MFD split
-// constants, argument checks that need the data.
-template <int RK, int DIR, int VK>
+// Initialisation: per-cell external pending counts, done flags, argument
+// checks that need the data.
 __global__ __launch_bounds__(256) void k_engine_init(EngineParams P) {
   if (P.gate && *P.gate == 0) return;  // another path finished the solve
   const int64_t n = P.nrows * P.ncols;
@@ -117,74 +85,17 @@ __global__ __launch_bounds__(256) void k_engine_init(EngineParams P) {
       const int64_t rr = r + nb_dr(k), cc = c + nb_dc(k);
       const bool in_grid = rr >= 0 && rr < P.nrows && cc >= 0 && cc < P.ncols;
       const int64_t j = rr * P.ncols + cc;
-      const bool recv = is_recv(RK, ci, k);
+      const bool recv = is_recv(ci, k);
       if (recv && !in_grid) badcode = true;
       if (!in_grid) continue;
-      bool input;
-      if (DIR == DIR_FWD)
-        input = is_recv(RK, P.code[j], 7 - k);  // neighbour gives water to i
-      else
-        input = recv;  // i gives water to the neighbour
+      const bool input = is_recv(P.code[j], 7 - k);  // neighbour gives water to i
       if (input && (rr / ENG_TH != tr || cc / ENG_TW != tc)) ++ext;
-      if (RK == RK_MULTI && recv && !(P.z[j] < P.z[i])) badcode = true;
     }
-    if (RK == RK_SINGLE && ci != SINK && ci > 7) badcode = true;
+    if (ci != SINK && ci > 7) badcode = true;
     P.ext[i] = (uint8_t)ext;
     P.done[i] = 0;
     if (P.src32 && !isfinite(P.src32[i])) nonfinite = true;
     if (P.src64 && !isfinite(P.src64[i])) nonfinite = true;
-    if (RK == RK_MULTI) {
-      const float zi = P.z[i];
-      if (!isfinite(zi)) nonfinite = true;
-      if (VK == VK_FF) {
-        float smax = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          if (!is_recv(RK, ci, k)) continue;
-          const int64_t rr = r + nb_dr(k), cc = c + nb_dc(k);
-          if (rr < 0 || rr >= P.nrows || cc < 0 || cc >= P.ncols) continue;
-          const float drop = zi - P.z[rr * P.ncols + cc];
-          const float s = nb_diag(k) ? drop * kInvSqrt2f : drop;
-          smax = s > smax ? s : smax;
-        }
-        const float rs = smax > 0.0f ? 1.0f / smax : 0.0f;
-        float sum = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          if (!is_recv(RK, ci, k)) continue;
-          const int64_t rr = r + nb_dr(k), cc = c + nb_dc(k);
-          if (rr < 0 || rr >= P.nrows || cc < 0 || cc >= P.ncols) continue;
-          sum += mfd_t32(zi, P.z[rr * P.ncols + cc], k, rs, (float)P.p);
-        }
-        const float iw = sum > 0.0f ? 1.0f / sum : 0.0f;
-        // The rounded fractions f_k = t_k * iw do not sum to 1 exactly, and
-        // along a long flow path the excess would compound: with their
-        // exact (float-float) sum s, every contribution is scaled by
-        // 1 + d, d = 1 - s, which restores the sum to first order.  The
-        // f_k here are computed exactly as the edges recompute them.
-        ff es{0.0f, 0.0f};
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          if (!is_recv(RK, ci, k)) continue;
-          const int64_t rr = r + nb_dr(k), cc = c + nb_dc(k);
-          if (rr < 0 || rr >= P.nrows || cc < 0 || cc >= P.ncols) continue;
-          es = ff_add(es, ff{mfd_t32(zi, P.z[rr * P.ncols + cc], k, rs, (float)P.p) * iw, 0.0f});
-        }
-        P.rs32[i] = rs;
-        P.iw32[i] = iw;
-        P.d32[i] = sum > 0.0f ? -((es.hi - 1.0f) + es.lo) : 0.0f;
-      } else if (VK == VK_F64) {
-        double sum = 0.0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          if (!is_recv(RK, ci, k)) continue;
-          const int64_t rr = r + nb_dr(k), cc = c + nb_dc(k);
-          if (rr < 0 || rr >= P.nrows || cc < 0 || cc >= P.ncols) continue;
-          sum += mfd_w64(zi, P.z[rr * P.ncols + cc], k, P.p);
-        }
-        P.iw64[i] = sum > 0.0 ? 1.0 / sum : 0.0;
-      }
-    }
   }
   if (badcode) set_status(P.status, FR_ERR_BADCODE);
   if (nonfinite) set_status(P.status, FR_ERR_NONFINITE);
@@ -205,7 +116,7 @@ __global__ __launch_bounds__(256) void k_engine_init(EngineParams P) {
 
 // ---------------------------------------------------------------------------
 // Per-tile LDS storage.
-template <int RK, int VK, bool CNT>
+template <int VK, bool CNT>
 struct TileLds {
   static constexpr int TH = ENG_TH, TW = ENG_TW, HW = ENG_TW + 2;
   static constexpr int NC = ENG_TH * ENG_TW;
@@ -220,11 +131,6 @@ struct TileLds {
   ff vff[VK == VK_FF ? NC : 1];
   double v64[VK == VK_F64 ? NC : 1];
   uint64_t cnt[CNT ? NC : 1];
-  float z[RK == RK_MULTI ? NH : 1];
-  float rs[(RK == RK_MULTI && VK == VK_FF) ? NH : 1];
-  float iw[(RK == RK_MULTI && VK == VK_FF) ? NH : 1];
-  float dd[(RK == RK_MULTI && VK == VK_FF) ? NH : 1];
-  double iw64[(RK == RK_MULTI && VK == VK_F64) ? NH : 1];
 };
 
 // Device-coherent (agent scope) loads and stores.  The L2 of each XCD is
@@ -299,30 +205,14 @@ __device__ __forceinline__ void signal_external(const EngineParams& P, int it, i
   if (((old >> sh) & 0xFFu) == 1u) activate(P, it, (gr / ENG_TH) * P.ntc + gc / ENG_TW);
 }
 
-// Fraction of the water on the edge between cell h and its neighbour hn in
-// direction k (from h): forward solves pull along donor -> h edges (the
-// donor's split), adjoint solves along h -> receiver edges (h's split).
-// Float32 mode: x times the fraction, with the splitting cell's correction.
-template <int DIR, class L>
-__device__ __forceinline__ ff edge_ff(const L& S, ff x, int h, int hn, int k, float p) {
-  if (DIR == DIR_FWD) return ff_mul_fd(x, mfd_t32(S.z[hn], S.z[h], 7 - k, S.rs[hn], p) * S.iw[hn], S.dd[hn]);
-  return ff_mul_fd(x, mfd_t32(S.z[h], S.z[hn], k, S.rs[h], p) * S.iw[h], S.dd[h]);
-}
-template <int DIR, class L>
-__device__ __forceinline__ double edge_f64(const L& S, int h, int hn, int k, double p) {
-  if (DIR == DIR_FWD) return mfd_w64(S.z[hn], S.z[h], 7 - k, p) * S.iw64[hn];
-  return mfd_w64(S.z[h], S.z[hn], k, p) * S.iw64[h];
-}
-
 // Does cell (lr, lc) have an output outside the tile?
-template <int RK, int DIR, class L>
+template <class L>
 __device__ __forceinline__ bool leaves(const L& S, int h, int lr, int lc, int th, int tw) {
   const uint8_t ci = S.code[h];
   bool any = false;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    const int hn = h + nb_dr(k) * L::HW + nb_dc(k);
-    const bool out = (DIR == DIR_FWD) ? is_recv(RK, ci, k) : is_recv(RK, S.code[hn], 7 - k);
+    const bool out = is_recv(ci, k);
     const int nr = lr + nb_dr(k), nc = lc + nb_dc(k);
     if (out && !(nr >= 0 && nr < th && nc >= 0 && nc < tw)) any = true;
   }
@@ -334,12 +224,11 @@ __device__ __forceinline__ int32_t ld_dev(const int32_t* p) {
 }
 
 // One iteration: every tile of list it % 3 (grid-stride over workgroups).
-template <int RK, int DIR, int VK, bool CNT>
-__device__ __forceinline__ void engine_iter(TileLds<RK, VK, CNT>& S, const EngineParams& P, int it) {
-  using L = TileLds<RK, VK, CNT>;
+template <int VK, bool CNT>
+__device__ __forceinline__ void engine_iter(TileLds<VK, CNT>& S, const EngineParams& P, int it) {
+  using L = TileLds<VK, CNT>;
   constexpr int TH = L::TH, TW = L::TW, HW = L::HW, NC = L::NC, NH = L::NH;
   const int tid = threadIdx.x;
-  const float pf = (float)P.p;
   const int n_active = ld_dev(P.nlist + it % 3);
   const int32_t* list = (it & 1) ? P.list1 : P.list0;
   // List (it + 2) % 3 was read in the previous iteration and is filled in
@@ -354,23 +243,13 @@ __device__ __forceinline__ void engine_iter(TileLds<RK, VK, CNT>& S, const Engin
     const int th = (int)(P.nrows - r0 < TH ? P.nrows - r0 : TH);
     const int tw = (int)(P.ncols - c0 < TW ? P.ncols - c0 : TW);
 
-    // 1. Load codes (and MFD split data) with a one-cell halo.
+    // 1. Load codes with a one-cell halo.
     for (int h = tid; h < NH; h += ENG_THREADS) {
       const int hr = h / HW - 1, hc = h % HW - 1;
       const int64_t gr = r0 + hr, gc = c0 + hc;
       const bool in_grid = gr >= 0 && gr < P.nrows && gc >= 0 && gc < P.ncols;
       const int64_t g = gr * P.ncols + gc;
-      S.code[h] = in_grid ? P.code[g] : (RK == RK_SINGLE ? SINK : (uint8_t)0);
-      if (RK == RK_MULTI) {
-        S.z[h] = in_grid ? P.z[g] : INFINITY;
-        if (VK == VK_FF) {
-          S.rs[h] = in_grid ? P.rs32[g] : 0.0f;
-          S.iw[h] = in_grid ? P.iw32[g] : 0.0f;
-          S.dd[h] = in_grid ? P.d32[g] : 0.0f;
-        } else if (VK == VK_F64) {
-          S.iw64[h] = in_grid ? P.iw64[g] : 0.0;
-        }
-      }
+      S.code[h] = in_grid ? P.code[g] : SINK;
     }
     // 2. Cell state.
     for (int l = tid; l < NC; l += ENG_THREADS) {
@@ -403,7 +282,6 @@ __device__ __forceinline__ void engine_iter(TileLds<RK, VK, CNT>& S, const Engin
       const int h = (lr + 1) * HW + (lc + 1);
       const int64_t gr = r0 + lr, gc = c0 + lc;
       const int64_t g = gr * P.ncols + gc;
-      const uint8_t ci = S.code[h];
       uint32_t pend = 0;
       ff vf = {0.0f, 0.0f};
       double vd = 0.0;
@@ -423,7 +301,7 @@ __device__ __forceinline__ void engine_iter(TileLds<RK, VK, CNT>& S, const Engin
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
         const int hn = h + nb_dr(k) * HW + nb_dc(k);
-        const bool input = (DIR == DIR_FWD) ? is_recv(RK, S.code[hn], 7 - k) : is_recv(RK, ci, k);
+        const bool input = is_recv(S.code[hn], 7 - k);
         if (!input) continue;
         const int nr = lr + nb_dr(k), nc = lc + nb_dc(k);
         if (gr + nb_dr(k) < 0 || gr + nb_dr(k) >= P.nrows || gc + nb_dc(k) < 0 || gc + nb_dc(k) >= P.ncols)
@@ -439,12 +317,10 @@ __device__ __forceinline__ void engine_iter(TileLds<RK, VK, CNT>& S, const Engin
         const int64_t gn = g + nb_dr(k) * P.ncols + nb_dc(k);
         if (VK == VK_FF) {
           ff vj = same ? ff{P.vhi[gn], P.vlo[gn]} : ff{ld_dev(P.vhi + gn), ld_dev(P.vlo + gn)};
-          if (RK == RK_MULTI) vj = edge_ff<DIR>(S, vj, h, hn, k, pf);
           vf = ff_add(vf, vj);
         }
         if (VK == VK_F64) {
           double vj = same ? P.v64[gn] : ld_dev(P.v64 + gn);
-          if (RK == RK_MULTI) vj *= edge_f64<DIR>(S, h, hn, k, P.p);
           vd += vj;
         }
         if (CNT) cn += same ? P.cnt[gn] : ld_dev(P.cnt + gn);
@@ -491,7 +367,7 @@ __device__ __forceinline__ void engine_iter(TileLds<RK, VK, CNT>& S, const Engin
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
             const int hn = h + nb_dr(k) * HW + nb_dc(k);
-            const bool input = (DIR == DIR_FWD) ? is_recv(RK, S.code[hn], 7 - k) : is_recv(RK, ci, k);
+            const bool input = is_recv(S.code[hn], 7 - k);
             if (!input) continue;
             const int nr = lr + nb_dr(k), nc = lc + nb_dc(k);
             if (!(nr >= 0 && nr < th && nc >= 0 && nc < tw)) continue;
@@ -499,12 +375,10 @@ __device__ __forceinline__ void engine_iter(TileLds<RK, VK, CNT>& S, const Engin
             if (S.st[ln] & ST_PREV) continue;  // already in the known part
             if (VK == VK_FF) {
               ff vj = S.vff[ln];
-              if (RK == RK_MULTI) vj = edge_ff<DIR>(S, vj, h, hn, k, pf);
               vf = ff_add(vf, vj);
             }
             if (VK == VK_F64) {
               double vj = S.v64[ln];
-              if (RK == RK_MULTI) vj *= edge_f64<DIR>(S, h, hn, k, P.p);
               vd += vj;
             }
             if (CNT) cn += S.cnt[ln];
@@ -519,8 +393,7 @@ __device__ __forceinline__ void engine_iter(TileLds<RK, VK, CNT>& S, const Engin
           bool ready = false;
           int ln = 0;
           if (act) {
-            const int hn = h + nb_dr(k) * HW + nb_dc(k);
-            const bool out = (DIR == DIR_FWD) ? is_recv(RK, ci, k) : is_recv(RK, S.code[hn], 7 - k);
+            const bool out = is_recv(ci, k);
             const int nr = lr + nb_dr(k), nc = lc + nb_dc(k);
             if (out && nr >= 0 && nr < th && nc >= 0 && nc < tw) {
               ln = nr * TW + nc;
@@ -545,7 +418,7 @@ __device__ __forceinline__ void engine_iter(TileLds<RK, VK, CNT>& S, const Engin
       const int lr = l / TW, lc = l % TW;
       const int h = (lr + 1) * HW + (lc + 1);
       const int64_t g = (r0 + lr) * P.ncols + (c0 + lc);
-      const bool lv = leaves<RK, DIR>(S, h, lr, lc, th, tw);
+      const bool lv = leaves(S, h, lr, lc, th, tw);
       if (VK == VK_FF) {
         if (lv) {
           st_dev(P.vhi + g, S.vff[l].hi);
@@ -576,8 +449,7 @@ __device__ __forceinline__ void engine_iter(TileLds<RK, VK, CNT>& S, const Engin
       const uint8_t ci = S.code[h];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        const int hn = h + nb_dr(k) * HW + nb_dc(k);
-        const bool out = (DIR == DIR_FWD) ? is_recv(RK, ci, k) : is_recv(RK, S.code[hn], 7 - k);
+        const bool out = is_recv(ci, k);
         const int nr = lr + nb_dr(k), nc = lc + nb_dc(k);
         if (!out || (nr >= 0 && nr < th && nc >= 0 && nc < tw)) continue;
         const int64_t ngr = gr + nb_dr(k), ngc = gc + nb_dc(k);
@@ -622,12 +494,12 @@ __device__ bool grid_sync(unsigned long long* bar, int epoch) {
 // cell is final, or (cells left over) the routing has a cycle.  Every
 // workgroup reads the same list length after the same barrier, so all of
 // them leave together.
-template <int RK, int DIR, int VK, bool CNT>
+template <int VK, bool CNT>
 __global__ __launch_bounds__(ENG_THREADS) void k_engine_run(EngineParams P) {
-  __shared__ TileLds<RK, VK, CNT> S;
+  __shared__ TileLds<VK, CNT> S;
   if (P.gate && *P.gate == 0) return;  // uniform: another path finished the solve
   for (int it = 0;; ++it) {
-    engine_iter<RK, DIR, VK, CNT>(S, P, it);
+    engine_iter<VK, CNT>(S, P, it);
     if (!grid_sync(P.bar, it)) {
       if (threadIdx.x == 0) set_status(P.status, FR_ERR_STALL);
       return;
@@ -717,68 +589,42 @@ int init_grid(const EngineParams& P) {
   return (int)(b < 1 ? 1 : b);
 }
 
-template <int RK, int DIR>
-hipError_t init_dispatch_vk(ValKind vk, const EngineParams& P, hipStream_t s) {
-  const int g = init_grid(P);
-  switch (vk) {
-    case VK_FF: hipLaunchKernelGGL((k_engine_init<RK, DIR, VK_FF>), dim3(g), dim3(256), 0, s, P); break;
-    case VK_F64: hipLaunchKernelGGL((k_engine_init<RK, DIR, VK_F64>), dim3(g), dim3(256), 0, s, P); break;
-    default: hipLaunchKernelGGL((k_engine_init<RK, DIR, VK_NONE>), dim3(g), dim3(256), 0, s, P); break;
-  }
-  return hipGetLastError();
-}
-
 }  // namespace
 
-hipError_t launch_engine_init(const EngineConfig& cfg, const EngineParams& P, hipStream_t s) {
-  if (cfg.rk == RK_SINGLE)
-    return cfg.dir == DIR_FWD ? init_dispatch_vk<RK_SINGLE, DIR_FWD>(cfg.vk, P, s)
-                              : init_dispatch_vk<RK_SINGLE, DIR_ADJ>(cfg.vk, P, s);
-  return cfg.dir == DIR_FWD ? init_dispatch_vk<RK_MULTI, DIR_FWD>(cfg.vk, P, s)
-                            : init_dispatch_vk<RK_MULTI, DIR_ADJ>(cfg.vk, P, s);
+hipError_t launch_engine_init(const EngineParams& P, hipStream_t s) {
+  hipLaunchKernelGGL(k_engine_init, dim3(init_grid(P)), dim3(256), 0, s, P);
+  return hipGetLastError();
 }
 
 // Workgroups of the persistent engine: as many as can be resident at once
 // (at most two per compute unit), so that its grid barriers always complete.
-template <int RK, int DIR, int VK, bool CNT>
+template <int VK, bool CNT>
 hipError_t run_t(const EngineParams& P, hipStream_t s) {
   int dev = 0, cus = 0, per = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_engine_run<RK, DIR, VK, CNT>, ENG_THREADS, 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_engine_run<VK, CNT>, ENG_THREADS, 0);
   if (e != hipSuccess) return e;
   if (per < 1 || cus < 1) return hipErrorLaunchFailure;
   int64_t grid = (int64_t)cus * (per > 2 ? 2 : per);
   const int64_t ntiles = (int64_t)P.ntr * P.ntc;
   if (grid > ntiles) grid = ntiles;
-  hipLaunchKernelGGL((k_engine_run<RK, DIR, VK, CNT>), dim3((unsigned)(grid < 1 ? 1 : grid)), dim3(ENG_THREADS), 0, s,
+  hipLaunchKernelGGL((k_engine_run<VK, CNT>), dim3((unsigned)(grid < 1 ? 1 : grid)), dim3(ENG_THREADS), 0, s,
                      P);
   return hipGetLastError();
 }
 
-hipError_t launch_engine_run(const EngineConfig& cfg, const EngineParams& P, hipStream_t s) {
-  if (cfg.rk == RK_SINGLE) {
-    if (cfg.dir == DIR_FWD) {
-      if (cfg.counts) {
-        switch (cfg.vk) {
-          case VK_FF: return run_t<RK_SINGLE, DIR_FWD, VK_FF, true>(P, s);
-          case VK_F64: return run_t<RK_SINGLE, DIR_FWD, VK_F64, true>(P, s);
-          default: return run_t<RK_SINGLE, DIR_FWD, VK_NONE, true>(P, s);
-        }
-      }
-      if (cfg.vk == VK_FF) return run_t<RK_SINGLE, DIR_FWD, VK_FF, false>(P, s);
-      return run_t<RK_SINGLE, DIR_FWD, VK_F64, false>(P, s);
+hipError_t launch_engine_run(ValKind vk, bool counts, const EngineParams& P, hipStream_t s) {
+  if (counts) {
+    switch (vk) {
+      case VK_FF: return run_t<VK_FF, true>(P, s);
+      case VK_F64: return run_t<VK_F64, true>(P, s);
+      default: return run_t<VK_NONE, true>(P, s);
     }
-    if (cfg.vk == VK_FF) return run_t<RK_SINGLE, DIR_ADJ, VK_FF, false>(P, s);
-    return run_t<RK_SINGLE, DIR_ADJ, VK_F64, false>(P, s);
   }
-  if (cfg.dir == DIR_FWD) {
-    if (cfg.vk == VK_FF) return run_t<RK_MULTI, DIR_FWD, VK_FF, false>(P, s);
-    return run_t<RK_MULTI, DIR_FWD, VK_F64, false>(P, s);
-  }
-  if (cfg.vk == VK_FF) return run_t<RK_MULTI, DIR_ADJ, VK_FF, false>(P, s);
-  return run_t<RK_MULTI, DIR_ADJ, VK_F64, false>(P, s);
+  if (vk == VK_FF) return run_t<VK_FF, false>(P, s);
+  return run_t<VK_F64, false>(P, s);
 }
 
 hipError_t launch_mass(RuleKind rk, ValKind vk, const EngineParams& P, double* partial, int nblocks,

@@ -37,19 +37,13 @@ constexpr int ENG_THREADS = 256;
 struct EngineParams {
   int64_t nrows, ncols;
   int32_t ntr, ntc;            // tile grid
-  const uint8_t* code;         // D8/D4 direction codes or MFD masks
-  const float* z;              // elevations (MFD)
-  double p;                    // MFD slope exponent
-  const float* src32;          // source term (rain or qbar), float32, or NULL
+  const uint8_t* code;         // D8/D4 direction codes (the mass reduction: or MFD masks)
+  const float* src32;          // source term (rain), float32, or NULL
   const double* src64;         // source term float64, or NULL (both NULL: unit)
   float* vhi;                  // float-float value, high part (= float32 output)
   float* vlo;                  // float-float value, low part (workspace)
   double* v64;                 // float64 value (output)
   uint64_t* cnt;               // exact counts (D8 forward), or NULL
-  float* rs32;                 // MFD: 1 / steepest slope of the cell (float32 mode)
-  float* iw32;                 // MFD: 1 / sum of normalised weights (float32 mode)
-  float* d32;                  // MFD: 1 - sum of the cell's float32 fractions (float32 mode)
-  double* iw64;                // MFD: 1 / sum of weights (float64 mode)
   uint8_t* ext;                // per cell: inputs in other tiles not yet finished
   uint8_t* done;               // per cell: 1 once its value is final
   int32_t* stamp;              // per tile: last iteration it was queued for
@@ -97,7 +91,7 @@ inline int block_iter_height(int64_t nrows, int64_t ncols) {
 // alone and can be captured in a HIP graph.  Zeroed by the call's first
 // kernel.
 struct CallCtl {
-  int32_t fallback;          // 1: the peeling engine runs (exit list overflow, sweep budget spent)
+  int32_t fallback;          // 1: the path behind runs (exit list overflow, sweep budget spent)
   int32_t sweep_stop;        // 1: no further sweep pass runs
   int32_t sweep_dir;         // row direction of the next sweep pass (-1 or +1)
   uint32_t sweep_fin[2];     // cells the last pass going up / down finished
@@ -173,7 +167,7 @@ int64_t d8t_tiles(int64_t nrows, int64_t ncols);
 uint64_t d8t_exit_bound(int64_t nrows, int64_t ncols);
 size_t d8t_mass_words(int64_t nrows, int64_t ncols);
 // Opens the path's gate (C->d8_tiles) when the row sweeps' exit list
-// overflowed (C->fallback) or `force`, closing the engine's gate again.
+// overflowed (C->fallback) or `force`, and clears that flag.
 hipError_t launch_d8t_gate(CallCtl* C, bool force, hipStream_t s);
 // Phase A (up) or C (down) of every tile; both return at once while the
 // gate is closed.
@@ -274,11 +268,6 @@ struct WsParams {
   uint32_t* ctr;           // [0] cells finished by the last pass, [1]/[2] probe counts
   int32_t* status;
   int debug;               // float64 value: unfinished cells carry their state in the NaN payload
-  // MFD float-float variant only: codes are D8/D4 directions (turned into
-  // one-bit masks, fraction 1), and counts written from the (integer)
-  // float-float values, exact below 2^31.
-  int codes_single;
-  uint64_t* cnt_ff;
 };
 
 size_t ws_edge_words(int64_t nrows, int64_t ncols);
@@ -330,8 +319,8 @@ hipError_t launch_ws_ctl(const WsParams& P, CallCtl* C, int pass, bool last, hip
 // The peeling engine: set-up, then one persistent launch that runs its
 // iterations with grid barriers until every cell is final (or a cycle
 // leaves the queue empty).  Both return at once when P.gate is closed.
-hipError_t launch_engine_init(const EngineConfig& cfg, const EngineParams& P, hipStream_t s);
-hipError_t launch_engine_run(const EngineConfig& cfg, const EngineParams& P, hipStream_t s);
+hipError_t launch_engine_init(const EngineParams& P, hipStream_t s);
+hipError_t launch_engine_run(ValKind vk, bool counts, const EngineParams& P, hipStream_t s);
 // Device queue of tiles (fr_queue.hpp): its words, a cache line each, and its
 // arrays.
 struct TileCtl {

@@ -335,21 +335,16 @@ __device__ void ws_strip(WsShared<RK, VK, CNT>& S, const WsParams& P, const int6
 
   if (wave == 1) {
     // ======================= I/O wavefront ===============================
-    // Direction codes run as one-bit masks (fraction 1) in the MFD variant.
-    auto as_mask = [&](uint32_t code) -> uint32_t {
-      if (RK == RK_MULTI && P.codes_single) return code <= 7u ? (1u << code) : 0u;
-      return code;
-    };
     auto load_geo = [&](int t) -> Geo {
       Geo g{NOC, NOC, INFINITY, INFINITY};
       if (t < 0 || t >= nr) return g;
       const int64_t rb = row_of(t) * nc;
       if (live) {
-        g.code = as_mask(P.code[rb + c]);
+        g.code = P.code[rb + c];
         if (RK == RK_MULTI) g.z = P.z[rb + c];
       }
       if (has_side) {
-        g.scode = as_mask(P.code[rb + cs]);
+        g.scode = P.code[rb + cs];
         if (RK == RK_MULTI) g.sz = P.z[rb + cs];
       }
       return g;
@@ -1015,7 +1010,6 @@ __device__ void ws_strip(WsShared<RK, VK, CNT>& S, const WsParams& P, const int6
         const ff v = S.val[sf][li];
         P.vhi[i] = v.hi;
         P.vlo[i] = v.lo;
-        if (RK == RK_MULTI && P.cnt_ff) P.cnt_ff[i] = (uint64_t)((int64_t)v.hi + (int64_t)v.lo);
       } else if constexpr (VK == VK_F64) {
         P.v64[i] = S.val[sf][li];
       }
