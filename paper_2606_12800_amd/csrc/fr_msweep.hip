@@ -51,10 +51,14 @@
 // which ghost columns are refreshed, and with what, depends only on the
 // data.
 //
-// Precision: float-float accumulation for float32 output (hi written; the
-// low part stays in registers), float64 otherwise; fractions as in the
-// general sweep (float32 (s / s_max)^p with a conservation correction, or
-// float64 pow).
+// Precision: float64 values for both outputs (a float32 output is rounded
+// once); fractions float32 (s / s_max)^p with a conservation correction, or
+// float64.  The row step is a serial chain of a few hundred instructions in
+// one wavefront, so its length is what counts: a float64 fused multiply-add
+// issues like a float32 one and takes the place of the five to eight of a
+// float-float step (float32 output, ms, float-float against float64: 8192^2
+// 18.9 -> 13.7, 16384^2 42.3 -> 32.0; float64 output 13.6 and 36.2 before
+// and after).
 #include <math.h>
 
 #include "fr_ff.hpp"
@@ -95,84 +99,33 @@ __device__ __forceinline__ double sh_r(double x) {
   const uint64_t u = (uint64_t)__double_as_longlong(x);
   return __longlong_as_double((long long)(((uint64_t)sh_r((uint32_t)(u >> 32)) << 32) | sh_r((uint32_t)u)));
 }
-__device__ __forceinline__ ff sh_l(ff x) { return {sh_l(x.hi), sh_l(x.lo)}; }
-__device__ __forceinline__ ff sh_r(ff x) { return {sh_r(x.hi), sh_r(x.lo)}; }
 
 __device__ __forceinline__ uint64_t ballot(bool p) { return (uint64_t)__builtin_amdgcn_ballot_w64(p); }
 
-// Value arithmetic of the two precisions.
+// Values are float64 in both precisions; the fractions (F) are float32 for
+// float32 output, with the sending cell's correction d, and float64
+// otherwise.  weight: the share of the sender's value that an edge carries.
 template <int VK>
-struct Arith;
-
-template <>
-struct Arith<VK_FF> {
-  using V = ff;
+struct Arith {
   using F = float;
-  static __device__ __forceinline__ V zero() { return {0.0f, 0.0f}; }
-  static __device__ __forceinline__ V one() { return {1.0f, 0.0f}; }
-  static __device__ __forceinline__ V from_src(float r) { return {r, 0.0f}; }
-  static __device__ __forceinline__ V from_src(double r) {
-    const float h = (float)r;
-    return {h, (float)(r - (double)h)};
-  }
-  static __device__ __forceinline__ V add(V a, V b) { return ffa::add(a, b); }
-  static __device__ __forceinline__ V contrib(V v, F f, float d) { return ffa::mul_fd(v, f, d); }
-  static __device__ __forceinline__ bool nz(V v) { return v.hi != 0.0f; }
-  // Unnormalised variants for inner loops (|lo| may exceed ulp(hi)/2 by a
-  // few units; the sum is renormalised once at the end): x * f * (1 + d),
-  // and a + b.
-  static __device__ __forceinline__ V contrib_lean(V x, F f, float d) {
-    const float p = x.hi * f;
-    float e = fmaf(x.hi, f, -p);
-    e = fmaf(x.lo, f, e);
-    return {p, fmaf(p, d, e)};
-  }
-  static __device__ __forceinline__ V add_lean(V a, V b) {
-    const ff s = ffa::two_sum(a.hi, b.hi);
-    return {s.hi, s.lo + (a.lo + b.lo)};
-  }
-  static __device__ __forceinline__ V norm(V v) { return ffa::fast_two_sum(v.hi, v.lo); }
-  // Either part nonzero (signs ignored).
-  static __device__ __forceinline__ bool nz_any(V v) {
-    return ((__float_as_uint(v.hi) | __float_as_uint(v.lo)) << 1) != 0u;
-  }
-  static __device__ __forceinline__ bool finite(V v) { return isfinite(v.hi) && isfinite(v.lo); }
-  static __device__ __forceinline__ double wide(V v) { return (double)v.hi + (double)v.lo; }
-  // The low part's last 8 bits carry the tag (a change of at most 2^-40 of
-  // the value).
-  static __device__ __forceinline__ uint64_t pack(V v, uint32_t tag) {
-    return ((uint64_t)__float_as_uint(v.hi) << 32) | ((__float_as_uint(v.lo) & ~0xFFu) | tag);
-  }
-  static __device__ __forceinline__ V unpack(uint64_t w) {
-    return {__uint_as_float((uint32_t)(w >> 32)), __uint_as_float((uint32_t)w & ~0xFFu)};
-  }
+  static __device__ __forceinline__ double weight(float f, float d) { return fma((double)f, (double)d, (double)f); }
+  // A source the output's type cannot hold counts as non-finite.
+  static __device__ __forceinline__ bool finite(double v) { return isfinite((float)v); }
 };
 
 template <>
 struct Arith<VK_F64> {
-  using V = double;
   using F = double;
-  static __device__ __forceinline__ V zero() { return 0.0; }
-  static __device__ __forceinline__ V one() { return 1.0; }
-  static __device__ __forceinline__ V from_src(float r) { return (double)r; }
-  static __device__ __forceinline__ V from_src(double r) { return r; }
-  static __device__ __forceinline__ V add(V a, V b) { return a + b; }
-  static __device__ __forceinline__ V contrib(V v, F f, float) { return v * f; }
-  static __device__ __forceinline__ bool nz(V v) { return v != 0.0; }
-  static __device__ __forceinline__ V contrib_lean(V x, F f, float) { return x * f; }
-  static __device__ __forceinline__ V add_lean(V a, V b) { return a + b; }
-  static __device__ __forceinline__ V norm(V v) { return v; }
-  static __device__ __forceinline__ bool nz_any(V v) { return v != 0.0; }
-  static __device__ __forceinline__ bool finite(V v) { return isfinite(v); }
-  static __device__ __forceinline__ double wide(V v) { return v; }
-  // The last 8 bits of the significand carry the tag (2^-45 relative).
-  static __device__ __forceinline__ uint64_t pack(V v, uint32_t tag) {
-    return ((uint64_t)__double_as_longlong(v) & ~0xFFull) | tag;
-  }
-  static __device__ __forceinline__ V unpack(uint64_t w) {
-    return __longlong_as_double((long long)(w & ~0xFFull));
-  }
+  static __device__ __forceinline__ double weight(double f, float) { return f; }
+  static __device__ __forceinline__ bool finite(double v) { return isfinite(v); }
 };
+
+// A published value: the last 8 bits of the significand carry the tag
+// (2^-45 relative).
+__device__ __forceinline__ uint64_t pack(double v, uint32_t tag) {
+  return ((uint64_t)__double_as_longlong(v) & ~0xFFull) | tag;
+}
+__device__ __forceinline__ double unpack(uint64_t w) { return __longlong_as_double((long long)(w & ~0xFFull)); }
 
 __device__ __forceinline__ void st_word(uint64_t* p, uint64_t v) {
   __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)v, __ATOMIC_RELAXED,
@@ -280,26 +233,21 @@ __device__ __forceinline__ Frac<VK, FLOW_UP> fractions(float zc, float znm, floa
 
 // Resolves same-row chains: q = a + sum over same-row inputs of their
 // contributions, by pulls repeated until no increment is left (exact: an
-// increment travels one cell per pull and chains end).  fin_l / fin_r:
-// fraction of the left / right neighbour's value this cell takes (0: no
-// such input), with the sender's correction din_l / din_r.
-template <int VK>
-__device__ __forceinline__ typename Arith<VK>::V lateral(typename Arith<VK>::V a, typename Arith<VK>::F fin_l,
-                                                        float din_l, typename Arith<VK>::F fin_r, float din_r) {
-  using A = Arith<VK>;
-  using V = typename A::V;
-  V q = a, d0 = a, d1;
+// increment travels one cell per pull and chains end).  wl / wr: share of
+// the left / right neighbour's value this cell takes (0: no such input).
+__device__ __forceinline__ double lateral(double a, double wl, double wr) {
+  double q = a, d0 = a, d1;
   // Two pulls per trip (ping-pong increments, no register copies); an
   // increment moves one cell per pull, so 64 pulls cross any window.
   for (int it = 0; it < MS_LANES / 2; ++it) {
-    d1 = A::add_lean(A::contrib_lean(sh_l(d0), fin_l, din_l), A::contrib_lean(sh_r(d0), fin_r, din_r));
-    if (ballot(A::nz_any(d1)) == 0ull) break;
-    q = A::add_lean(q, d1);
-    d0 = A::add_lean(A::contrib_lean(sh_l(d1), fin_l, din_l), A::contrib_lean(sh_r(d1), fin_r, din_r));
-    if (ballot(A::nz_any(d0)) == 0ull) break;
-    q = A::add_lean(q, d0);
+    d1 = fma(sh_l(d0), wl, sh_r(d0) * wr);
+    if (ballot(d1 != 0.0) == 0ull) break;
+    q += d1;
+    d0 = fma(sh_l(d1), wl, sh_r(d1) * wr);
+    if (ballot(d0 != 0.0) == 0ull) break;
+    q += d0;
   }
-  return A::norm(q);
+  return q;
 }
 
 // Dirt carried along same-row chains (hl / hr: lanes taking input from the
@@ -315,14 +263,12 @@ __device__ __forceinline__ uint64_t spread(uint64_t d, uint64_t hl, uint64_t hr)
 
 // Polls until every lane in `need` reads a word tagged `tag` at its address;
 // returns false after the spin limit (the status word then says so).
-template <int VK>
-__device__ __forceinline__ bool wait_words(const uint64_t* addr, bool need, uint32_t tag,
-                                           typename Arith<VK>::V& out) {
+__device__ __forceinline__ bool wait_words(const uint64_t* addr, bool need, uint32_t tag, double& out) {
   for (uint32_t it = 0;; ++it) {
     uint64_t w = 0;
     if (need) w = ld_word(addr);
     const bool ok = !need || (uint32_t)(w & 0xFFu) == tag;
-    if (need && ok) out = Arith<VK>::unpack(w);
+    if (need && ok) out = unpack(w);
     if (ballot(!ok) == 0ull) return true;
     if (it >= MS_SPIN_LIMIT) return false;
     __builtin_amdgcn_s_sleep(1);
@@ -373,7 +319,7 @@ template <int VK>
 struct Stage {
   typename Arith<VK>::F nm[MS_LANES], n0[MS_LANES], np[MS_LANES], l[MS_LANES], r[MS_LANES];
   float d[MS_LANES];
-  typename Arith<VK>::V src[MS_LANES];
+  double src[MS_LANES];
   uint32_t code[MS_LANES];
 };
 
@@ -411,7 +357,6 @@ __device__ __forceinline__ int ms_strip_of_block(int b, int n) {
 template <int VK, bool ADJ, bool FLOW_UP, int SRC>
 __global__ __launch_bounds__(64 * (1 + ms_producers<VK>())) void k_ms(MsParams P, const CallCtl* C) {
   using A = Arith<VK>;
-  using V = typename A::V;
   using F = typename A::F;
   constexpr int NP = ms_producers<VK>();
   const int32_t gate = C->ms_flags;
@@ -521,9 +466,7 @@ __global__ __launch_bounds__(64 * (1 + ms_producers<VK>())) void k_ms(MsParams P
       }
       const Frac<VK, FLOW_UP> fr =
           fractions<VK, FLOW_UP>(cur.zc, sh_l(zo), zo, sh_r(zo), sh_l(cur.zc), sh_r(cur.zc), m, pf, P.p);
-      V sv;
-      if constexpr (SRC == SRC_UNIT) sv = A::one();
-      else sv = A::from_src(cur.src);
+      const double sv = SRC == SRC_UNIT ? 1.0 : (double)cur.src;
       Stage<VK>& S = stage[slot];
       S.nm[lane] = fr.nm;
       S.n0[lane] = fr.n0;
@@ -564,14 +507,11 @@ __global__ __launch_bounds__(64 * (1 + ms_producers<VK>())) void k_ms(MsParams P
   int32_t nb_prog = 0;  // smallest neighbour progress seen (rows finished)
   uint64_t* pub = ring_mine + (owned ? lane - MS_G : 0);
 
-  // A row's inputs in the form the recurrence takes them: pull weights
-  // toward the previous row's three cells (lane shifts -1, 0, +1), same-row
-  // input fractions from the left / right, with the senders' corrections,
-  // the source term and the masks of lanes taking each input.
+  // A row's inputs in the form the recurrence takes them: shares of the
+  // previous row's three cells (lane shifts -1, 0, +1) and of the same-row
+  // neighbours, the source term and the masks of lanes taking each input.
   struct Ctx {
-    F wl, w0, wr, fl, fr;
-    float dwl, dw0, dwr, dfl, dfr;
-    V src;
+    double wl, w0, wr, fl, fr, src;
     uint32_t code;
     uint64_t tm, t0, tp, hl, hr;
   };
@@ -584,7 +524,7 @@ __global__ __launch_bounds__(64 * (1 + ms_producers<VK>())) void k_ms(MsParams P
     c.src = S.src[lane];
     c.code = S.code[lane];
     if (!ADJ) {
-      // Forward: a cell takes a fraction of each upslope neighbour in the
+      // Forward: a cell takes a share of each upslope neighbour in the
       // previous row (that cell's own fractions) and of its same-row donors.
       F pnm = 0, pn0 = 0, pnp = 0;
       float pd = 0.0f;
@@ -595,51 +535,42 @@ __global__ __launch_bounds__(64 * (1 + ms_producers<VK>())) void k_ms(MsParams P
         pnp = Q.np[lane];
         pd = Q.d[lane];
       }
-      c.wl = sh_l(pnp);
-      c.dwl = sh_l(pd);
-      c.w0 = pn0;
-      c.dw0 = pd;
-      c.wr = sh_r(pnm);
-      c.dwr = sh_r(pd);
-      c.fl = sh_l(r);
-      c.dfl = sh_l(d);
-      c.fr = sh_r(l);
-      c.dfr = sh_r(d);
+      c.wl = sh_l(A::weight(pnp, pd));
+      c.w0 = A::weight(pn0, pd);
+      c.wr = sh_r(A::weight(pnm, pd));
+      c.fl = sh_l(A::weight(r, d));
+      c.fr = sh_r(A::weight(l, d));
     } else {
       // Adjoint: a cell takes its own fractions of its receivers' values.
-      c.wl = nm;
-      c.w0 = n0;
-      c.wr = np;
-      c.fl = l;
-      c.fr = r;
-      c.dwl = c.dw0 = c.dwr = c.dfl = c.dfr = d;
+      c.wl = A::weight(nm, d);
+      c.w0 = A::weight(n0, d);
+      c.wr = A::weight(np, d);
+      c.fl = A::weight(l, d);
+      c.fr = A::weight(r, d);
     }
-    c.tm = ballot(c.wl != (F)0);
-    c.t0 = ballot(c.w0 != (F)0);
-    c.tp = ballot(c.wr != (F)0);
-    c.hl = ballot(c.fl != (F)0);
-    c.hr = ballot(c.fr != (F)0);
+    c.tm = ballot(c.wl != 0.0);
+    c.t0 = ballot(c.w0 != 0.0);
+    c.tp = ballot(c.wr != 0.0);
+    c.hl = ballot(c.fl != 0.0);
+    c.hr = ballot(c.fr != 0.0);
     return c;
   };
-  auto pull_prev = [&](const Ctx& c, V vprev) -> V {
-    const V cl = A::contrib_lean(sh_l(vprev), c.wl, c.dwl);
-    const V cm = A::contrib_lean(vprev, c.w0, c.dw0);
-    const V cr = A::contrib_lean(sh_r(vprev), c.wr, c.dwr);
-    return A::norm(A::add_lean(c.src, A::add_lean(A::add_lean(cl, cm), cr)));
+  auto pull_prev = [&](const Ctx& c, double vprev) -> double {
+    return c.src + fma(sh_r(vprev), c.wr, fma(vprev, c.w0, sh_l(vprev) * c.wl));
   };
   auto dirt_prev = [&](const Ctx& c, uint64_t d) -> uint64_t {
     return ((d << 1) & c.tm) | (d & c.t0) | ((d >> 1) & c.tp);
   };
   // One row from the previous row's values and dirt: q and its dirt.
-  auto solve_row = [&](const Ctx& c, V vprev, uint64_t pl, uint64_t pr, V& a, V& q, uint64_t& dl, uint64_t& dr) {
+  auto solve_row = [&](const Ctx& c, double vprev, uint64_t pl, uint64_t pr, double& a, double& q, uint64_t& dl, uint64_t& dr) {
     a = pull_prev(c, vprev);
     dl = spread(dirt_prev(c, pl) | edge_l, c.hl, c.hr);
     dr = spread(dirt_prev(c, pr) | edge_r, c.hl, c.hr);
-    q = lateral<VK>(a, c.fl, c.dfl, c.fr, c.dfr);
+    q = lateral(a, c.fl, c.fr);
   };
 
   // Previous row: values and dirt by side of origin.
-  V vp = A::zero();
+  double vp = 0.0;
   uint64_t dpl = 0, dpr = 0;
 
   double msum = 0.0, rsum = 0.0;
@@ -667,13 +598,13 @@ __global__ __launch_bounds__(64 * (1 + ms_producers<VK>())) void k_ms(MsParams P
     Ctx cx = load_ctx(t);
     compiler_fence();
     if (lane == 0) lds_st(&cons_row, (int32_t)(t - 1));
-    if (!valid) cx.src = A::zero();
+    if (!valid) cx.src = 0.0;
     if (!A::finite(cx.src)) {
       nonfinite = true;
-      cx.src = A::zero();
+      cx.src = 0.0;
     }
 
-    V a, q;
+    double a, q;
     uint64_t dl, dr;
     solve_row(cx, vp, dpl, dpr, a, q, dl, dr);
 
@@ -684,8 +615,8 @@ __global__ __launch_bounds__(64 * (1 + ms_producers<VK>())) void k_ms(MsParams P
         const bool ld = valid && ((need_l && ghost_l) || (need_r && ghost_r));
         const uint32_t tag = (uint32_t)((t - 1) & 0xFF);
         const int rs = (int)((t - 1) % MS_RING);
-        V got = vp;
-        if (!wait_words<VK>(ld ? ring_ghost + (size_t)rs * MS_OWN : nullptr, ld, tag, got)) {
+        double got = vp;
+        if (!wait_words(ld ? ring_ghost + (size_t)rs * MS_OWN : nullptr, ld, tag, got)) {
           stalled = true;
           break;
         }
@@ -701,21 +632,21 @@ __global__ __launch_bounds__(64 * (1 + ms_producers<VK>())) void k_ms(MsParams P
         const uint32_t tag = (uint32_t)(t & 0xFF);
         const int rs = (int)(t % MS_RING);
         const bool ld = valid && ((need2_l && ghost_l) || (need2_r && ghost_r));
-        V got = a;
-        if (!wait_words<VK>(ld ? ring_ghost + (size_t)rs * MS_OWN : nullptr, ld, tag, got)) {
+        double got = a;
+        if (!wait_words(ld ? ring_ghost + (size_t)rs * MS_OWN : nullptr, ld, tag, got)) {
           stalled = true;
           break;
         }
         // Fixed ghost values take no same-row input.
-        F gl = cx.fl, gr = cx.fr;
+        double gl = cx.fl, gr = cx.fr;
         if (ld) {
           a = got;
-          gl = 0;
-          gr = 0;
+          gl = 0.0;
+          gr = 0.0;
         }
         const uint64_t fixed = ballot(ld);
         const uint64_t hl2 = cx.hl & ~fixed, hr2 = cx.hr & ~fixed;
-        q = lateral<VK>(a, gl, cx.dfl, gr, cx.dfr);
+        q = lateral(a, gl, gr);
         dl = spread((dirt_prev(cx, dpl) | edge_l) & ~fixed, hl2, hr2);
         dr = spread((dirt_prev(cx, dpr) | edge_r) & ~fixed, hl2, hr2);
         if ((dl | dr) & own_mask) {
@@ -727,11 +658,11 @@ __global__ __launch_bounds__(64 * (1 + ms_producers<VK>())) void k_ms(MsParams P
 
     // Results: the owned cells, their ring words, the progress word.
     if (owned) {
-      if constexpr (VK == VK_FF) P.vhi[i] = q.hi;
+      if constexpr (VK == VK_FF) P.vhi[i] = (float)q;
       else P.v64[i] = q;
-      st_word(pub + (size_t)(t % MS_RING) * MS_OWN, A::pack(q, (uint32_t)(t & 0xFF)));
-      if (!ADJ && cx.code == 0u) msum += A::wide(q);
-      rsum += A::wide(cx.src);
+      st_word(pub + (size_t)(t % MS_RING) * MS_OWN, pack(q, (uint32_t)(t & 0xFF)));
+      if (!ADJ && cx.code == 0u) msum += q;
+      rsum += cx.src;
     }
     if (lane == 0) st_i32(P.progress + s, (int32_t)(t + 1));
 
