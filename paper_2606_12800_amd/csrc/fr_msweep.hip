@@ -58,7 +58,10 @@
 // issues like a float32 one and takes the place of the five to eight of a
 // float-float step (float32 output, ms, float-float against float64: 8192^2
 // 18.9 -> 13.7, 16384^2 42.3 -> 32.0; float64 output 13.6 and 36.2 before
-// and after).
+// and after).  Likewise the next row's staged words are read while a row is
+// solved, and dirt spreads along a chain by one addition's carry, not a cell
+// a step (8192^2 13.8 -> 12.6, float64 13.6 -> 12.5; 16384^2 32.0 -> 30.4,
+// 36.2 -> 34.7).
 #include <math.h>
 
 #include "fr_ff.hpp"
@@ -251,10 +254,18 @@ __device__ __forceinline__ double lateral(double a, double wl, double wr) {
 }
 
 // Dirt carried along same-row chains (hl / hr: lanes taking input from the
-// left / right).
+// left / right).  A run of hl bits above a dirty lane is flooded by the carry
+// of one addition (bits of the run that the sum clears, and the seeds
+// themselves); leftward the same on reversed words.  Water does not turn round
+// within a row, so the second trip finds nothing new.
+__device__ __forceinline__ uint64_t flood(uint64_t d, uint64_t h) {
+  const uint64_t seed = (d << 1) & h;
+  return (h & ~(h + seed)) | seed;
+}
 __device__ __forceinline__ uint64_t spread(uint64_t d, uint64_t hl, uint64_t hr) {
+  const uint64_t hr_rev = __builtin_bitreverse64(hr);
   for (int it = 0; it < MS_LANES; ++it) {
-    const uint64_t n = d | ((d << 1) & hl) | ((d >> 1) & hr);
+    const uint64_t n = d | flood(d, hl) | __builtin_bitreverse64(flood(__builtin_bitreverse64(d), hr_rev));
     if (n == d) break;
     d = n;
   }
@@ -439,9 +450,8 @@ __global__ __launch_bounds__(64 * (1 + ms_producers<VK>())) void k_ms(MsParams P
         }
       }
       const int slot = (int)(t % MS_PR);
-      // Wait until the consumer has released the row this slot held (it
-      // keeps its current row and the one before).
-      while (lds_ld(&cons_row) <= t - MS_PR) {
+      // Wait until the consumer has taken the row this slot held.
+      while (lds_ld(&cons_row) < t - MS_PR) {
         if (lds_ld(&abort_flag)) return;
         __builtin_amdgcn_s_sleep(1);
       }
@@ -515,31 +525,50 @@ __global__ __launch_bounds__(64 * (1 + ms_producers<VK>())) void k_ms(MsParams P
     uint32_t code;
     uint64_t tm, t0, tp, hl, hr;
   };
-  // The staged rows t - 1 and t stay in the ring while row t is computed.
-  auto load_ctx = [&](int64_t tt) -> Ctx {
-    const Stage<VK>& S = stage[tt % MS_PR];
+  // Row tt's staged words are read while row tt - 1 is solved, the flag that
+  // they are there before them; where it was not up yet they are read again.
+  struct Staged {
+    F nm, n0, np, l, r;
+    float d;
+    double src;
+    uint32_t code;
+    int32_t row;
+  };
+  auto peek = [&](int slot) -> Staged {
+    const Stage<VK>& S = stage[slot];
+    Staged w;
+    w.row = lds_ld(&slot_row[slot]);
+    compiler_fence();
+    w.nm = S.nm[lane];
+    w.n0 = S.n0[lane];
+    w.np = S.np[lane];
+    w.l = S.l[lane];
+    w.r = S.r[lane];
+    w.d = S.d[lane];
+    w.src = S.src[lane];
+    w.code = S.code[lane];
+    return w;
+  };
+  F pnm = 0, pn0 = 0, pnp = 0;  // the previous row's fractions and correction
+  float pd = 0.0f;
+  auto load_ctx = [&](const Staged& w) -> Ctx {
     Ctx c;
-    const F nm = S.nm[lane], n0 = S.n0[lane], np = S.np[lane], l = S.l[lane], r = S.r[lane];
-    const float d = S.d[lane];
-    c.src = S.src[lane];
-    c.code = S.code[lane];
+    const F nm = w.nm, n0 = w.n0, np = w.np, l = w.l, r = w.r;
+    const float d = w.d;
+    c.src = w.src;
+    c.code = w.code;
     if (!ADJ) {
       // Forward: a cell takes a share of each upslope neighbour in the
       // previous row (that cell's own fractions) and of its same-row donors.
-      F pnm = 0, pn0 = 0, pnp = 0;
-      float pd = 0.0f;
-      if (tt > 0) {
-        const Stage<VK>& Q = stage[(tt - 1) % MS_PR];
-        pnm = Q.nm[lane];
-        pn0 = Q.n0[lane];
-        pnp = Q.np[lane];
-        pd = Q.d[lane];
-      }
       c.wl = sh_l(A::weight(pnp, pd));
       c.w0 = A::weight(pn0, pd);
       c.wr = sh_r(A::weight(pnm, pd));
       c.fl = sh_l(A::weight(r, d));
       c.fr = sh_r(A::weight(l, d));
+      pnm = nm;
+      pn0 = n0;
+      pnp = np;
+      pd = d;
     } else {
       // Adjoint: a cell takes its own fractions of its receivers' values.
       c.wl = A::weight(nm, d);
@@ -576,6 +605,8 @@ __global__ __launch_bounds__(64 * (1 + ms_producers<VK>())) void k_ms(MsParams P
   double msum = 0.0, rsum = 0.0;
   bool nonfinite = false, stalled = false;
 
+  int slot = 0;
+  Staged nx = peek(0);
   for (int64_t t = 0; t < nr && !stalled; ++t) {
     const int64_t y = row_of(t);
     const int64_t i = y * nc + ccol;
@@ -590,14 +621,16 @@ __global__ __launch_bounds__(64 * (1 + ms_producers<VK>())) void k_ms(MsParams P
         break;
       }
     }
-    // This row's staged inputs; rows up to t - 2 are released (forward, the
-    // previous row's fractions are read again with this row's).
-    const int slot = (int)(t % MS_PR);
-    while (lds_ld(&slot_row[slot]) != (int32_t)t) __builtin_amdgcn_s_sleep(1);
+    // This row's staged inputs, which releases their slot.
+    while (nx.row != (int32_t)t) {
+      __builtin_amdgcn_s_sleep(1);
+      nx = peek(slot);
+    }
+    Ctx cx = load_ctx(nx);
     compiler_fence();
-    Ctx cx = load_ctx(t);
-    compiler_fence();
-    if (lane == 0) lds_st(&cons_row, (int32_t)(t - 1));
+    if (lane == 0) lds_st(&cons_row, (int32_t)t);
+    slot = slot + 1 == MS_PR ? 0 : slot + 1;
+    nx = peek(slot);
     if (!valid) cx.src = 0.0;
     if (!A::finite(cx.src)) {
       nonfinite = true;
