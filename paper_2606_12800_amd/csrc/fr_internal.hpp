@@ -365,11 +365,17 @@ struct PeelGrid {
 };
 // A batch's workspace: this, its grids in schedule order, the schedule, each
 // grid's words, tile states, ring.
+// Grids are solved in groups, one after another, each with a queue of its own
+// (a slice of the ring): a grid belongs to group tile0 / span.
+constexpr int PEEL_GROUPS = 64;
 struct PeelBatch {
-  TileCtl ctl;
+  TileCtl ctl[PEEL_GROUPS];
   TileQueue queue;
   PeelGrid* grids;
   int32_t ngrids;
+  int32_t ngroups;
+  int32_t span;
+  int32_t lo[PEEL_GROUPS + 1];  // a group's first tile
 };
 inline __host__ __device__ size_t peel_align(size_t x) { return (x + 255) / 256 * 256; }
 inline __host__ __device__ size_t peel_batch_head_bytes(int64_t ntiles) {

@@ -99,3 +99,25 @@ def test_peel_batch_on_one_workgroup():
     assert relnorm(tiles[0]["q"].cpu().numpy(), oracle.accumulate_mfd(z, None, 1.1)) <= 1e-6
     _, want = oracle.accumulate_single(oracle.receivers(z2), None, z=z2)
     assert np.array_equal(tiles[1]["counts"].cpu().numpy().astype(np.uint64), want)
+
+
+def test_peel_batch_in_groups():
+    """More tiles than one group of a batch holds: 140 grids of 32 x 16 tiles with one elevation, every other one
+    D8 counts.  All of a kind give the same bits, and those are the oracle's within the bars."""
+    n, z = 1000, synth.dem(53, 1000, 1000)
+    zt = dev(z)
+    tiles = []
+    for i in range(140):
+        t = {"z": zt, "rule": "mfd" if i % 2 else "d8"}
+        if i % 2:
+            t["q"] = torch.empty((n, n), dtype=torch.float32, device="cuda")
+        else:
+            t["counts"] = torch.empty((n, n), dtype=torch.int64, device="cuda")
+        tiles.append(t)
+    fr.Batch(tiles).run()
+    for t in tiles[2:]:
+        k = "q" if t["rule"] == "mfd" else "counts"
+        assert torch.equal(t[k], tiles[1 if k == "q" else 0][k])
+    _, cnt = oracle.accumulate_single(oracle.receivers(z), None, z=z)
+    assert np.array_equal(tiles[0]["counts"].cpu().numpy().astype(np.int64), cnt.astype(np.int64))
+    assert relnorm(tiles[1]["q"].cpu().numpy(), oracle.accumulate_mfd(z, None, 1.1)) <= 1e-6
