@@ -46,7 +46,6 @@ MEASURED_TRAFFIC = {
         "d8_up": (1.3366e10, "profiles/d8_43360_hbm_traffic.md"),
         "d8_down": (3.3176e10, "profiles/d8_43360_hbm_traffic.md"),
     },
-    ("mfd", 16384, 16384): {"row_sweep": (5.3063e9, "profiles/mfd_16384_row_sweep.md")},
 }
 # Algorithmic bytes per cell of the secondary workloads' dominant kernel
 # (arrays visible at the C ABI, each touched once): MFD float32 sweep z 4 +
