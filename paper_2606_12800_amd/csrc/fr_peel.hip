@@ -777,12 +777,13 @@ __global__ __launch_bounds__(PT, RK == RK_MULTI && VK == VK_F64 ? 2 : 3) void k_
   }
 }
 
-// A batch's grids are solved in groups of about this many tiles (as many
-// groups as there are queues, at most).  In one queue the tiles' first turns
-// of all grids come before any second one, and what is woken meanwhile waits
-// behind them: 512 grids (286 thousand tiles) took 882 ms, in groups 177;
-// 128 grids (65 thousand tiles) are one group, 38 ms.
-constexpr int32_t GROUP_TILES = 65536;
+// A batch's grids are solved in groups of about this many tiles a workgroup
+// (as many groups as there are queues, at most).  In one queue the tiles'
+// first turns of all grids come before any second one, and what is woken
+// meanwhile waits behind them: 512 grids (286 thousand tiles, 768 workgroups)
+// took 882 ms, in groups 177; 128 grids (65 thousand tiles) are one group, 38
+// ms.
+constexpr int32_t GROUP_TILES = 85;
 
 __device__ __forceinline__ TileQueue group_queue(const PeelBatch* B, int g) {
   TileQueue Q = B->queue;
@@ -887,8 +888,8 @@ __device__ int64_t scan_inc(int64_t x, int64_t* sh) {
 // order with their first tile, words and queue, all in the workspace, laid
 // out as peel_batch_bytes() counts it.
 __global__ __launch_bounds__(1024) void k_peel_batch_setup(const fr_tile* tiles, int32_t ntiles, int order,
-                                                           int32_t limit, char* ws, size_t ws_bytes,
-                                                           int32_t* status) {
+                                                           int32_t limit, int32_t group, char* ws,
+                                                           size_t ws_bytes, int32_t* status) {
   __shared__ int64_t sh[1024];
   __shared__ int bad_sh;
   PeelBatch* B = reinterpret_cast<PeelBatch*>(ws);
@@ -977,7 +978,7 @@ __global__ __launch_bounds__(1024) void k_peel_batch_setup(const fr_tile* tiles,
     B->grids = grids;
     B->ngrids = fits ? ntiles : 0;
     B->span = (int32_t)(tile0 / (PEEL_GROUPS - 1) + 1);
-    if (B->span < GROUP_TILES) B->span = GROUP_TILES;
+    if (B->span < group) B->span = group;
     B->ngroups = fits ? (int32_t)(tile0 / B->span) + 1 : 0;
     for (int g = 0; g <= PEEL_GROUPS; ++g) B->lo[g] = (int32_t)tile0;
   }
@@ -1080,7 +1081,7 @@ hipError_t launch_peel_batch(const fr_tile* tiles_dev, int32_t ntiles, int order
   if (e != hipSuccess) return e;
   if (workers > 0 && grid > workers) grid = workers;
   hipLaunchKernelGGL(k_peel_batch_setup, dim3(1), dim3(1024), 0, s, tiles_dev, ntiles, order,
-                     limit, ws, ws_bytes, status);
+                     limit, (int32_t)(GROUP_TILES * grid), ws, ws_bytes, status);
   const PeelBatch* B = reinterpret_cast<const PeelBatch*>(ws);
   hipLaunchKernelGGL(k_peel_batch_init, dim3((unsigned)ntiles, BATCH_FILL_BLOCKS), dim3(256), 0, s, B);
   hipLaunchKernelGGL(k_peel_batch, dim3((unsigned)grid), dim3(PT), 0, s, B);
