@@ -58,6 +58,7 @@
 #include <math.h>
 
 #include "fr_queue.hpp"
+#include "fr_slopes.hpp"
 
 namespace fr {
 namespace {
@@ -175,23 +176,29 @@ template <>
 __device__ __forceinline__ void put_fractions<float>(Tile<float>& T, int at, uint32_t put, uint32_t m, float zc,
                                                      const float (&zk)[8], double p) {
   const float pf = (float)p;
-  float s[8], smax = 0.0f;
+  float s[8], smax = 0.0f, smin = INFINITY;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
     const float drop = zc - zk[k];
     s[k] = ((m >> k) & 1u) ? (nb_diag(k) ? drop * kInvSqrt2f : drop) : 0.0f;
     smax = fmaxf(smax, s[k]);
+    smin = fminf(smin, ((m >> k) & 1u) ? s[k] : INFINITY);
   }
-  const float ism = smax > 0.0f ? __builtin_amdgcn_rcpf(smax) : 0.0f;
+  if (smin < SLOPE_LO || smax > SLOPE_HI) {
+    wide_weights(zc, zk, m, 0xA5u, pf, s);
+  } else {
+    const float ism = smax > 0.0f ? __builtin_amdgcn_rcpf(smax) : 0.0f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      // s / smax, its rounding corrected once (the steepest gives 1 exactly).
+      const float q = s[k] * ism;
+      const float x = fmaf(fmaf(-q, smax, s[k]), ism, q);
+      s[k] = ((m >> k) & 1u) ? __builtin_amdgcn_exp2f(pf * __builtin_amdgcn_logf(x)) : 0.0f;
+    }
+  }
   float sum = 0.0f;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    // s / smax, its rounding corrected once (the steepest gives 1 exactly).
-    const float q = s[k] * ism;
-    const float x = fmaxf(fmaf(fmaf(-q, smax, s[k]), ism, q), 0x1p-126f);
-    s[k] = ((m >> k) & 1u) ? __builtin_amdgcn_exp2f(pf * __builtin_amdgcn_logf(x)) : 0.0f;
-    sum += s[k];
-  }
+  for (int k = 0; k < 8; ++k) sum += s[k];
   const float is = sum > 0.0f ? __builtin_amdgcn_rcpf(sum) : 0.0f;
   put &= m;
 #pragma unroll
