@@ -66,6 +66,7 @@
 
 #include "fr_ff.hpp"
 #include "fr_internal.hpp"
+#include "fr_slopes.hpp"
 
 namespace fr {
 namespace {
@@ -194,26 +195,28 @@ __device__ __forceinline__ Frac<VK, FLOW_UP> fractions(float zc, float znm, floa
     out.l = w[3] * iw;
     out.r = w[4] * iw;
   } else {
-    // Branch-free: t_j = 2^(p log2(s_j / s_max)) with the hardware log2 and
-    // exp2 (about 1 ulp each; the ratio is held above the float32 normal
-    // range, where t_j is negligible anyway), f_j = t_j / sum t.
-    float sl[5], smax = 0.0f;
+    // t_j = 2^(p log2(s_j / s_max)) with the hardware log2 and exp2 (about 1
+    // ulp each), f_j = t_j / sum t.
+    float sl[5], smax = 0.0f, smin = INFINITY;
 #pragma unroll
     for (int j = 0; j < 5; ++j) {
       const float drop = zc - zz[j];
       const float sj = dg[j] ? drop * kInvSqrt2f : drop;
       sl[j] = ((rcv >> j) & 1u) ? sj : 0.0f;
       smax = fmaxf(smax, sl[j]);
+      smin = fminf(smin, ((rcv >> j) & 1u) ? sj : INFINITY);
     }
-    const float ism = smax > 0.0f ? __builtin_amdgcn_rcpf(smax) : 0.0f;
     float tk[5], sum = 0.0f;
+    if (smin < SLOPE_LO || smax > SLOPE_HI) {
+      wide_weights(zc, zz, rcv, 0x5u, pf, tk);
+    } else {
+      const float ism = smax > 0.0f ? __builtin_amdgcn_rcpf(smax) : 0.0f;
 #pragma unroll
-    for (int o = 0; o < 5; ++o) {
-      const int j = ord[o];
-      const float r = fmaxf(sl[j] * ism, 0x1p-126f);
-      tk[j] = ((rcv >> j) & 1u) ? __builtin_amdgcn_exp2f(pf * __builtin_amdgcn_logf(r)) : 0.0f;
-      sum += tk[j];
+      for (int j = 0; j < 5; ++j)
+        tk[j] = ((rcv >> j) & 1u) ? __builtin_amdgcn_exp2f(pf * __builtin_amdgcn_logf(sl[j] * ism)) : 0.0f;
     }
+#pragma unroll
+    for (int o = 0; o < 5; ++o) sum += tk[ord[o]];
     const float isum = sum > 0.0f ? __builtin_amdgcn_rcpf(sum) : 0.0f;
     float f[5];
 #pragma unroll

@@ -34,7 +34,7 @@ __device__ __forceinline__ void wide_weights(float zc, const float (&zk)[N], uin
     const double x = s[k] * ism;  // above 2^-280
     const float l = __builtin_amdgcn_logf((float)__builtin_amdgcn_frexp_mant(x)) +
                     (float)__builtin_amdgcn_frexp_exp(x);
-    t[k] = ((m >> k) & 1u) ? __builtin_amdgcn_exp2f(p * l) : 0.0f;
+    t[k] = s[k] > 0.0 ? __builtin_amdgcn_exp2f(p * l) : 0.0f;
   }
 }
 

@@ -87,3 +87,38 @@ def test_workflow_and_batch_slopes(kind):
     tile = {"z": zt, "rule": "mfd", "rain": dev(rain), "q": torch.empty_like(zt)}
     fr.Batch([tile]).run()
     assert relnorm(tile["q"].cpu().numpy(), ref) <= 1e-6
+
+
+def ramp(kind, nr=90, nc=200):
+    """Every row lies below the one before it: no cell sends water up."""
+    u = synth.uniform(74, synth.STREAM_NOISE, nr * nc).reshape(nr, nc)
+    r = np.arange(nr)[:, None]
+    if kind == "subnormal":
+        return ((4 * (nr - r) + np.floor(3 * u)) * 2.0**-149).astype(np.float32)
+    z = 0.01 * (nr - r) + 0.004 * u
+    if kind == "sea":  # ordinary slopes that run out into subnormal ones
+        return np.where(r < 60, z, (4 * (nr - r) + np.floor(3 * u)) * 2.0**-149).astype(np.float32)
+    if kind == "nodata":
+        return np.where(r == nr - 1, np.float32(-np.finfo(np.float32).max), z).astype(np.float32)
+    # A drop above float32's largest value from row 39 to row 40.
+    high, low = 3e38 * (1 - 1e-3 * r - 1e-4 * u), -3e38 * (1 + 1e-3 * r + 1e-4 * u)
+    return np.where(r < 40, high, low).astype(np.float32)
+
+
+@pytest.mark.parametrize("up", [False, True])
+@pytest.mark.parametrize("p", [0.1, 1.1, 4.0])
+@pytest.mark.parametrize("kind", ["subnormal", "sea", "nodata", "peaks"])
+def test_row_sweep_slopes(kind, p, up):
+    print(f"row sweep slopes {kind} p {p}", flush=True)
+    z = ramp(kind)
+    z = np.ascontiguousarray(z[::-1]) if up else z
+    rain = synth.rain(75, *z.shape) + np.float32(2.0**-24)
+    zt, rt = dev(z), dev(rain)
+    code = fr.receivers(zt, "mfd")
+    q, _, mass = fr.accumulate(code, zt, rt, "mfd", torch.float32, mass=True, p=p)
+    assert fr.served_by() == "row_sweep"
+    rbar = fr.adjoint(code, rt, zt, "mfd", p=p)
+    assert fr.served_by() == "row_sweep"
+    assert relnorm(q.cpu().numpy(), oracle.accumulate_mfd(z, rain, p)) <= 1e-6
+    assert mass[0].item() == pytest.approx(float(rain.astype(np.float64).sum()), rel=1e-6)
+    assert relnorm(rbar.cpu().numpy(), oracle.adjoint_mfd(z, rain.astype(np.float64), p)) <= 1e-6
