@@ -217,11 +217,16 @@ __device__ __forceinline__ void put_fractions<double>(Tile<double>& T, int at, u
       smax = s[k] > smax ? s[k] : smax;
     }
   }
-  const double ism = smax > 0.0 ? 1.0 / smax : 0.0;
+  // s^p, as accurate as pow() (2^(p log2(s / s_max)), which is 1.25 times
+  // faster in all, loses about log2(s / s_max) units: 5e-15 against 6e-16
+  // over 40 binary orders).  Where it might overflow or vanish the slopes
+  // are divided by the steepest one's binade first, which is exact.
+  const int binade = smax > 0.0 ? ilogb(smax) : 0;
+  const int e = fabs((double)binade) * p < 500.0 ? 0 : binade;
   double sum = 0.0;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    s[k] = ((m >> k) & 1u) ? exp2(p * log2(s[k] * ism)) : 0.0;
+    s[k] = ((m >> k) & 1u) ? pow(ldexp(s[k], -e), p) : 0.0;
     sum += s[k];
   }
   const double is = sum > 0.0 ? 1.0 / sum : 0.0;
