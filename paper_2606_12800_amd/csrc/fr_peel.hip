@@ -447,7 +447,8 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const TileQueue& Q,
   for (int i = 0; i < 8; ++i) {
     const int r = or0 + i;
     double v = P.src64 ? bitsd(raw[i]) : (double)__uint_as_float((uint32_t)raw[i]);
-    if (!isfinite(v)) {
+    // A source the result's type cannot hold counts as non-finite.
+    if (VK == VK_FF ? !isfinite((float)v) : !isfinite(v)) {
       nonfinite = true;
       v = 0.0;
     }
