@@ -109,7 +109,8 @@ extern "C" {
 #define FR_ERR_BADCODE -7    /* device: code not 0..7/0xFF or leaves the grid */
 #define FR_ERR_TOOLARGE -8   /* grid larger than the library supports        */
 #define FR_ERR_STALL -9      /* device: a persistent launch's workgroups could
-                                not all run at once (barrier wait timed out) */
+                                not all run at once, or stopped making
+                                progress (a bounded wait ended)              */
 #define FR_ERR_CAPACITY -10  /* device: block iterations found more exits than
                                 their workspace holds                        */
 

@@ -179,12 +179,14 @@ PeelGrid peel_grid(int64_t nrows, int64_t ncols, const uint8_t* code, const floa
   return P;
 }
 
-TileQueue peel_queue(char* body, const PeelLayout& L, int32_t* status) {
+TileQueue peel_queue(RuleKind rk, char* body, const PeelLayout& L, int32_t* status) {
   TileQueue Q{};
   Q.state = reinterpret_cast<uint32_t*>(body + L.state);
   Q.ring = reinterpret_cast<uint64_t*>(body + L.ring);
   Q.ctl = reinterpret_cast<TileCtl*>(body + L.ctl);
   Q.status = status;
+  // Several receivers are strictly lower cells: no cycle.
+  Q.stuck = rk == RK_SINGLE ? FR_ERR_NOTDAG : FR_ERR_STALL;
   Q.cap = L.cap;
   return Q;
 }
@@ -858,7 +860,7 @@ int fr_accumulate(const float* z, const uint8_t* code, int64_t nrows, int64_t nc
     M.gate = nullptr;
     if (launch_mass(cfg.rk, cfg.vk, M, partial, kMassBlocks, mass_out, stream) != hipSuccess) return FR_ERR_HIP;
   }
-  if ((rc = enqueue_peel(cfg.rk, false, cfg.vk, Q, peel_queue(body, PL, dev_status), peel_gate, stream)) != FR_OK) return rc;
+  if ((rc = enqueue_peel(cfg.rk, false, cfg.vk, Q, peel_queue(cfg.rk, body, PL, dev_status), peel_gate, stream)) != FR_OK) return rc;
   if (mass_out) {
     ph = phase_begin("mass", stream);
     if (launch_peel_mass(Q, peel_partial, kMassBlocks, mass_out, peel_gate, stream) != hipSuccess) return FR_ERR_HIP;
@@ -1109,7 +1111,7 @@ int fr_accumulate_adjoint(const float* z, const uint8_t* code, int64_t nrows, in
   Q.src64 = s64;
   Q.out32 = o32;
   Q.out64 = o64;
-  return enqueue_peel(cfg.rk, true, cfg.vk, Q, peel_queue(body, PL, dev_status), peel_gate, stream);
+  return enqueue_peel(cfg.rk, true, cfg.vk, Q, peel_queue(cfg.rk, body, PL, dev_status), peel_gate, stream);
 }
 
 size_t fr_batched_workspace_bytes(const fr_tile* tiles_host, int32_t ntiles) {

@@ -329,7 +329,7 @@ struct TileCtl {
   uint32_t tail;   // next ticket to give out
   uint32_t pad1[31];
   uint32_t left;   // tiles left: 0 ends the work
-  uint32_t stop;   // 1: given up (a cycle)
+  uint32_t stop;   // 1: given up
   uint32_t pad2[30];
 };
 struct TileQueue {
@@ -337,6 +337,7 @@ struct TileQueue {
   uint64_t* ring;          // queue: ticket and tile
   TileCtl* ctl;
   int32_t* status;
+  int32_t stuck;           // reported when given up: FR_ERR_NOTDAG where codes may hold a cycle, else FR_ERR_STALL
   uint32_t cap;            // ring entries: twice the tiles (a tile waits in the queue at most once; the rest keeps
                            // a slow workgroup's ticket from being reached by the next round)
 };

@@ -985,6 +985,7 @@ __global__ __launch_bounds__(1024) void k_peel_batch_setup(const fr_tile* tiles,
     Q.ring = reinterpret_cast<uint64_t*>(ws + off);
     off += peel_align((size_t)Q.cap * sizeof(uint64_t));
     Q.status = status;
+    Q.stuck = FR_ERR_STALL;
     const bool fits = off <= ws_bytes && !bad;
     if (!fits && status) atomicCAS(status, 0, bad ? FR_ERR_ARG : FR_ERR_WORKSPACE);
     B->queue = Q;

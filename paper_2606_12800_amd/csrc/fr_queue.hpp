@@ -11,9 +11,10 @@ namespace fr {
 // Tile states (idle: 0).
 constexpr uint32_t ST_PENDING = 1, ST_RUNNING = 2, ST_DONE = 4;
 // A workgroup without a tile gives up when neither the queue nor the count of
-// tiles left has moved for this long (100 MHz ticks): the work depends on
-// itself (single receivers in a cycle, from malformed codes).
-constexpr long long STUCK_TICKS = 20000000;
+// tiles left has moved over this many of its own looks (0.27 s; a tile in
+// another workgroup's hands is done or let go within some 1000).  Looks, not a
+// clock's time: while the whole hardware queue is switched out nobody looks.
+constexpr uint32_t STUCK_LOOKS = 1u << 19;
 
 __device__ __forceinline__ uint64_t ld64(const uint64_t* p) {
   return (uint64_t)__hip_atomic_load(reinterpret_cast<unsigned long long*>(const_cast<uint64_t*>(p)),
@@ -37,8 +38,7 @@ __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)
 __device__ inline int32_t take_tile(const TileQueue& Q) {
   TileCtl* C = Q.ctl;
   uint32_t ticket = atomicAdd(&C->head, 1u);
-  uint32_t last_tail = 0, last_left = 0;
-  long long since = wall_clock64();
+  uint32_t last_tail = 0, last_left = 0, since = 0;
   for (uint32_t it = 0;; ++it) {
     const uint64_t w = ld64(Q.ring + ticket % Q.cap);
     const uint32_t at = (uint32_t)(w >> 32);
@@ -60,14 +60,13 @@ __device__ inline int32_t take_tile(const TileQueue& Q) {
     if (it % 4u != 0u) continue;
     const uint32_t left = ld32(&C->left), tail = ld32(&C->tail);
     if (left == 0u || ld32(&C->stop)) return -1;
-    const long long now = wall_clock64();
-    if (left != last_left || tail != last_tail || it == 0) {
+    if (left != last_left || tail != last_tail) {
       last_left = left;
       last_tail = tail;
-      since = now;
-    } else if (now - since > STUCK_TICKS) {
+      since = it;
+    } else if (it - since > STUCK_LOOKS) {
       atomicExch(&C->stop, 1u);
-      if (Q.status) atomicCAS(Q.status, 0, FR_ERR_NOTDAG);
+      if (Q.status) atomicCAS(Q.status, 0, Q.stuck);
       return -1;
     }
   }
