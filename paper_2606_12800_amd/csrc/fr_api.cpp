@@ -453,16 +453,32 @@ WsParams ws_params(int64_t nrows, int64_t ncols, const uint8_t* code, const floa
 
 // Wavefront-sweep passes, each followed by its control step: after the last
 // pass of the budget, cells still unfinished open C->fallback.
-int enqueue_ws(const EngineConfig& cfg, const WsParams& P, CallCtl* C, hipStream_t s) {
+int enqueue_ws(const EngineConfig& cfg, const WsParams& P, CallCtl* C, int passes, bool one_way, hipStream_t s) {
   const int ph = phase_begin("sweep", s);
-  if (launch_ws_setup(cfg, P, C, s) != hipSuccess) return FR_ERR_HIP;
-  for (int pass = 0; pass < kMaxSweepPasses; ++pass) {
+  if (launch_ws_setup(cfg, P, C, one_way, s) != hipSuccess) return FR_ERR_HIP;
+  for (int pass = 0; pass < passes; ++pass) {
     if (launch_ws_pass(cfg, P, C, pass == 0 ? 1 : 0, s) != hipSuccess ||
-        launch_ws_ctl(P, C, pass, pass == kMaxSweepPasses - 1, s) != hipSuccess)
+        launch_ws_ctl(P, C, pass, pass == passes - 1, s) != hipSuccess)
       return FR_ERR_HIP;
   }
   phase_end(ph, s);
   return FR_OK;
+}
+
+// Adjoint of single receivers on wide grids that drain along their columns:
+// the wavefront sweep takes about 2.6 us a row whatever its length (one strip
+// a wavefront), the peeling solver a time for each cell.  Measured on tilted
+// grids, D8, float32, peeling solver against sweep (ms): 4000 x 16384 8.1 and
+// 9.8, 4000 x 20000 9.6 and 9.6, 4000 x 32768 13.4 and 10.8, 20000 x 20000
+// 48.7 and 47.2, 6000 x 60000 29.0 and 16.5, 43360^2 205 and 134; short ones,
+// where the sweep's set-up counts: 300 x 24576 0.81 and 0.92, 300 x 32768
+// 1.04 and 0.93.  Where water runs both ways the sweep needs many passes (raw
+// 20000^2 426 ms, peeling solver 27), so a probe of 64 rows decides, and the
+// peeling solver serves what two passes leave.
+constexpr int kWideAdjointPasses = 2;
+bool wide_adjoint(RuleKind rk, int64_t nrows, int64_t ncols) {
+  return rk == RK_SINGLE && (g_path == FR_PATH_AUTO || g_path == FR_PATH_TILES) &&
+         ncols >= (nrows < 512 ? 28672 : 20000);
 }
 
 // Sets the control block's fallback word from the host's path choice
@@ -825,7 +841,7 @@ int fr_accumulate(const float* z, const uint8_t* code, int64_t nrows, int64_t nc
     W.vhi = q32;
     W.v64 = q64;
     W.cnt = counts_out;
-    if ((rc = enqueue_ws(cfg, W, C, stream)) != FR_OK) return rc;
+    if ((rc = enqueue_ws(cfg, W, C, kMaxSweepPasses, false, stream)) != FR_OK) return rc;
     peel_gate = &C->fallback;
   } else if (g_path == FR_PATH_ENGINE) {
     hipLaunchKernelGGL(k_open_gate, dim3(1), dim3(64), 0, stream, C);
@@ -1075,11 +1091,12 @@ int fr_accumulate_adjoint(const float* z, const uint8_t* code, int64_t nrows, in
   const double* s64 = dtype == FR_F64 ? static_cast<const double*>(qbar) : nullptr;
   float* o32 = dtype == FR_F32 ? static_cast<float*>(rbar_out) : nullptr;
   double* o64 = dtype == FR_F64 ? static_cast<double*>(rbar_out) : nullptr;
-  if (launch_ctl_init(C, g_path == FR_PATH_SWEEP ? FR_SERVED_SWEEP : FR_SERVED_ENGINE, stream) != hipSuccess)
+  const bool wide = wide_adjoint(cfg.rk, nrows, ncols);
+  if (launch_ctl_init(C, g_path == FR_PATH_SWEEP || wide ? FR_SERVED_SWEEP : FR_SERVED_ENGINE, stream) != hipSuccess)
     return FR_ERR_HIP;
   int rc = FR_OK;
-  // The row sweep where no cell sends against a row order, else the peeling
-  // solver.
+  // Several receivers: the row sweep where no cell sends against a row order,
+  // else the peeling solver.  One: that, or on wide grids the wavefront sweep.
   const int32_t* peel_gate = nullptr;
   const WsLayout WL = ws_layout(nrows, ncols, dtype);
   if (ms_applicable(cfg.rk, cfg.vk, ncols)) {
@@ -1093,13 +1110,13 @@ int fr_accumulate_adjoint(const float* z, const uint8_t* code, int64_t nrows, in
     const int ph = phase_begin("row_sweep", stream);
     if (launch_ms(cfg.vk, true, M, C, stream) != hipSuccess) return FR_ERR_HIP;
     phase_end(ph, stream);
-  } else if (g_path == FR_PATH_SWEEP) {
+  } else if (g_path == FR_PATH_SWEEP || wide) {
     WsParams W = ws_params(nrows, ncols, code, z, mfd_p, body, WL, cfg.vk, dev_status);
     W.src32 = s32;
     W.src64 = s64;
     W.vhi = o32;
     W.v64 = o64;
-    if ((rc = enqueue_ws(cfg, W, C, stream)) != FR_OK) return rc;
+    if ((rc = enqueue_ws(cfg, W, C, wide ? kWideAdjointPasses : kMaxSweepPasses, wide, stream)) != FR_OK) return rc;
     peel_gate = &C->fallback;
   } else if (g_path == FR_PATH_ENGINE) {
     hipLaunchKernelGGL(k_open_gate, dim3(1), dim3(64), 0, stream, C);

@@ -310,8 +310,10 @@ int64_t ws_strips(int64_t ncols);
 // control), then passes, each followed by a control step that counts the
 // cells finished, picks the next direction and stops the sequence (done,
 // cycle, device error) or, after the last pass of the budget, opens the
-// engine's gate.  Passes return at once after a stop.
-hipError_t launch_ws_setup(const EngineConfig& cfg, const WsParams& P, CallCtl* C, hipStream_t s);
+// gate of the path behind.  Passes return at once after a stop.  one_way: no
+// pass runs, and that gate opens, unless 31 of 32 sampled cells send water to
+// the same neighbouring row.
+hipError_t launch_ws_setup(const EngineConfig& cfg, const WsParams& P, CallCtl* C, bool one_way, hipStream_t s);
 hipError_t launch_ws_pass(const EngineConfig& cfg, const WsParams& P, const CallCtl* C, int first,
                           hipStream_t s);
 hipError_t launch_ws_ctl(const WsParams& P, CallCtl* C, int pass, bool last, hipStream_t s);

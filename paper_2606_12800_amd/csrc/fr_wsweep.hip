@@ -1153,14 +1153,19 @@ __global__ __launch_bounds__(128) void k_ws_pass(WsParams P, const CallCtl* C, i
 // finished nothing (a pass always finishes the highest unfinished cell of a
 // DAG), open the engine's gate when the budget is spent, otherwise pick the
 // direction (after one pass each way, the one whose last pass finished more
-// cells) -- and clears the pass counter and progress words for it.
-__global__ __launch_bounds__(256) void k_ws_ctl(WsParams P, CallCtl* C, int pass, int fwd, int last) {
+// cells) -- and clears the pass counter and progress words for it.  one_way:
+// receivers the probe must have counted on one side for any pass to run.
+__global__ __launch_bounds__(256) void k_ws_ctl(WsParams P, CallCtl* C, int pass, int fwd, int last, int64_t one_way) {
   __shared__ int s_run;
   if (threadIdx.x == 0) {
     int run = 0;
     if (pass < 0 && (C->ms_flags & MS_TAKEN)) {
       // The row sweep has served the call: no pass runs.
       C->sweep_stop = 1;
+    } else if (pass < 0 && (int64_t)(P.ctr[1] > P.ctr[2] ? P.ctr[1] : P.ctr[2]) < one_way) {
+      // Water runs both ways: the path behind the gate serves the call.
+      C->sweep_stop = 1;
+      C->fallback = 1;
     } else if (pass < 0) {
       // Visit first the rows holding most inputs: forward inputs are donors,
       // upstream of their receivers; adjoint inputs are the receivers.
@@ -1231,7 +1236,9 @@ __global__ __launch_bounds__(256) void k_ws_probe(WsParams P, int nsample) {
   }
 }
 
-__global__ __launch_bounds__(256) void k_fill_u64(uint64_t* p, int64_t n, uint64_t v) {
+// C: not after the control step stopped the sequence.
+__global__ __launch_bounds__(256) void k_fill_u64(uint64_t* p, int64_t n, uint64_t v, const CallCtl* C) {
+  if (C && C->sweep_stop) return;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
@@ -1251,23 +1258,26 @@ size_t ws_edge_words(int64_t nrows, int64_t ncols) {
   return (size_t)((ncols + WS_OWN - 1) / WS_OWN) * (size_t)nrows * 2 * WS_EW;
 }
 
-hipError_t launch_ws_setup(const EngineConfig& cfg, const WsParams& P, CallCtl* C, hipStream_t s) {
+hipError_t launch_ws_setup(const EngineConfig& cfg, const WsParams& P, CallCtl* C, bool one_way, hipStream_t s) {
   const int64_t n = (int64_t)ws_edge_words(P.nrows, P.ncols);
   int64_t b = (n + 255) / 256;
   if (b > 8192) b = 8192;
-  hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)(b < 1 ? 1 : b)), dim3(256), 0, s, P.edge, n, REC_EMPTY);
-  hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, s, reinterpret_cast<uint64_t*>(P.ctr), (int64_t)2, 0ull);
+  hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, s, reinterpret_cast<uint64_t*>(P.ctr), (int64_t)2, 0ull,
+                     (const CallCtl*)nullptr);
   const int ns = P.nrows < 64 ? (int)P.nrows : 64;
   if (cfg.rk == RK_SINGLE)
     hipLaunchKernelGGL(k_ws_probe<RK_SINGLE>, dim3(ns), dim3(256), 0, s, P, ns);
   else
     hipLaunchKernelGGL(k_ws_probe<RK_MULTI>, dim3(ns), dim3(256), 0, s, P, ns);
-  hipLaunchKernelGGL(k_ws_ctl, dim3(1), dim3(256), 0, s, P, C, -1, cfg.dir == DIR_FWD ? 1 : 0, 0);
+  hipLaunchKernelGGL(k_ws_ctl, dim3(1), dim3(256), 0, s, P, C, -1, cfg.dir == DIR_FWD ? 1 : 0, 0,
+                     one_way ? ns * P.ncols / 32 * 31 : (int64_t)0);
+  hipLaunchKernelGGL(k_fill_u64, dim3((unsigned)(b < 1 ? 1 : b)), dim3(256), 0, s, P.edge, n, REC_EMPTY,
+                     (const CallCtl*)C);
   return hipGetLastError();
 }
 
 hipError_t launch_ws_ctl(const WsParams& P, CallCtl* C, int pass, bool last, hipStream_t s) {
-  hipLaunchKernelGGL(k_ws_ctl, dim3(1), dim3(256), 0, s, P, C, pass, 0, last ? 1 : 0);
+  hipLaunchKernelGGL(k_ws_ctl, dim3(1), dim3(256), 0, s, P, C, pass, 0, last ? 1 : 0, (int64_t)0);
   return hipGetLastError();
 }
 
