@@ -533,6 +533,15 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const TileQueue& Q,
             v = fma(fmax(ADJ ? ok : -ok, 0.0), gk[k], v);
             if (CORRECT) give += fmax(ok, 0.0);
           }
+          if (VK == VK_F64 && !isfinite(v)) {
+            // An overflow, if it is among the inputs (0 * inf is not).
+            v = 0.0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              const double ok = (double)o[k], w = fmax(ADJ ? ok : -ok, 0.0);
+              if (w > 0.0) v = fma(w, gk[k], v);
+            }
+          }
           const double fix = CORRECT && give > 0.0 ? 2.0 - give : 1.0;
           const double own = gc;
           const double q = ADJ && CORRECT ? fma(v, fix, own) : own + v;

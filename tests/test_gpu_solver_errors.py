@@ -47,3 +47,42 @@ def test_rain_beyond_float32(tilt, path):
     assert e.value.code == fr.ERR_NONFINITE
     q, _, _ = fr.accumulate(code, zt, dev(rain), "mfd", torch.float64)
     assert q[low].item() == 1e39
+
+
+@pytest.mark.parametrize("path", ["engine", "sweep"])
+@pytest.mark.parametrize("rule", ["d8", "mfd"])
+def test_overflow_stays_downstream(rule, path):
+    """Float64 sums beyond its range are infinite there and where the values go, and no neighbour that takes nothing
+    from such a cell is touched."""
+    print(f"overflow {rule} {path}", flush=True)
+    nr, nc = 70, 130
+    # Steps: neighbours of one height exchange nothing.
+    z = np.floor(12 * synth.dem(82, nr, nc, tilt=0.0)).astype(np.float32)
+    x = np.ones(z.shape)
+    x.ravel()[np.argsort(synth.uniform(83, synth.STREAM_NOISE, z.size))[:2000]] = 1.5e308
+    zt, xt = dev(z), dev(x)
+    with np.errstate(over="ignore", invalid="ignore"):
+        if rule == "d8":
+            code = oracle.receivers(z)
+            back = oracle.adjoint_single(code, x, z=z)
+        else:
+            code, frac = oracle.mfd_fractions(z, 1.1)
+            back = oracle.adjoint_mfd(z, x, 1.1)
+            q = x.copy().ravel()
+            for i in np.argsort(-z.ravel(), kind="stable"):
+                for k, (dr, dc) in enumerate(oracle.OFFSETS):
+                    if (int(code.ravel()[i]) >> k) & 1:
+                        q[i + dr * nc + dc] += frac.reshape(-1, 8)[i, k] * q[i]
+            q = q.reshape(z.shape)
+    assert np.isinf(back).sum() > 20 and np.isfinite(back).sum() > 1000
+    with fr.accumulate_path(path):
+        got = [(fr.adjoint(dev(code), xt, zt if rule == "mfd" else None, rule), back)]
+        if rule == "mfd":
+            assert np.isinf(q).sum() > 20 and np.isfinite(q).sum() > 1000
+            got.append((fr.accumulate(dev(code), zt, xt, "mfd", torch.float64)[0], q))
+    for g, want in got:
+        g = g.cpu().numpy()
+        ok = np.isfinite(want)
+        assert np.array_equal(np.isfinite(g), ok)
+        assert not np.isnan(g).any()
+        assert np.max(np.abs(g[ok] / want[ok] - 1)) <= 1e-10
