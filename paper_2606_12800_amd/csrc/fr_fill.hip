@@ -51,14 +51,16 @@ constexpr uint32_t KEY_INF = 0xFF800000u;  // key of +inf
 constexpr int FILL_ROUNDS = 256;           // sweep rounds per tile and launch
 static_assert(FT == FILL_TILE + 2, "a window is a tile and its halo");
 
-// Order-preserving map of float32 to uint32 (-0 read as +0) and back.
+// Order-preserving map of float32 to uint32 (-0 read as +0) and back.  The
+// negative numbers' keys lie one above their inverted bits, which closes the
+// gap that -0 would leave: the next key is the next float32 everywhere.
 __device__ __forceinline__ uint32_t fkey(float x) {
   uint32_t b = __float_as_uint(x);
   if (b == 0x80000000u) b = 0;
-  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+  return (b & 0x80000000u) ? ~b + 1u : (b | 0x80000000u);
 }
 __device__ __forceinline__ float fval(uint32_t k) {
-  return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
+  return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~(k - 1u));
 }
 
 // Lane i receives x of lane i - 1, or of lane i + 1; the halo lanes at the

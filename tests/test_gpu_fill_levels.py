@@ -45,3 +45,18 @@ def test_fill_with_coarser_levels(kind, shape, rule, conn):
         f = fr.fill_depressions(torch.from_numpy(z).cuda(), rule, eps).cpu().numpy()
         ref = oracle.fill_depressions(z, conn, eps)
         assert np.array_equal(f.view(np.uint32), ref.view(np.uint32)), eps
+
+
+@pytest.mark.parametrize("rule,conn", [("d8", 8), ("d4", 4)])
+@pytest.mark.parametrize("shape", [(40, 40), (130, 200), (520, 600)])
+@pytest.mark.parametrize("kind", ["flat", "steps"])
+def test_fill_through_zero(kind, shape, rule, conn):
+    """Rises of 1.4e-45 from below 0 to above it, across tiles and coarser levels (compared by value: the oracle's
+    zero may be -0)."""
+    print(f"fill through zero {kind} {shape} {rule}", flush=True)
+    z = np.full(shape, -5.0) if kind == "flat" else np.floor(10 * terrain("noise", *shape))
+    z = (z * 2.0**-149).astype(np.float32)
+    f, n = fr.fill_depressions(torch.from_numpy(z).cuda(), rule, True, launches=True)
+    ref = oracle.fill_depressions(z, conn, True)
+    assert (ref < 0).any() and (ref > 0).any()
+    assert np.array_equal(f.cpu().numpy(), ref)
