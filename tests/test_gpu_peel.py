@@ -121,3 +121,17 @@ def test_peel_batch_in_groups():
     _, cnt = oracle.accumulate_single(oracle.receivers(z), None, z=z)
     assert np.array_equal(tiles[0]["counts"].cpu().numpy().astype(np.int64), cnt.astype(np.int64))
     assert relnorm(tiles[1]["q"].cpu().numpy(), oracle.accumulate_mfd(z, None, 1.1)) <= 1e-6
+
+
+@pytest.mark.parametrize("workers", [5, 6, 9])
+def test_peel_batch_few_workgroups_several_tile_columns(workers):
+    """A few workgroups on grids several tiles wide (as wide as the plan's 48 columns a workgroup allow)."""
+    print(f"batch on {workers} workgroups", flush=True)
+    z = terrain("filled", 300, 48 * workers, 55)
+    z2 = terrain("noise", 130, 200, 56)
+    tiles = [{"z": dev(z), "rule": "mfd", "q": torch.empty(z.shape, device="cuda")},
+             {"z": dev(z2), "rule": "d8", "counts": torch.empty(z2.shape, dtype=torch.int64, device="cuda")}]
+    fr.Batch(tiles).run(plan=fr.BatchPlan(workers, fr.ORDER_GIVEN))
+    assert relnorm(tiles[0]["q"].cpu().numpy(), oracle.accumulate_mfd(z, None, 1.1)) <= 1e-6
+    _, want = oracle.accumulate_single(oracle.receivers(z2), None, z=z2)
+    assert np.array_equal(tiles[1]["counts"].cpu().numpy().astype(np.uint64), want)

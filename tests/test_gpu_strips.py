@@ -50,3 +50,16 @@ def test_row_sweep_tiles(nr, nc):
     assert np.array_equal(gcnt.cpu().numpy().astype(np.int64), cnt.astype(np.int64))
     got = got.cpu().numpy().astype(np.float64)
     assert np.linalg.norm(got - q) / np.linalg.norm(q) <= 1e-6
+
+
+@pytest.mark.parametrize("nr,nc", [(97, 257), (1281, 3329), (2561, 2049), (5249, 1025), (8193, 257)])
+def test_row_sweep_tiles_per_cell(nr, nc):
+    """Float32 water of single receivers: within 1e-6 in every cell, float64 within 1e-10."""
+    print(f"row sweeps {nr}x{nc} per cell", flush=True)
+    z = synth.dem(62, nr, nc)
+    rain = synth.rain(62, nr, nc) + np.float32(2.0**-24)
+    code = oracle.receivers(z)
+    q, _ = oracle.accumulate_single(code, rain, z=z)
+    for dtype, bar in ((torch.float32, 1e-6), (torch.float64, 1e-10)):
+        got = fr.accumulate(dev(code), None, dev(rain), "d8", dtype)[0].cpu().numpy().astype(np.float64)
+        assert np.max(np.abs(got - q) / q) <= bar
