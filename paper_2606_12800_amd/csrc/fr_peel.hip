@@ -55,6 +55,7 @@
 // a cell passes on its water times 2 - sum f (float64), which makes up for
 // the rounding of its fractions to first order, as in the row sweep.  For
 // float64 results the fractions are float64.
+#include <limits.h>
 #include <math.h>
 
 #include "fr_queue.hpp"
@@ -72,7 +73,6 @@ constexpr int PH_RUN = 0, PH_STOP = 1;
 // let go: while other tiles are queued, and while none is.
 constexpr int LINGER_BUSY = 32, LINGER_IDLE = 96;
 __device__ constexpr float kInvSqrt2f = 0x1.6a09e6p-1f;
-__device__ constexpr double kSqrt2 = 1.4142135623730950488;
 
 __device__ __forceinline__ uint32_t l_ld(const uint32_t* p) {
   return __hip_atomic_load(const_cast<uint32_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -208,25 +208,20 @@ __device__ __forceinline__ void put_fractions<float>(Tile<float>& T, int at, uin
 template <>
 __device__ __forceinline__ void put_fractions<double>(Tile<double>& T, int at, uint32_t put, uint32_t m, float zc,
                                                       const float (&zk)[8], double p) {
-  double s[8], smax = 0.0;
+  // Relative to the highest drop's binade, so that no power overflows and the
+  // steepest ones do not vanish, whatever p.
+  double s[8];
+  int e = INT_MIN;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    s[k] = 0.0;
-    if ((m >> k) & 1u) {
-      s[k] = ((double)zc - (double)zk[k]) / (nb_diag(k) ? kSqrt2 : 1.0);
-      smax = s[k] > smax ? s[k] : smax;
-    }
+    s[k] = (double)zc - (double)zk[k];
+    const int ek = __builtin_amdgcn_frexp_exp(s[k]);
+    e = ((m >> k) & 1u) && ek > e ? ek : e;
   }
-  // s^p, as accurate as pow() (2^(p log2(s / s_max)), which is 1.25 times
-  // faster in all, loses about log2(s / s_max) units: 5e-15 against 6e-16
-  // over 40 binary orders).  Where it might overflow or vanish the slopes
-  // are divided by the steepest one's binade first, which is exact.
-  const int binade = smax > 0.0 ? ilogb(smax) : 0;
-  const int e = fabs((double)binade) * p < 500.0 ? 0 : binade;
   double sum = 0.0;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    s[k] = ((m >> k) & 1u) ? pow(ldexp(s[k], -e), p) : 0.0;
+    s[k] = ((m >> k) & 1u) ? slope_power(s[k], nb_diag(k), e, p) : 0.0;
     sum += s[k];
   }
   const double is = sum > 0.0 ? 1.0 / sum : 0.0;
