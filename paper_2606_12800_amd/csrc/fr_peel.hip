@@ -58,6 +58,8 @@
 #include <limits.h>
 #include <math.h>
 
+#include <type_traits>
+
 #include "fr_queue.hpp"
 #include "fr_slopes.hpp"
 
@@ -121,6 +123,7 @@ struct Tile {
   uint32_t done[64];               // final cells per lane (while loading: per row, two words)
   uint32_t wait[64];               // cells with an input from outside that is not final, per lane
   uint32_t phase, polls, queue_empty;
+  uint32_t gaps;                   // float64 fractions: some cell exchanges nothing with a neighbour
   int32_t tile, cmd;
   int32_t simd[5];                 // the wavefronts' SIMDs, the workgroup's slot
 };
@@ -324,6 +327,7 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const TileQueue& Q,
     T.phase = PH_RUN;
     T.polls = 0;
     T.queue_empty = 0;
+    T.gaps = 0;
   }
   __syncthreads();
 
@@ -398,6 +402,7 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const TileQueue& Q,
   // feeds a cell outside.
   {
     uint32_t m[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    bool gap = false;
 #pragma unroll 1
     for (int i = 0; i < 8; ++i) {
       const int r = 8 * wave + i, c = col_at(lane, r);
@@ -414,11 +419,13 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const TileQueue& Q,
         m[k] |= inside ? b : 0u;
         m[8] |= inside ? 0u : b;
         m[10] |= !inside && (ADJ ? o < (F)0 : o > (F)0) ? 1u << i : 0u;
+        if (sizeof(F) == 8) gap |= o == (F)0 && on_grid(r, c) && on_grid(r + nb_dr(k), c + nb_dc(k));
       }
       m[9] |= ((T.done[2 * r + (c >> 5)] >> (c & 31)) & 1u) << i;
     }
 #pragma unroll
     for (int k = 0; k < 11; ++k) T.mask[k][lane][wave] = (uint8_t)m[k];
+    if (gap) l_st(&T.gaps, 1u);
   }
   __syncthreads();
   // Roles: the peeling wavefront is the one on SIMD (workgroup slot mod 4).
@@ -479,81 +486,93 @@ __device__ __forceinline__ void peel_tile(const PeelGrid& P, const TileQueue& Q,
       uint32_t idle_from = 0;
       bool idle = false;
       uint32_t outside = l_ld(&T.wait[lane]);
-      for (;;) {
-        const uint32_t a1 = from_below(done), a2 = from_below(a1), a3 = from_below(a2);
-        const uint32_t b1 = from_above(done), b2 = from_above(b1), b3 = from_above(b2);
-        uint32_t wait = outside;
-        wait |= in[0] & ~(a3 << 1);
-        wait |= in[1] & ~(a2 << 1);
-        wait |= in[2] & ~(a1 << 1);
-        wait |= in[3] & ~a1;
-        wait |= in[4] & ~b1;
-        wait |= in[5] & ~(b1 >> 1);
-        wait |= in[6] & ~(b2 >> 1);
-        wait |= in[7] & ~(b3 >> 1);
-        // Read now, used in the next step.
-        outside = l_ld(&T.wait[lane]);
-        fence();
-        const uint32_t ready = ~(done | wait);
-        if (ballot(ready != 0u) == 0ull) {
-          if (ballot(done != ~0u) == 0ull) break;
-          // Nothing ready: wait for cells around the tile, for a few polls.
-          const uint32_t polls = l_ld(&T.polls);
-          if (!idle) {
-            idle = true;
-            idle_from = polls;
-          } else if (polls - idle_from > (uint32_t)(l_ld(&T.queue_empty) ? LINGER_IDLE : LINGER_BUSY)) {
-            break;
+      // GAPS: some neighbours exchange nothing (equal heights).  In float64
+      // such a neighbour, once overflowed, would add 0 * inf; a branch behind
+      // the sum costs 5%, so tiles without such cells have a loop without it.
+      auto peel = [&](auto gaps) __attribute__((always_inline)) {
+        constexpr bool GAPS = decltype(gaps)::value;
+        for (;;) {
+          const uint32_t a1 = from_below(done), a2 = from_below(a1), a3 = from_below(a2);
+          const uint32_t b1 = from_above(done), b2 = from_above(b1), b3 = from_above(b2);
+          uint32_t wait = outside;
+          wait |= in[0] & ~(a3 << 1);
+          wait |= in[1] & ~(a2 << 1);
+          wait |= in[2] & ~(a1 << 1);
+          wait |= in[3] & ~a1;
+          wait |= in[4] & ~b1;
+          wait |= in[5] & ~(b1 >> 1);
+          wait |= in[6] & ~(b2 >> 1);
+          wait |= in[7] & ~(b3 >> 1);
+          // Read now, used in the next step.
+          outside = l_ld(&T.wait[lane]);
+          fence();
+          const uint32_t ready = ~(done | wait);
+          if (ballot(ready != 0u) == 0ull) {
+            if (ballot(done != ~0u) == 0ull) break;
+            // Nothing ready: wait for cells around the tile, for a few polls.
+            const uint32_t polls = l_ld(&T.polls);
+            if (!idle) {
+              idle = true;
+              idle_from = polls;
+            } else if (polls - idle_from > (uint32_t)(l_ld(&T.queue_empty) ? LINGER_IDLE : LINGER_BUSY)) {
+              break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+            continue;
           }
-          __builtin_amdgcn_s_sleep(1);
-          continue;
-        }
-        idle = false;
-        if (ready != 0u) {
-          const int r = __builtin_ctz(ready), c = col_at(lane, r);
-          const int at = place<F>(r, c);
-          double* g0 = &T.g[0][0] + (at - Tile<F>::W - 1);  // the upper left neighbour
-          F o[8];
-          double gk[8];
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            o[k] = out_at(T, at, k);
-            gk[k] = g0[(nb_dr(k) + 1) * Tile<F>::W + nb_dc(k) + 1];
-          }
-          double& gc = g0[Tile<F>::W + 1];
-          double v = 0.0, give = 0.0;
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const double ok = (double)o[k];
-            v = fma(fmax(ADJ ? ok : -ok, 0.0), gk[k], v);
-            if (CORRECT) give += fmax(ok, 0.0);
-          }
-          if (VK == VK_F64 && !isfinite(v)) {
-            // An overflow, if it is among the inputs (0 * inf is not).
-            v = 0.0;
+          idle = false;
+          if (ready != 0u) {
+            const int r = __builtin_ctz(ready), c = col_at(lane, r);
+            const int at = place<F>(r, c);
+            double* g0 = &T.g[0][0] + (at - Tile<F>::W - 1);  // the upper left neighbour
+            F o[8];
+            double gk[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-              const double ok = (double)o[k], w = fmax(ADJ ? ok : -ok, 0.0);
-              if (w > 0.0) v = fma(w, gk[k], v);
+              o[k] = out_at(T, at, k);
+              gk[k] = g0[(nb_dr(k) + 1) * Tile<F>::W + nb_dc(k) + 1];
             }
+            double& gc = g0[Tile<F>::W + 1];
+            double v = 0.0, give = 0.0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+              if (RK == RK_SINGLE) {
+                v = (ADJ ? o[k] : -o[k]) > (F)0 ? gk[k] : v;  // one input
+                continue;
+              }
+              const double ok = (double)o[k];
+              v = fma(fmax(ADJ ? ok : -ok, 0.0), gk[k], v);
+              if (CORRECT) give += fmax(ok, 0.0);
+            }
+            if (GAPS && !isfinite(v)) {
+              // The inputs alone.
+              v = 0.0;
+#pragma unroll
+              for (int k = 0; k < 8; ++k) {
+                const double ok = (double)o[k], w = fmax(ADJ ? ok : -ok, 0.0);
+                if (w > 0.0) v = fma(w, gk[k], v);
+              }
+            }
+            const double fix = CORRECT && give > 0.0 ? 2.0 - give : 1.0;
+            const double own = gc;
+            const double q = ADJ && CORRECT ? fma(v, fix, own) : own + v;
+            gc = !ADJ && CORRECT ? q * fix : q;
+            done |= 1u << r;
+            fence();
+            l_st(&T.done[lane], done);
+            const int64_t cell = cell0 + (int64_t)((uint32_t)r * (uint32_t)nc + (uint32_t)c);
+            // Stored at once for the tiles that poll it; the publishing
+            // wavefront stores it again, to know when it has arrived.
+            if ((feeder >> r) & 1u) st64(P.word + cell, dword(gc));
+            if (VK == VK_F64) P.out64[cell] = q;
+            else if (!BATCH || P.out32) P.out32[cell] = (float)q;
+            else P.cnt[cell] = (uint64_t)q;  // whole numbers below 2^31
           }
-          const double fix = CORRECT && give > 0.0 ? 2.0 - give : 1.0;
-          const double own = gc;
-          const double q = ADJ && CORRECT ? fma(v, fix, own) : own + v;
-          gc = !ADJ && CORRECT ? q * fix : q;
-          done |= 1u << r;
           fence();
-          l_st(&T.done[lane], done);
-          const int64_t cell = cell0 + (int64_t)((uint32_t)r * (uint32_t)nc + (uint32_t)c);
-          // Stored at once for the tiles that poll it; the publishing
-          // wavefront stores it again, to know when it has arrived.
-          if ((feeder >> r) & 1u) st64(P.word + cell, dword(gc));
-          if (VK == VK_F64) P.out64[cell] = q;
-          else if (!BATCH || P.out32) P.out32[cell] = (float)q;
-          else P.cnt[cell] = (uint64_t)q;  // whole numbers below 2^31
         }
-        fence();
-      }
+      };
+      if (sizeof(F) == 8 && __builtin_amdgcn_readfirstlane((int)l_ld(&T.gaps)) != 0) peel(std::true_type{});
+      else peel(std::false_type{});
       l_st(&T.phase, PH_STOP);
       __builtin_amdgcn_s_setprio(0);
     } else if (role == 1) {
