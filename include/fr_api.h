@@ -416,7 +416,8 @@ int fr_set_autotune_cache(const char* path);
  * every direction (more than 1.5x an eighth of the cells draining sideways
  * or to the next row, on grids of 2^18 cells and more) or their exit list
  * overflows --, the row sweep for MFD where no cell sends against a row
- * order, the peeling engine otherwise), FR_PATH_SWEEP (wavefront sweep, then
+ * order, the wavefront sweep for D8/D4 adjoints of wide grids that drain
+ * along their columns, the peeling engine otherwise), FR_PATH_SWEEP (wavefront sweep, then
  * the engine),
  * FR_PATH_ENGINE (the peeling engine alone) or FR_PATH_TILES (the tile
  * forest for single receivers at once, for terrain known to drain in every
@@ -440,7 +441,8 @@ int fr_set_accumulate_path(int path);
  *                        direction: predicted by the code sample, or the
  *                        row sweeps' exit list overflowed)
  *   FR_SERVED_ROW_SWEEP  MFD row sweep
- *   FR_SERVED_SWEEP      wavefront sweep (FR_PATH_SWEEP)
+ *   FR_SERVED_SWEEP      wavefront sweep (FR_PATH_SWEEP; D8/D4 adjoints of
+ *                        wide grids)
  *   FR_SERVED_ENGINE     peeling engine
  *   FR_SERVED_NONE       not known
  * Reads the workspace's control block with a copy on `stream` and waits for

@@ -374,8 +374,9 @@ D8Params d8_params(const uint8_t* code, int64_t nrows, int64_t ncols, int th, co
 }
 
 // Row-sweep path for single-receiver codes, forward solve: phases A, B, C
-// and the mass reduction, every one of them ordered on the stream.  An exit
-// list overflow opens C->fallback, which the enqueued engine then serves.
+// and the mass reduction, every one of them ordered on the stream.  Where the
+// exit list overflows, or a probe predicts it, the tile forest enqueued behind
+// them serves the call.
 int enqueue_d8(const uint8_t* code, int64_t nrows, int64_t ncols, const void* rain, int rain_dtype, ValKind vk,
                float* q32, double* q64, uint64_t* cnt, double* mass_out, int32_t* status, char* body, CallCtl* C,
                bool tiles_only, hipStream_t s) {
@@ -800,8 +801,9 @@ int fr_accumulate(const float* z, const uint8_t* code, int64_t nrows, int64_t nc
   double* partial = reinterpret_cast<double*>(body + L.partial);
 
   // Every kernel below is ordered on the stream; decisions between them
-  // (exit overflow, sweep passes, the engine's gate) are taken on the
-  // device through the control block, which starts zeroed.
+  // (exit overflow, whether the row sweep applies, sweep passes, the gate of
+  // the path behind) are taken on the device through the control block, which
+  // starts zeroed.
   const bool tiles_only = cfg.rk == RK_SINGLE && g_path == FR_PATH_TILES;
   const bool multi = cfg.rk == RK_MULTI;
   const int32_t first = g_path == FR_PATH_ENGINE || (multi && g_path != FR_PATH_SWEEP) ? FR_SERVED_ENGINE

@@ -36,8 +36,9 @@
 // tiles with a cell that a tile's new values in launch k - 1 would lower (the
 // first list: all tiles); the host stops once a list is empty.
 //
-// Measured (epsilon variant, 8 neighbours, untilted fractal): 8192^2 17.8 -> 6.9 ms (96 launches -> 17
-// on the coarser grids and 53 on the grid), 2048^2 2.2 -> 1.2 ms.  The first
+// Measured (epsilon variant, 8 neighbours, untilted fractal): 8192^2 17.1 ->
+// 6.4 ms (96 launches with work -> 53 on the grid, after 16 on each of the two
+// coarser ones, which cost about 3 us each once a list is empty).  The first
 // launches over all 17424 tiles of 8192^2 take 1.2 ms each (four 33 KB
 // workgroups a compute unit), those of the chain's end about 40 us, one
 // tile's time.

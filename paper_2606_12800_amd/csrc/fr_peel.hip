@@ -35,12 +35,14 @@
 //     progress, and every wait is bounded.
 //
 // Measured (float32 water; the windowed wavefront sweep and, after 32 of its
-// passes, an engine with grid-wide barriers did this before): filled 2048^2
-// MFD route 731 -> 3.8 ms; forward and gradient on a filled 1200 x 1601 grid
-// 1203 -> 4.5 ms; tilted 4096^2 adjoint 21.5 -> 11.8 ms; 48 tiles of 64 to
-// 2048 cells a side 48.0 -> 15.4 ms.  A step takes 0.35 to 0.4 us (a chain of
-// lane rotations, 17 LDS reads and a sum of eight products), a value's way to
-// the next tile about 3 us, loading a tile 15 to 25 us.  Against that: with
+// passes, an engine with grid-wide barriers did this before; both timed in
+// turn in one run): filled 2048^2 MFD route 863 -> 3.9 ms; forward and gradient
+// on a filled 1200 x 1601 grid 1028 -> 4.6; tilted 4096^2 adjoint 29.1 -> 13.4;
+// 48 tiles of 64 to 2048 cells a side 72 -> 15.4.  Larger single grids, raw
+// terrain: 8192^2 MFD 963 -> 6.3 ms, 20000^2 2441 -> 51, 30000^2 7624 -> 398.
+// A step takes 0.35 to 0.4 us (a chain of lane rotations, 17 LDS reads and a
+// sum of eight products), a value's way to a tile already in LDS about 3 us,
+// loading a tile 15 to 25 us.  Against that: with
 // the peeling wavefronts left on one SIMD a step of three workgroups on a
 // compute unit took 1.0 us; tiles let go after 2 polls without news instead
 // of 32 were loaded up to 4 times as often (48 tiles: 30 ms); a queue for
@@ -51,10 +53,11 @@
 // float32 fractions fill a compute unit's LDS (53 KB each).
 //
 // Arithmetic: float64 sums.  For float32 results the fractions are float32,
-// t_j = (s_j / s_max)^p by the hardware log2 and exp2 and f_j = t_j / sum t;
+// t_j = (s_j / s_max)^p by the hardware log2 and exp2 and f_j = t_j / sum t
+// (cells with slopes outside 2^-60 to 2^60: from float64 drops and quotients);
 // a cell passes on its water times 2 - sum f (float64), which makes up for
 // the rounding of its fractions to first order, as in the row sweep.  For
-// float64 results the fractions are float64.
+// float64 results the fractions are float64 (slope_power()).
 #include <limits.h>
 #include <math.h>
 
