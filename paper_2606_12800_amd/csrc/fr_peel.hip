@@ -57,7 +57,7 @@
 // (cells with slopes outside 2^-60 to 2^60: from float64 drops and quotients);
 // a cell passes on its water times 2 - sum f (float64), which makes up for
 // the rounding of its fractions to first order, as in the row sweep.  For
-// float64 results the fractions are float64 (slope_power()).
+// float64 results the fractions are float64 (slope_log2(), slope_exp2()).
 #include <limits.h>
 #include <math.h>
 
@@ -214,21 +214,41 @@ __device__ __forceinline__ void put_fractions<float>(Tile<float>& T, int at, uin
 template <>
 __device__ __forceinline__ void put_fractions<double>(Tile<double>& T, int at, uint32_t put, uint32_t m, float zc,
                                                       const float (&zk)[8], double p) {
-  // Relative to the highest drop's binade, so that no power overflows and the
-  // steepest ones do not vanish, whatever p.
-  double s[8];
-  int e = INT_MIN;
+  double s[8], sum = 0.0;
+  if (p <= 500.0) {
+    // Relative to the highest drop's binade: the steepest power is at least
+    // 2^(-1.5 p).
+    int e = INT_MIN;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    s[k] = (double)zc - (double)zk[k];
-    const int ek = __builtin_amdgcn_frexp_exp(s[k]);
-    e = ((m >> k) & 1u) && ek > e ? ek : e;
-  }
-  double sum = 0.0;
+    for (int k = 0; k < 8; ++k) {
+      s[k] = (double)zc - (double)zk[k];
+      const int ek = __builtin_amdgcn_frexp_exp(s[k]);
+      e = ((m >> k) & 1u) && ek > e ? ek : e;
+    }
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    s[k] = ((m >> k) & 1u) ? slope_power(s[k], nb_diag(k), e, p) : 0.0;
-    sum += s[k];
+    for (int k = 0; k < 8; ++k) {
+      double l, ll;
+      slope_log2(s[k], nb_diag(k), e, l, ll);
+      s[k] = ((m >> k) & 1u) ? slope_exp2(l, ll, p) : 0.0;
+      sum += s[k];
+    }
+  } else {
+    // Relative to the steepest slope (2% slower in all).
+    double sl[8], top = -INFINITY, topl = 0.0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      slope_log2((double)zc - (double)zk[k], nb_diag(k), 0, s[k], sl[k]);
+      const bool higher = ((m >> k) & 1u) && (s[k] > top || (s[k] == top && sl[k] > topl));
+      top = higher ? s[k] : top;
+      topl = higher ? sl[k] : topl;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const double d = s[k] - top, b = d - s[k];
+      const double dl = ((s[k] - (d - b)) - (top + b)) + (sl[k] - topl);
+      s[k] = ((m >> k) & 1u) ? slope_exp2(d, dl, p) : 0.0;
+      sum += s[k];
+    }
   }
   const double is = sum > 0.0 ? 1.0 / sum : 0.0;
   put &= m;

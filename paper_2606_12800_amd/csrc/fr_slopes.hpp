@@ -39,16 +39,16 @@ __device__ __forceinline__ void wide_weights(float zc, const float (&zk)[N], uin
   }
 }
 
-// (drop / (diag ? sqrt 2 : 1) / 2^e)^p in float64, drop > 0, within 0.7 units
-// in the last place for any p whose result is not subnormal: log2 from the
-// series of atanh, log2 x = (2 / ln 2) atanh((x - 1) / (x + 1)), its quotient
-// and leading term in two doubles, then the series of 2^z on |z| <= 1/2.  The
-// diagonal is half a unit of the logarithm, and 2^e a whole number of them.
-// Against pow() on slopes: the slope itself is not rounded, and there are no
-// special cases: the peeling solver's float64 MFD takes 2.3 ms against 3.0 on a
-// raw 4096^2 grid and 33 against 90 on 12288^2, and its fractions are off by at
-// most 4.3e-16 against 5.9e-16 (p = 1.1, slopes over 40 binary orders).
-__device__ __forceinline__ double slope_power(double drop, bool diag, int e, double p) {
+// Powers (s / 2^e)^p in float64, s = drop / (diag ? sqrt 2 : 1), in two steps:
+// log2(s / 2^e) as l + ll, from the series of atanh, log2 x = (2 / ln 2)
+// atanh((x - 1) / (x + 1)), its quotient and leading term in two doubles; then
+// 2^(p (l + ll)) by the series of 2^z on |z| <= 1/2.  The diagonal is half a
+// unit of the logarithm, so no slope is rounded; a power is within 0.7 units in
+// the last place.  Against pow() on the slopes there are no special cases: the
+// peeling solver's float64 MFD takes 2.3 ms against 3.0 on a raw 4096^2 grid
+// and 37 against 90 on 12288^2, and its fractions are off by at most 4.3e-16
+// against 5.9e-16 (p = 1.1, slopes over 40 binary orders).
+__device__ __forceinline__ void slope_log2(double drop, bool diag, int e, double& l, double& ll) {
   double m = __builtin_amdgcn_frexp_mant(drop);  // [1/2, 1)
   int ex = __builtin_amdgcn_frexp_exp(drop) - e;
   if (m < 0x1.6a09e667f3bcdp-1) {  // to [1 / sqrt 2, sqrt 2)
@@ -79,7 +79,12 @@ __device__ __forceinline__ double slope_power(double drop, bool diag, int e, dou
   const double a = ch * f;
   const double al = fma(a * u, q, fma(ch, f, -a) + fma(ch, fl, cl * f));
   const double whole = (double)ex - (diag ? 0.5 : 0.0);  // 0 or at least |a|
-  const double l = whole + a, ll = (a - (l - whole)) + al;
+  const double h = whole + a, hl = (a - (h - whole)) + al;
+  l = h + hl;
+  ll = hl - (l - h);
+}
+// 2^(p (l + ll)), l below 1; below 2^-1100 it is 0.
+__device__ __forceinline__ double slope_exp2(double l, double ll, double p) {
   const double ph = p * l, pl = fma(p, ll, fma(p, l, -ph));
   const double y = ph + pl, n = rint(y);
   const double z = (y - n) + (pl - (y - ph));
@@ -98,7 +103,7 @@ __device__ __forceinline__ double slope_power(double drop, bool diag, int e, dou
   w = fma(w, z, 0x1.c6b08d704a0cp-5);
   w = fma(w, z, 0x1.ebfbdff82c58fp-3);
   w = fma(w, z, 0x1.62e42fefa39efp-1);
-  return ldexp(fma(w, z, 1.0), (int)n);
+  return y >= -1100.0 ? ldexp(fma(w, z, 1.0), (int)n) : 0.0;
 }
 
 }  // namespace fr

@@ -124,15 +124,17 @@ def test_row_sweep_slopes(kind, p, up):
     assert relnorm(rbar.cpu().numpy(), oracle.adjoint_mfd(z, rain.astype(np.float64), p)) <= 1e-6
 
 
-@pytest.mark.parametrize("p", [0.5, 1.1, 2.0, 60.0])
+@pytest.mark.parametrize("p", [0.5, 1.1, 2.0, 60.0, 3000.0])
 def test_float64_fractions(p):
     """Peaks with rain 1 over three pits each (one straight, two diagonal) whose only water is the peak's share, drops
-    over 40 binary orders (large powers: over one, of large drops): the shares against extended precision.  With u = 2^-53 a slope is within 2 u (its division
+    over 40 binary orders (large powers: shares over 60): the shares against extended precision.  With u = 2^-53 a slope is within 2 u (its division
     and sqrt 2), its power within 2 p u and pow's own 2 u, their sum within 2 u of that, reciprocal and product within
     u each: 2 (2 p + 2) + 4 units, whatever the slopes' ratio."""
     n = 128
     u = synth.uniform(76, synth.STREAM_NOISE, 3 * n * n).reshape(3, n, n)
-    drop = np.exp2(-40.0 * u if p < 10 else 120 - u).astype(np.float32)
+    drop = np.exp2(-40.0 * u if p < 10 else 120 - 60 * u / p).astype(np.float32)
+    if p >= 10:
+        drop[1:] *= np.float32(2**0.5)
     z = np.full((4 * n, 4 * n), 10, dtype=np.float32)
     z[1::4, 1::4] = 0
     at = [(0, 1), (2, 0), (2, 2)]
@@ -146,7 +148,7 @@ def test_float64_fractions(p):
     q = q.cpu().numpy()
     s = drop.astype(np.longdouble)
     s[1:] /= np.sqrt(np.longdouble(2))
-    w = s ** np.longdouble(p)
+    w = (s / s.max(0)) ** np.longdouble(p)
     want = w / w.sum(0)
     got = np.stack([q[r::4, c::4] for r, c in at]).astype(np.longdouble)
     err = float(np.max(np.abs(got - want) / want))
